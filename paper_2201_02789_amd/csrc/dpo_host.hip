@@ -133,6 +133,7 @@ struct CachedGraph {
   const void* fourth;
   int pgrid, cgrid, tgrid, fgrid, steps;
   Args args;
+  uint32_t* flags;
   hipGraphExec_t exec;
   uint64_t last_use;
 };
@@ -227,15 +228,16 @@ dpo_status add_node(hipGraph_t graph, hipGraphNode_t* prev, const void* fn, int 
 // K level steps (parent kernel, then child kernel unless flat, then the third
 // kernel if any: SSSP's thresholded children, on the parent kernel's grid, or
 // BFS's harvest; then the fourth if any: SSSP's harvest) and the advance of the
-// level base, as one instantiated graph.
+// level base, which reports to `flags` (host, pinned), as one instantiated
+// graph.
 dpo_status get_exec(Runtime& r, const void* parent, const void* child, const void* third,
                     const void* fourth, int pgrid, int cgrid, int tgrid, int fgrid, int steps,
-                    const Args& args, hipGraphExec_t* out, bool cached = true) {
+                    const Args& args, uint32_t* flags, hipGraphExec_t* out, bool cached = true) {
   for (auto& e : r.graphs) {
     if (!cached) break;
     if (e.parent == parent && e.child == child && e.third == third && e.fourth == fourth &&
         e.pgrid == pgrid && e.cgrid == cgrid && e.tgrid == tgrid && e.fgrid == fgrid &&
-        e.steps == steps && std::memcmp(&e.args, &args, sizeof(Args)) == 0) {
+        e.steps == steps && e.flags == flags && std::memcmp(&e.args, &args, sizeof(Args)) == 0) {
       e.last_use = ++r.tick;
       *out = e.exec;
       return DPO_OK;
@@ -257,7 +259,7 @@ dpo_status get_exec(Runtime& r, const void* parent, const void* child, const voi
   }
   State* st = a.st;
   uint32_t k = (uint32_t)steps;
-  void* aparams[] = {&st, &k};
+  void* aparams[] = {&st, &k, &flags};
   if (s == DPO_OK) s = add_node(graph, &prev, advance_kernel_ptr(), 1, 64, aparams);
   hipGraphExec_t exec;
   if (s == DPO_OK && hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess)
@@ -276,8 +278,8 @@ dpo_status get_exec(Runtime& r, const void* parent, const void* child, const voi
     r.graphs.erase(r.graphs.begin() + victim);
   }
   r.graphs.push_back(
-      CachedGraph{parent, child, third, fourth, pgrid, cgrid, tgrid, fgrid, steps, args, exec,
-                  ++r.tick});
+      CachedGraph{parent, child, third, fourth, pgrid, cgrid, tgrid, fgrid, steps, args, flags,
+                  exec, ++r.tick});
   *out = exec;
   return DPO_OK;
 }
@@ -465,11 +467,20 @@ dpo_status start_set(Runtime& r, SetRun& sr) {
   return DPO_OK;
 }
 
-// One replay of K level steps; reads back base, done, error, levels_run.
+// Start of a single traversal (one launch instead of init and admission).
+dpo_status start_single(Runtime& r, SetRun& sr, const Query& q) {
+  Query Q = q;
+  void* p[] = {&sr.a, &Q};
+  const int64_t work = std::max<int64_t>(sr.a.slots, 3 * (int64_t)sr.lay.ngroups_cap);
+  const int64_t grid = std::min<int64_t>(cdiv(work, PB), 8 * (int64_t)r.cu_count);
+  return hip_ok(hipLaunchKernel(start_kernel_ptr(sr.problem), dim3((unsigned)grid), dim3(PB), p, 0,
+                                sr.stream));
+}
+
+// One replay of K level steps; its last kernel reports base, done, error and
+// levels_run to the host's flags.
 dpo_status replay(Runtime& r, SetRun& sr, hipGraphExec_t exec) {
   if (hipGraphLaunch(exec, sr.stream) != hipSuccess) return DPO_ERR_HIP;
-  if (hipMemcpyAsync(r.host_flags, sr.a.st, 16, hipMemcpyDeviceToHost, sr.stream) != hipSuccess)
-    return DPO_ERR_HIP;
   if (hipStreamSynchronize(sr.stream) != hipSuccess) return DPO_ERR_HIP;
   if (r.host_flags[2] != 0) return (dpo_status)(-(int32_t)r.host_flags[2]);
   return DPO_OK;
@@ -480,7 +491,7 @@ dpo_status run_to_completion(Runtime& r, SetRun& sr, int64_t max_levels) {
   hipGraphExec_t exec;
   dpo_status s =
       get_exec(r, sr.parent, sr.child, sr.third, sr.fourth, sr.pgrid, sr.cgrid, sr.tgrid, sr.fgrid,
-               sr.steps, sr.a, &exec);
+               sr.steps, sr.a, r.host_flags, &exec);
   if (s != DPO_OK) return s;
   const int64_t max_replays = max_levels / sr.steps + 2;
   for (int64_t rep = 0; rep < max_replays; ++rep) {
@@ -532,12 +543,8 @@ dpo_status traverse(int problem, const dpo_csr* g, int32_t source, const dpo_opt
                   tm);
   if (s != DPO_OK) return s;
   if (tm && hipMemsetAsync(tm, 0, DPO_TIMING_BYTES, sr.stream) != hipSuccess) return DPO_ERR_HIP;
-  Query* hq = r.host_q;
-  hq[0] = Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source};
-  int32_t* hl = r.host_list;
-  hl[0] = 0;
-  if ((s = start_set(r, sr)) != DPO_OK) return s;
-  if ((s = admit(r, sr, hq, hl, 1, 0)) != DPO_OK) return s;
+  s = start_single(r, sr, Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source});
+  if (s != DPO_OK) return s;
   if ((s = run_to_completion(r, sr, g->n)) != DPO_OK) return s;
   return read_stats(r, sr, st);
 }
@@ -670,15 +677,11 @@ dpo_status traverse_noalloc(int problem, const dpo_csr* g, int32_t source, const
   s = prepare_set(r, problem, g, *o, round32(g->n), 1, out, ws, DPO_NOALLOC_SCRATCH_BYTES, stream,
                   false, &sr);
   if (s != DPO_OK) return s;
-  // the query record, its index and the admit prefix, from host stack memory
-  // (copied by the runtime before hipMemcpyAsync returns)
-  Query hq[1] = {Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source}};
-  int32_t hl[3] = {0, 0, 0};
-  // init_kernel clears the state, the level sets, the group counters and the
-  // statistics rows, and the admit kernels the outputs and visited state, so
-  // nothing left in the array by an earlier call is read
-  if ((s = start_set(r, sr)) != DPO_OK) return s;
-  if ((s = admit(r, sr, hq, hl, 1, 0)) != DPO_OK) return s;
+  // the start kernel clears the state, the level sets, the group counters, the
+  // outputs and the visited state, so nothing left in the array by an earlier
+  // call is read
+  s = start_single(r, sr, Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source});
+  if (s != DPO_OK) return s;
   uint32_t flags[4] = {0, 0, 0, 0};  // base, done, error, levels_run
   const int64_t max_replays = (int64_t)g->n / sr.steps + 2;
   State* st = sr.a.st;
@@ -686,7 +689,8 @@ dpo_status traverse_noalloc(int problem, const dpo_csr* g, int32_t source, const
   for (int64_t rep = 0; rep < max_replays; ++rep) {
     for (int i = 0; i < sr.steps; ++i)
       if ((s = launch_step(sr, (uint32_t)i)) != DPO_OK) return s;
-    void* ap[] = {&st, &k};
+    uint32_t* no_flags = nullptr;  // no pinned memory here: the flags are copied
+    void* ap[] = {&st, &k, &no_flags};
     if (hipLaunchKernel(advance_kernel_ptr(), dim3(1), dim3(64), ap, 0, sr.stream) != hipSuccess)
       return DPO_ERR_HIP;
     if (hipMemcpyAsync(flags, st, sizeof(flags), hipMemcpyDeviceToHost, sr.stream) != hipSuccess ||
@@ -839,8 +843,7 @@ dpo_status engine_step(dpo_engine* e) {
   }
   if (e->running > 0) {
     if (hipGraphLaunch(e->exec, sr.stream) != hipSuccess) return DPO_ERR_HIP;
-    if (hipMemcpyAsync(e->hflags, sr.a.st, 16, hipMemcpyDeviceToHost, sr.stream) != hipSuccess ||
-        hipMemcpyAsync(e->hq, sr.a.q, (size_t)e->max_queries * sizeof(Query),
+    if (hipMemcpyAsync(e->hq, sr.a.q, (size_t)e->max_queries * sizeof(Query),
                        hipMemcpyDeviceToHost, sr.stream) != hipSuccess)
       return DPO_ERR_HIP;
     e->inflight = true;
@@ -909,7 +912,8 @@ dpo_status dpo_engine_create(const dpo_arena* arena, int32_t kind, const dpo_opt
     e->hlist = (int32_t*)(e->hq + max_queries);
     std::memset(e->hq, 0, (size_t)max_queries * sizeof(Query));
     s = get_exec(r, e->sr.parent, e->sr.child, e->sr.third, e->sr.fourth, e->sr.pgrid,
-                 e->sr.cgrid, e->sr.tgrid, e->sr.fgrid, e->sr.steps, e->sr.a, &e->exec, false);
+                 e->sr.cgrid, e->sr.tgrid, e->sr.fgrid, e->sr.steps, e->sr.a, e->hflags,
+                 &e->exec, false);
   }
   if (s == DPO_OK) s = start_set(r, e->sr);
   if (s == DPO_OK && e->sr.a.hint) {

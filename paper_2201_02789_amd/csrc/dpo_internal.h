@@ -145,6 +145,7 @@ const void* child_kernel_ptr(int problem, bool timed = false, bool nt = false);
 const void* serial_kernel_ptr(int problem, int gran, bool timed = false);
 const void* harvest_kernel_ptr(int problem, bool timed = false);
 const void* init_kernel_ptr(int problem);
+const void* start_kernel_ptr(int problem);
 const void* admit_kernel_ptr(int problem);
 const void* admit_sources_kernel_ptr();
 const void* clear_found_kernel_ptr();

@@ -1388,6 +1388,55 @@ __global__ __launch_bounds__(PB) void init_kernel(Args a) {
   for (uint32_t i = gid; i < sizeof(State) / 4; i += gsz) stw[i] = 0;
 }
 
+// Start of a single traversal in one launch: level sets, counters, outputs and
+// visited state, the query's record and its source as frontier 0.  No
+// workgroup reads what another writes, so what the batch and serving paths do
+// with an init kernel, two uploads and two admit kernels needs no order here;
+// the query travels by value.  Bound by its stores (s22: 26 MB); on small
+// graphs by the launch itself, which is why it is one.
+template <int P>
+__global__ __launch_bounds__(PB) void start_kernel(Args a, Query Q) {
+  const uint32_t gsz = gridDim.x * PB;
+  const uint32_t gid = blockIdx.x * PB + threadIdx.x;
+  const uint32_t src = (uint32_t)Q.src, n = (uint32_t)Q.n;
+  for (uint32_t v = gid; v < n; v += gsz) {
+    if (P == PROB_BFS) {
+      a.level[v] = (v == src) ? 0 : -1;
+    } else {
+      const uint32_t d = (v == src) ? 0u : 0xFFFFFFFFu;
+      a.dist[v] = d;
+      a.dist2[v] = d;
+      if (!a.hint) a.visit[v] = 0u;  // iteration stamps
+    }
+  }
+  for (uint32_t i = gid; i < (uint32_t)a.vwords; i += gsz) {
+    a.qmap[i] = 0;
+    if (P == PROB_BFS) {  // every bitmap in use holds the source
+      const uint32_t x = (i == src >> 5) ? (1u << (src & 31)) : 0u;
+      for (uint32_t h = 0; h < (a.hint ? 2u + NHINT : 2u); ++h) a.visit[(size_t)h * a.vwords + i] = x;
+    }
+  }
+  if (a.hint) {  // nothing found yet
+    uint32_t* f = (uint32_t*)a.found;
+    for (uint32_t i = gid; i < (uint32_t)a.vwords * 8u; i += gsz) f[i] = 0u;
+  }
+  for (uint32_t i = gid; i < 3u * (uint32_t)a.ngroups_cap; i += gsz) {
+    a.grp_packed[i] = 0;
+    a.grp_done[i] = 0;
+  }
+  if (a.count_stats)
+    for (uint32_t i = gid; i < (uint32_t)(MAX_GRID * NSTAT); i += gsz) a.stats[i] = 0;
+  // frontier 0 is the source alone, in the overflow queue: the fills of
+  // frontier L are in set (L + 2) % 3
+  uint32_t* stw = (uint32_t*)a.st;
+  const uint32_t fill = (uint32_t)(&a.st->set[2].fcnt[NQF] - stw);
+  for (uint32_t i = gid; i < sizeof(State) / 4; i += gsz) stw[i] = i == fill ? 1u : 0u;
+  if (gid == 0) {
+    a.q[0] = Q;
+    a.front0[(size_t)NQF * a.fcap] = Q.src;
+  }
+}
+
 // Starts the queries list[0 .. count) at level index L = st->base: their
 // outputs set to "unreached" except the source, their visit state cleared and
 // their 32-slot chunks mapped to them.  Query list[k] is served by the
@@ -1478,8 +1527,17 @@ __global__ void admit_sources_kernel(Args a, const int32_t* list, int32_t count)
   if (k == 0) st->done = 0;
 }
 
-__global__ void advance_kernel(State* st, uint32_t steps) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) st->base += steps;
+// End of a replay: the level base moves on, and base, done, error and
+// levels_run go to the host's flags (pinned memory) with this kernel, so that
+// no copy has to follow the replay.
+__global__ void advance_kernel(State* st, uint32_t steps, uint32_t* flags) {
+  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  const uint32_t base = st->base + steps;
+  st->base = base;
+  if (!flags) return;
+  const uint32_t v[4] = {base, st->done, st->error, st->levels_run};
+  for (int i = 0; i < 4; ++i)
+    __hip_atomic_store(&flags[i], v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---------------------------------------------------------------- tables
@@ -1537,6 +1595,11 @@ const void* child_kernel_ptr(int problem, bool timed, bool nt) {
 }
 
 const void* init_kernel_ptr(int) { return (const void*)init_kernel; }
+
+const void* start_kernel_ptr(int problem) {
+  return problem == PROB_BFS ? (const void*)start_kernel<PROB_BFS>
+                             : (const void*)start_kernel<PROB_SSSP>;
+}
 
 const void* admit_kernel_ptr(int problem) {
   return problem == PROB_BFS ? (const void*)admit_kernel<PROB_BFS>
