@@ -25,8 +25,9 @@
  *   - The CSR graph must be symmetric for the results to be shortest paths of
  *     an undirected graph; the kernels follow out-edges only.
  *   - Work is enqueued on `stream`.  The traversal calls synchronise `stream`
- *     once per `steps_per_replay` level steps to read the done flag, so they
- *     return only when the traversal has finished and outputs are final.
+ *     once per `steps_per_replay` level steps to read the done flag, or wait
+ *     for the flag of each run of narrow levels, so they return only when the
+ *     traversal has finished and outputs are final.
  *   - Errors are return codes, never exceptions.  Argument errors are found on
  *     the host before anything is enqueued.  Device-detected errors (queue
  *     capacity, a vertex id out of range) are read back at the end of the
@@ -81,7 +82,10 @@ typedef struct {
   int32_t agg;              /* dpo_agg (Sec. II-B, V-A)                             */
   int32_t agg_blocks;       /* k >= 2 for DPO_AGG_MULTIBLOCK (e.g. 4 or 16)         */
   int32_t child_block;      /* original child block size bDim in {64, 128, 256}    */
-  int32_t steps_per_replay; /* level steps per HIP-graph replay; 0 = 16            */
+  int32_t steps_per_replay; /* level steps per HIP-graph replay; 0 = 16.  A single
+                               traversal that needs no replays (nested, aggregated,
+                               without counters) launches its steps as they come
+                               due instead; results are the same               */
   int32_t agg_threshold;    /* aggregation threshold (Sec. V-B), wave and block
                                granularity only: when fewer than this many parents
                                of the wave / block launch, each launches its own

@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <deque>
 #include <map>
 #include <cstdlib>
@@ -23,6 +24,7 @@ namespace {
 
 constexpr int kDefaultSteps = 16;
 constexpr int kMaxCachedGraphs = 64;
+constexpr int kStepsAhead = 4;  // dpo_bfs_noalloc: level steps per look at the flags
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -150,7 +152,8 @@ struct Runtime {
   std::mutex mu;
   std::vector<CachedGraph> graphs;
   uint64_t tick = 0;
-  uint32_t* host_flags = nullptr;  // pinned: base, done, error, levels_run
+  uint32_t* host_flags = nullptr;  // pinned: base, done, error, levels_run; [8]: verdict
+  uint32_t ticket = 0;             // of the last narrow launch (24 bits)
   unsigned long long* host_stats = nullptr;  // pinned: MAX_GRID * NSTAT
   Query* host_q = nullptr;                   // pinned: MAX_QUERIES query records
   int32_t* host_list = nullptr;              // pinned: MAX_QUERIES query indices + prefix
@@ -502,6 +505,87 @@ dpo_status run_to_completion(Runtime& r, SetRun& sr, int64_t max_levels) {
   return DPO_ERR_TIMEOUT;
 }
 
+// The kernels of one level step, launched one by one.
+dpo_status launch_step(SetRun& sr, uint32_t step) {
+  void* p[] = {&sr.a, &step};
+  if (hipLaunchKernel(sr.parent, dim3((unsigned)sr.pgrid), dim3(PB), p, 0, sr.stream) != hipSuccess)
+    return DPO_ERR_HIP;
+  if (sr.child &&
+      hipLaunchKernel(sr.child, dim3((unsigned)sr.cgrid), dim3(PB), p, 0, sr.stream) != hipSuccess)
+    return DPO_ERR_HIP;
+  if (sr.third &&
+      hipLaunchKernel(sr.third, dim3((unsigned)sr.tgrid), dim3(PB), p, 0, sr.stream) != hipSuccess)
+    return DPO_ERR_HIP;
+  if (sr.fourth &&
+      hipLaunchKernel(sr.fourth, dim3((unsigned)sr.fgrid), dim3(PB), p, 0, sr.stream) != hipSuccess)
+    return DPO_ERR_HIP;
+  return DPO_OK;
+}
+
+// The narrow levels' kernel: one workgroup.  adv: level steps run since the
+// last one.  verdict: pinned word it reports to, or nullptr.
+dpo_status launch_narrow(SetRun& sr, uint32_t adv, uint32_t ticket, uint32_t* verdict) {
+  void* p[] = {&sr.a, &adv, &ticket, &verdict};
+  return hip_ok(hipLaunchKernel(narrow_kernel_ptr(sr.problem, sr.a.slots), dim3(1), dim3(NARROW_BLOCK), p, 0,
+                                sr.stream));
+}
+
+// Narrow levels run in one workgroup where their kernel has a form for the
+// graph, except where the caller asks for the level step itself: the paper's
+// two literal forms (flat, and one grid per parent), its counters, its phase
+// timing.
+bool use_narrow(const SetRun& sr, const dpo_options& o, bool stats, bool timed) {
+  return narrow_kernel_ptr(sr.problem, sr.a.slots) && o.mode == DPO_MODE_NESTED &&
+         o.agg != DPO_AGG_NONE && !stats && !timed;
+}
+
+// Waits for the verdict of narrow launch `ticket`.  The word is polled: a
+// stream synchronisation per narrow launch would cost more than most of them.
+// Every 2 ms the stream is asked too, so that a failed launch ends the wait.
+dpo_status wait_verdict(const uint32_t* verdict, uint32_t ticket, hipStream_t stream, uint32_t* out) {
+  auto look = [&] {
+    *out = __atomic_load_n(verdict, __ATOMIC_ACQUIRE);
+    return (*out >> 8) == ticket;
+  };
+  auto asked = std::chrono::steady_clock::now();
+  for (uint32_t i = 1;; ++i) {
+    if (look()) return DPO_OK;
+    if (i % 256) continue;
+    const auto now = std::chrono::steady_clock::now();
+    if (now - asked < std::chrono::milliseconds(2)) continue;
+    asked = now;
+    const hipError_t e = hipStreamQuery(stream);
+    if (e == hipErrorNotReady) {
+      (void)hipGetLastError();  // not an error of the caller's
+      continue;
+    }
+    return e == hipSuccess && look() ? DPO_OK : DPO_ERR_HIP;
+  }
+}
+
+// A single traversal: narrow levels in one launch, a level step for each wide
+// one.  The host learns from the narrow kernel's verdict whether a level step
+// follows, so nothing is launched that has nothing to do.
+dpo_status run_narrow_and_wide(Runtime& r, SetRun& sr, int64_t max_levels) {
+  uint32_t* verdict = r.host_flags + 8;
+  uint32_t adv = 0;
+  for (int64_t rep = 0; rep < max_levels + 2; ++rep) {
+    r.ticket = (r.ticket + 1) & 0xFFFFFFu;
+    dpo_status s = launch_narrow(sr, adv, r.ticket, verdict);
+    uint32_t v = 0;
+    if (s == DPO_OK) s = wait_verdict(verdict, r.ticket, sr.stream, &v);
+    if (s != DPO_OK) return s;
+    const uint32_t code = v & 15u;
+    if (code == V_DONE || code == V_ERROR) {
+      if (hipStreamSynchronize(sr.stream) != hipSuccess) return DPO_ERR_HIP;
+      return code == V_DONE ? DPO_OK : (dpo_status)(-(int32_t)((v >> 4) & 15u));
+    }
+    adv = code == V_WIDE ? 1u : 0u;
+    if (adv && (s = launch_step(sr, 0u)) != DPO_OK) return s;
+  }
+  return DPO_ERR_TIMEOUT;
+}
+
 dpo_status read_stats(Runtime& r, SetRun& sr, dpo_stats* st) {
   if (!st) return DPO_OK;
   if (hipMemcpyAsync(r.host_stats, sr.a.stats, (size_t)MAX_GRID * NSTAT * 8, hipMemcpyDeviceToHost,
@@ -545,8 +629,9 @@ dpo_status traverse(int problem, const dpo_csr* g, int32_t source, const dpo_opt
   if (tm && hipMemsetAsync(tm, 0, DPO_TIMING_BYTES, sr.stream) != hipSuccess) return DPO_ERR_HIP;
   s = start_single(r, sr, Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source});
   if (s != DPO_OK) return s;
-  if ((s = run_to_completion(r, sr, g->n)) != DPO_OK) return s;
-  return read_stats(r, sr, st);
+  s = use_narrow(sr, *o, st != nullptr, tm != nullptr) ? run_narrow_and_wide(r, sr, g->n)
+                                                   : run_to_completion(r, sr, g->n);
+  return s != DPO_OK ? s : read_stats(r, sr, st);
 }
 
 dpo_status check_arena(const dpo_arena* ar, bool need_w) {
@@ -640,24 +725,6 @@ dpo_status scratch_of_current_device(void** out) {
   return DPO_OK;
 }
 
-// One level step launched kernel by kernel (no HIP graph: instantiating one
-// allocates).
-dpo_status launch_step(SetRun& sr, uint32_t step) {
-  void* p[] = {&sr.a, &step};
-  if (hipLaunchKernel(sr.parent, dim3((unsigned)sr.pgrid), dim3(PB), p, 0, sr.stream) != hipSuccess)
-    return DPO_ERR_HIP;
-  if (sr.child &&
-      hipLaunchKernel(sr.child, dim3((unsigned)sr.cgrid), dim3(PB), p, 0, sr.stream) != hipSuccess)
-    return DPO_ERR_HIP;
-  if (sr.third &&
-      hipLaunchKernel(sr.third, dim3((unsigned)sr.tgrid), dim3(PB), p, 0, sr.stream) != hipSuccess)
-    return DPO_ERR_HIP;
-  if (sr.fourth &&
-      hipLaunchKernel(sr.fourth, dim3((unsigned)sr.fgrid), dim3(PB), p, 0, sr.stream) != hipSuccess)
-    return DPO_ERR_HIP;
-  return DPO_OK;
-}
-
 dpo_status traverse_noalloc(int problem, const dpo_csr* g, int32_t source, const dpo_options* o,
                             void* out, void* stream) {
   if (!o || !out) return DPO_ERR_ARG;
@@ -683,15 +750,22 @@ dpo_status traverse_noalloc(int problem, const dpo_csr* g, int32_t source, const
   s = start_single(r, sr, Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source});
   if (s != DPO_OK) return s;
   uint32_t flags[4] = {0, 0, 0, 0};  // base, done, error, levels_run
-  const int64_t max_replays = (int64_t)g->n / sr.steps + 2;
   State* st = sr.a.st;
   uint32_t k = (uint32_t)sr.steps;
+  uint32_t* no_flags = nullptr;  // no pinned memory here: the flags are copied
+  // narrow levels run in one workgroup; a few wide ones are launched ahead of
+  // each look at the flags (those past the end find nothing to do)
+  const bool narrow = use_narrow(sr, *o, false, false);
+  const int ahead = narrow ? std::min(sr.steps, kStepsAhead) : sr.steps;
+  const int64_t max_replays = (int64_t)g->n / ahead + 2;
+  if (narrow && (s = launch_narrow(sr, 0u, 0u, nullptr)) != DPO_OK) return s;
   for (int64_t rep = 0; rep < max_replays; ++rep) {
-    for (int i = 0; i < sr.steps; ++i)
-      if ((s = launch_step(sr, (uint32_t)i)) != DPO_OK) return s;
-    uint32_t* no_flags = nullptr;  // no pinned memory here: the flags are copied
+    for (int i = 0; i < ahead; ++i) {
+      if ((s = launch_step(sr, narrow ? 0u : (uint32_t)i)) != DPO_OK) return s;
+      if (narrow && (s = launch_narrow(sr, 1u, 0u, nullptr)) != DPO_OK) return s;
+    }
     void* ap[] = {&st, &k, &no_flags};
-    if (hipLaunchKernel(advance_kernel_ptr(), dim3(1), dim3(64), ap, 0, sr.stream) != hipSuccess)
+    if (!narrow && hipLaunchKernel(advance_kernel_ptr(), dim3(1), dim3(64), ap, 0, sr.stream) != hipSuccess)
       return DPO_ERR_HIP;
     if (hipMemcpyAsync(flags, st, sizeof(flags), hipMemcpyDeviceToHost, sr.stream) != hipSuccess ||
         hipStreamSynchronize(sr.stream) != hipSuccess)

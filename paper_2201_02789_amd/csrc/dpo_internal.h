@@ -25,6 +25,26 @@ constexpr int NHINT = 8;           // BFS per-XCD visited copies (Args::hint), o
 constexpr int HARVEST_RUNS = 4;    // harvest kernel: 64-slot runs per wave and round
 constexpr int HINT_AUTO_MIN_DEGREE = 8;  // DPO_HINT_AUTO: per-XCD copies from this average
                                          // degree (m / n) up
+// narrow levels (one workgroup, frontier in LDS)
+constexpr int NARROW_BLOCK = 1024;
+constexpr uint32_t NARROW_U = 8;              // edges per lane and batch
+constexpr uint32_t NARROW_WORDS = 38 * 1024;  // LDS words: bits, distances, frontier arrays
+constexpr uint32_t NARROW_FRONT = 8192;       // most frontier entries
+// Most edges of a narrow level.  One compute unit runs about 2.4 edges per
+// nanosecond when the visited bits (distances) are in its LDS, but makes only
+// about one random access per nanosecond to global ones, while a level step
+// takes 30 to 50 us (16 us on a road-like graph) however few its edges are.
+constexpr uint32_t NARROW_EDGES = 1 << 17;
+constexpr uint32_t NARROW_FAR_EDGES = 1 << 12;
+// Bitmap words (BFS) and distances (SSSP) that go to LDS, beside half of
+// NARROW_FRONT frontier entries or more.  SSSP with global distances has no
+// narrow form: one compute unit makes its probes and atomics more slowly than
+// level steps do (a 77,357-vertex road-like graph 12.6 ms against 9.9).
+constexpr int32_t NARROW_BITS = NARROW_WORDS - 4 * (NARROW_FRONT / 2);
+constexpr int32_t NARROW_DIST = 16384;
+constexpr uint32_t NONE = 0xFFFFFFFFu;        // no vertex
+constexpr uint32_t NARROW_LEVELS = 4096;      // most levels per launch (a few ms)
+enum { V_DONE = 1, V_WIDE = 2, V_MORE = 3, V_ERROR = 4 };  // how a narrow launch ended
 
 enum { PROB_BFS = 0, PROB_SSSP = 1 };
 enum { AGG_NONE = 0, AGG_WAVE = 1, AGG_BLOCK = 2, AGG_MULTI = 3, AGG_FLAT = 4 };
@@ -145,6 +165,7 @@ const void* child_kernel_ptr(int problem, bool timed = false, bool nt = false);
 const void* serial_kernel_ptr(int problem, int gran, bool timed = false);
 const void* harvest_kernel_ptr(int problem, bool timed = false);
 const void* init_kernel_ptr(int problem);
+const void* narrow_kernel_ptr(int problem, int32_t slots);
 const void* start_kernel_ptr(int problem);
 const void* admit_kernel_ptr(int problem);
 const void* admit_sources_kernel_ptr();

@@ -1373,6 +1373,351 @@ __global__ __launch_bounds__(PB) void harvest_kernel(Args a, uint32_t step) {
   tm_write<TM>(a, pc, TK_HARVEST, L, t_entry, tid);
 }
 
+// ------------------------------------------------------------ narrow levels
+// One workgroup runs consecutive narrow levels of a single traversal in one
+// launch, the frontier in LDS from level to level.  A narrow level has too few
+// edges to fill the chip; as a level step of its own it costs two to four
+// launches and their chains of dependent loads.  Here it is two dependent loads
+// (a vertex's row, its edges) and a few barriers: BFS on a 514 x 514 road-like
+// graph (about 610 levels of 430 vertices) 15.4 -> 3.9 us a level, 9.6 -> 2.4
+// ms; R-MAT of 4,096 vertices 238 -> 81 us.  What is left is latency: 0.7 us
+// per load and about 0.25 us per barrier.
+//
+// BFS keeps the visited bitmap in LDS too when it fits beside the frontier, so
+// that a claim is an LDS atomic; else it claims the global bitmap as a one-copy
+// level does.  SSSP runs here on graphs whose distances fit LDS: atomicMin
+// there, a bit per vertex so that the frontier takes an improved one once, and
+// no work for a parent that has been improved (and queued) again meanwhile.
+//
+// The kernel leaves what a level step expects (frontier, level sets, group
+// counters, visited copies) when a level is wide: more frontier entries than
+// LDS holds, or more edges than one compute unit runs in the time of a level
+// step's launches (NARROW_EDGES, NARROW_FAR_EDGES).
+struct NarrowLds {
+  uint32_t words[NARROW_WORDS];
+  uint32_t fpre[NQF + 2];
+  uint32_t wsum[NARROW_BLOCK / 64], wrows[NARROW_BLOCK / 64];
+  unsigned long long heads[NARROW_BLOCK / 64][NARROW_U];  // per wave: row starts in its chunk
+  uint32_t cnt, bad;
+};
+
+// Tells the host how the launch ended (pinned memory; nullptr: nobody waits).
+__device__ __forceinline__ void post_verdict(uint32_t* verdict, uint32_t ticket, uint32_t code,
+                                             uint32_t error) {
+  if (verdict)
+    __hip_atomic_store(verdict, ticket << 8 | error << 4 | code, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Workgroup barrier that orders LDS only: global stores stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// One batch of a wave's edges (v: target, or NONE; nd: SSSP distance through
+// the edge): f[u] = v[u] joins the next frontier.  All probes are issued before
+// any atomic, all atomics before any use, so their round trips overlap.
+template <int P, bool LDS>
+__device__ __forceinline__ void narrow_visit(const Args& a, uint32_t* s_bits, uint32_t* s_dist,
+                                             uint32_t* vis, const uint32_t (&v)[NARROW_U],
+                                             const uint32_t (&nd)[NARROW_U], uint32_t L,
+                                             bool (&f)[NARROW_U]) {
+  constexpr int U = NARROW_U;
+  uint32_t x[U];
+  if (P == PROB_BFS) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      x[u] = ~0u;
+      if (v[u] != NONE) x[u] = LDS ? s_bits[v[u] >> 5] : vis[v[u] >> 5];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t bit = 1u << (v[u] & 31);
+      if (x[u] & bit) x[u] = ~0u;
+      else x[u] = LDS ? atomicOr(&s_bits[v[u] >> 5], bit) : atomicOr(&vis[v[u] >> 5], bit);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      f[u] = !(x[u] & (1u << (v[u] & 31)));
+      if (f[u]) a.level[v[u]] = (int32_t)L + 1;
+    }
+    return;
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    x[u] = 0;
+    if (v[u] != NONE) x[u] = s_dist[v[u]];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (nd[u] < x[u]) x[u] = atomicMin(&s_dist[v[u]], nd[u]);
+    else x[u] = 0;
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t bit = 1u << (v[u] & 31);
+    if (nd[u] < x[u]) x[u] = atomicOr(&s_bits[v[u] >> 5], bit) & bit;
+    else x[u] = 1;
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) f[u] = x[u] == 0;
+}
+
+// adv: level steps run since the last launch (0 or 1).
+// LDS: the visited bits (SSSP: the distances, and a bit for the vertices queued
+// at this level) are in LDS.
+template <int P, bool LDS>
+__global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t adv, uint32_t ticket,
+                                                              uint32_t* verdict) {
+  __shared__ NarrowLds sh;
+  constexpr uint32_t NB = NARROW_BLOCK, PER = NARROW_FRONT / NB, U = NARROW_U;
+  const uint32_t tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  State* st = a.st;
+  if (st->done || st->error) {
+    if (tid == 0) post_verdict(verdict, ticket, st->error ? V_ERROR : V_DONE, st->error);
+    return;
+  }
+  uint32_t L = st->base + adv;
+  const uint32_t n = (uint32_t)a.q[0].n;
+  if (tid == 0) sh.bad = 0;
+  const LevelSet* prv = &st->set[(L + 2) % 3];
+  if (wave == 0) {
+    const uint32_t c = min(prv->fcnt[lane], (uint32_t)a.fcap);
+    const uint32_t incl = wave_incl_scan(c, lane);
+    sh.fpre[lane + 1] = incl;
+    if (lane == 0) sh.fpre[0] = 0;
+    if (lane == 63) sh.fpre[NQF + 1] = incl + prv->fcnt[NQF];
+  }
+  __syncthreads();
+  uint32_t F = sh.fpre[NQF + 1];
+  // LDS: the bits, the distances, then frontier arrays of FC entries each
+  constexpr uint32_t ARR = P == PROB_BFS ? 4 : 5;
+  const uint32_t nbits = LDS ? (uint32_t)a.vwords : 0u, ndist = P == PROB_SSSP ? n : 0u;
+  const uint32_t FC = min((uint32_t)NARROW_FRONT, (NARROW_WORDS - nbits - ndist) / ARR);
+  constexpr uint32_t max_edges = LDS ? NARROW_EDGES : NARROW_FAR_EDGES;
+  const uint32_t max_front = min(FC, max_edges);
+  uint32_t* s_bits = sh.words;
+  uint32_t* s_dist = sh.words + nbits;
+  uint32_t* s_front = sh.words + nbits + ndist;  // two of FC: this level's, the next one's
+  uint32_t* s_start = s_front + 2 * FC;
+  uint32_t* s_off = s_front + 3 * FC;
+  uint32_t* s_slot = s_front + 4 * FC;  // SSSP
+  uint32_t cur = 0, nxt = FC;         // offsets into s_front
+  const uint32_t c = st->vsel[L & 1];
+  // the copy this traversal's one-copy levels probe and update, and the other
+  uint32_t* vis = P == PROB_BFS ? a.visit + (a.hint ? 0u : c * (uint32_t)a.vwords)
+                                : (c ? a.dist2 : a.dist);
+  uint32_t* fold = c ? a.dist : a.dist2;  // SSSP
+  const uint32_t L0 = L;
+  bool wide = F > max_front;
+  const bool held = F != 0 && !wide;  // loaded into LDS
+  if (held) {
+    const int32_t* fin = (L & 1) ? a.front1 : a.front0;
+    for (uint32_t i = tid; i < F; i += NB) s_front[i] = (uint32_t)frontier_at(a, fin, sh.fpre, i);
+    for (uint32_t i = tid; i < nbits; i += NB) s_bits[i] = P == PROB_BFS ? vis[i] : 0u;
+    for (uint32_t i = tid; i < ndist; i += NB) s_dist[i] = vis[i];
+  }
+  __syncthreads();
+  while (F != 0 && !wide) {
+    // rows of this thread's entries [tid * per, tid * per + per)
+    const uint32_t per = ceil_div(F, NB);
+    uint32_t start[PER], deg[PER], sum = 0, rows = 0;
+    bool big = F > NB;
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j) {
+      const uint32_t i = tid * per + j;
+      start[j] = deg[j] = 0;
+      if (j < per && i < F) {
+        const uint32_t v = s_front[cur + i];
+        start[j] = (uint32_t)a.rp[v];
+        deg[j] = (uint32_t)a.rp[v + 1];
+        if (P == PROB_SSSP) atomicAnd(&s_bits[v >> 5], ~(1u << (v & 31)));  // may be queued again
+      }
+    }
+    if (tid == 0) sh.cnt = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j) {
+      deg[j] -= start[j];
+      sum += deg[j];
+      rows += deg[j] != 0;
+      big |= deg[j] > U;
+    }
+    int32_t* fout = (L & 1) ? a.front0 : a.front1;
+    // runs a batch of edges, and appends what joins the next frontier: to LDS,
+    // what does not fit to the overflow queue
+    auto edges = [&](const bool (&valid)[U], const uint32_t (&ei)[U], const uint32_t (&dv)[U]) {
+      uint32_t v[U], nd[U];
+      bool f[U];
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        v[u] = valid[u] ? (uint32_t)a.col[ei[u]] : NONE;
+        nd[u] = (P == PROB_SSSP && valid[u]) ? a.w[ei[u]] : 0u;
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        if (v[u] >= n && valid[u]) {
+          sh.bad = 1;
+          v[u] = NONE;
+        }
+        const uint32_t sum = dv[u] + nd[u];  // saturating, as in visit_batch
+        nd[u] = v[u] == NONE || sum < dv[u] ? 0xFFFFFFFFu : sum;
+      }
+      narrow_visit<P, LDS>(a, s_bits, s_dist, vis, v, nd, L, f);
+      unsigned long long m[U];
+      uint32_t total = 0, base = 0;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        m[u] = __ballot(f[u]);
+        total += (uint32_t)__popcll(m[u]);
+      }
+      if (total == 0) return;
+      if (lane == 0) base = atomicAdd(&sh.cnt, total);
+      base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t pos = base + lane_rank(m[u]);
+        base += (uint32_t)__popcll(m[u]);
+        if (!f[u]) continue;
+        if (pos < FC) s_front[nxt + pos] = v[u];
+        else if (pos < (uint32_t)a.slots) fout[(size_t)NQF * a.fcap + pos] = (int32_t)v[u];
+      }
+    };
+    if (!__syncthreads_or(big)) {
+      // one short row per thread: it runs the row, with no scan of the
+      // degrees and no search for an edge's row
+      if (__any(deg[0] != 0)) {
+        bool valid[U];
+        uint32_t ei[U], dv[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+          valid[u] = u < deg[0];
+          ei[u] = start[0] + u;
+          dv[u] = P == PROB_SSSP && valid[u] ? s_dist[s_front[cur + tid]] : 0u;
+        }
+        edges(valid, ei, dv);
+      }
+    } else {
+      // the non-empty rows and their scanned degrees, in LDS
+      const uint32_t incl = wave_incl_scan(sum, lane), rincl = wave_incl_scan(rows, lane);
+      if (lane == 63) {
+        sh.wsum[wave] = incl;
+        sh.wrows[wave] = rincl;
+      }
+      lds_barrier();
+      uint32_t run = incl - sum, E = 0, row = rincl - rows, R = 0;
+#pragma unroll
+      for (uint32_t w = 0; w < NB / 64; ++w) {
+        if (w < (uint32_t)wave) {
+          run += sh.wsum[w];
+          row += sh.wrows[w];
+        }
+        E += sh.wsum[w];
+        R += sh.wrows[w];
+      }
+      if (E > max_edges) {
+        wide = true;
+        break;
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < PER; ++j) {
+        if (deg[j] == 0) continue;
+        s_start[row] = start[j] - run;  // edge x of the level is start + x
+        s_off[row] = run;
+        if (P == PROB_SSSP) s_slot[row] = s_front[cur + tid * per + j];
+        run += deg[j];
+        ++row;
+      }
+      lds_barrier();
+      // A wave runs chunks of 64 * U consecutive edges of the level.  A bit per
+      // edge that begins a row gives each edge its row by a count of the bits
+      // up to it: one LDS atomic per row instead of a search per edge.
+      unsigned long long* heads = sh.heads[wave];
+      for (uint32_t x0 = wave * 64 * U; x0 < E; x0 += NB * U) {
+        const uint32_t p0 = wave_upper_search(R, x0, lane, [&](uint32_t k) { return s_off[k]; });
+        if (lane < (int)U) heads[lane] = 0;
+        wave_lds_sync();
+        for (uint32_t k = p0 + 1 + lane; k < R; k += 64) {
+          const uint32_t x = s_off[k] - x0;
+          if (x >= 64 * U) break;
+          atomicOr(&heads[x >> 6], 1ull << (x & 63));
+        }
+        wave_lds_sync();
+        bool valid[U];
+        uint32_t ei[U], dv[U], p = p0;
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+          const unsigned long long h = heads[u];
+          const uint32_t x = x0 + u * 64 + lane;
+          const uint32_t k = p + lane_rank(h) + (uint32_t)(h >> lane & 1u);
+          p += (uint32_t)__popcll(h);
+          valid[u] = x < E;
+          ei[u] = s_start[k] + x;
+          dv[u] = 0;
+          if (P == PROB_SSSP && valid[u]) {
+            const uint32_t s = s_slot[k];
+            valid[u] = !(s_bits[s >> 5] >> (s & 31) & 1u);  // else queued again
+            dv[u] = s_dist[s];
+          }
+        }
+        edges(valid, ei, dv);
+        wave_lds_sync();  // heads is cleared by the next chunk
+      }
+    }
+    lds_barrier();
+    ++L;
+    F = sh.cnt;
+    const uint32_t t = cur;
+    cur = nxt;
+    nxt = t;
+    if (F > max_front) wide = true;
+    lds_barrier();  // F read before the next level clears the count
+    if (L - L0 >= NARROW_LEVELS) break;
+  }
+  __syncthreads();
+  if (held)
+    for (uint32_t i = tid; i < ndist; i += NB) {
+      const uint32_t d = s_dist[i];
+      vis[i] = d;
+      fold[i] = d;
+    }
+  if (F == 0 || sh.bad) {
+    const uint32_t err = sh.bad ? (uint32_t)ERR_ARG : 0u;
+    if (tid == 0) {
+      st->done = 1;
+      st->error = err;
+      post_verdict(verdict, ticket, err ? V_ERROR : V_DONE, err);
+    }
+    return;
+  }
+  if (L != L0) {
+    // what a level step finds at level L
+    int32_t* fin = (L & 1) ? a.front1 : a.front0;
+    for (uint32_t i = tid; i < min(F, FC); i += NB)
+      fin[(size_t)NQF * a.fcap + i] = (int32_t)s_front[cur + i];
+    if (P == PROB_BFS)
+      for (uint32_t i = tid; i < nbits; i += NB) vis[i] = s_bits[i];
+    for (uint32_t i = tid; i < (uint32_t)a.ngroups_cap; i += NB) {
+      a.grp_packed[(L % 3) * a.ngroups_cap + i] = 0;
+      a.grp_done[(L % 3) * a.ngroups_cap + i] = 0;
+    }
+    uint32_t* sets = (uint32_t*)&st->set[0];
+    const uint32_t fill = (uint32_t)(&st->set[(L + 2) % 3].fcnt[NQF] - sets);
+    for (uint32_t i = tid; i < 3 * sizeof(LevelSet) / 4; i += NB) sets[i] = i == fill ? F : 0u;
+  }
+  if (tid == 0) {
+    st->base = L;
+    if (L != L0) {
+      st->vsel[L & 1] = c;
+      st->vstale[L & 1] = P == PROB_BFS ? 1u : 0u;
+      st->levels_run = L;
+    }
+    post_verdict(verdict, ticket, wide ? V_WIDE : V_MORE, 0);
+  }
+}
+
 // ------------------------------------------------------------ init / admit / advance
 // Traversal-set start: level sets and counters cleared.  Queries are
 // started by admit_kernel.
@@ -1595,6 +1940,13 @@ const void* child_kernel_ptr(int problem, bool timed, bool nt) {
 }
 
 const void* init_kernel_ptr(int) { return (const void*)init_kernel; }
+
+const void* narrow_kernel_ptr(int problem, int32_t slots) {
+  if (problem == PROB_SSSP)
+    return slots <= NARROW_DIST ? (const void*)narrow_kernel<PROB_SSSP, true> : nullptr;
+  return slots / 32 <= NARROW_BITS ? (const void*)narrow_kernel<PROB_BFS, true>
+                                   : (const void*)narrow_kernel<PROB_BFS, false>;
+}
 
 const void* start_kernel_ptr(int problem) {
   return problem == PROB_BFS ? (const void*)start_kernel<PROB_BFS>
