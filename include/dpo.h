@@ -23,7 +23,7 @@
  *     static device array serves dpo_bfs_noalloc) and never frees the caller's
  *     memory.  `stream` is a hipStream_t (NULL = default stream).
  *   - The CSR graph must be symmetric for the results to be shortest paths of
- *     an undirected graph; the kernels follow out-edges only.
+ *     an undirected graph; results are those of following out-edges only.
  *   - Work is enqueued on `stream`.  The traversal calls synchronise `stream`
  *     once per `steps_per_replay` level steps to read the done flag, or wait
  *     for the flag of each run of narrow levels, so they return only when the
@@ -128,7 +128,11 @@ typedef struct {
                                whose atomicMin improved a distance records the
                                vertex as found, and the harvest queues it once;
                                when off, an iteration stamp exchanged
-                               atomically does.  Speed only.                    */
+                               atomically does.  When on, a nested, aggregated
+                               BFS without counters also runs wide levels
+                               bottom-up (an unvisited vertex looks for a
+                               visited neighbour) if it finds the graph
+                               symmetric.  Speed only.                          */
 } dpo_options;
 
 typedef enum {

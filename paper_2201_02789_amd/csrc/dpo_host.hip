@@ -14,6 +14,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <random>
 #include <vector>
 
 #include "dpo.h"
@@ -154,6 +155,7 @@ struct Runtime {
   uint64_t tick = 0;
   uint32_t* host_flags = nullptr;  // pinned: base, done, error, levels_run; [8]: verdict
   uint32_t ticket = 0;             // of the last narrow launch (24 bits)
+  std::mt19937 keys{std::random_device{}()};  // of the symmetry checks
   unsigned long long* host_stats = nullptr;  // pinned: MAX_GRID * NSTAT
   Query* host_q = nullptr;                   // pinned: MAX_QUERIES query records
   int32_t* host_list = nullptr;              // pinned: MAX_QUERIES query indices + prefix
@@ -522,12 +524,27 @@ dpo_status launch_step(SetRun& sr, uint32_t step) {
   return DPO_OK;
 }
 
-// The narrow levels' kernel: one workgroup.  adv: level steps run since the
+// The narrow levels' kernel: one workgroup.  after: AFTER_*, what ran since the
 // last one.  verdict: pinned word it reports to, or nullptr.
-dpo_status launch_narrow(SetRun& sr, uint32_t adv, uint32_t ticket, uint32_t* verdict) {
-  void* p[] = {&sr.a, &adv, &ticket, &verdict};
+dpo_status launch_narrow(SetRun& sr, uint32_t after, uint32_t ticket, uint32_t* verdict) {
+  void* p[] = {&sr.a, &after, &ticket, &verdict};
   return hip_ok(hipLaunchKernel(narrow_kernel_ptr(sr.problem, sr.a.slots), dim3(1), dim3(NARROW_BLOCK), p, 0,
                                 sr.stream));
+}
+
+// A bottom-up level, if one is due; check: the symmetry check first, if due.
+dpo_status launch_bottom_up(Runtime& r, SetRun& sr, bool check) {
+  if (check) {
+    uint32_t key[4] = {(uint32_t)r.keys(), (uint32_t)r.keys(), (uint32_t)r.keys(), (uint32_t)r.keys()};
+    void* p[] = {&sr.a, key};
+    const int64_t grid = std::min<int64_t>(cdiv(sr.a.m, (int64_t)NW * SYM_EDGES), 8 * (int64_t)r.cu_count);
+    if (hipLaunchKernel(symmetry_kernel_ptr(), dim3((unsigned)std::max<int64_t>(grid, 1)), dim3(PB), p,
+                        0, sr.stream) != hipSuccess)
+      return DPO_ERR_HIP;
+  }
+  void* p[] = {&sr.a};
+  const int64_t grid = std::min<int64_t>(cdiv(sr.a.slots, PB), persistent_grid(r, bottom_up_kernel_ptr()));
+  return hip_ok(hipLaunchKernel(bottom_up_kernel_ptr(), dim3((unsigned)grid), dim3(PB), p, 0, sr.stream));
 }
 
 // Narrow levels run in one workgroup where their kernel has a form for the
@@ -563,15 +580,16 @@ dpo_status wait_verdict(const uint32_t* verdict, uint32_t ticket, hipStream_t st
   }
 }
 
-// A single traversal: narrow levels in one launch, a level step for each wide
-// one.  The host learns from the narrow kernel's verdict whether a level step
-// follows, so nothing is launched that has nothing to do.
+// A single traversal: narrow levels in one launch, then a wide one.  The host
+// learns from the narrow kernel's verdict which kernels that takes.  Bottom-up
+// levels follow each other more often than not: two are launched at a time, the
+// second of which finds out by itself whether it is due.
 dpo_status run_narrow_and_wide(Runtime& r, SetRun& sr, int64_t max_levels) {
   uint32_t* verdict = r.host_flags + 8;
-  uint32_t adv = 0;
+  uint32_t after = AFTER_NONE;
   for (int64_t rep = 0; rep < max_levels + 2; ++rep) {
     r.ticket = (r.ticket + 1) & 0xFFFFFFu;
-    dpo_status s = launch_narrow(sr, adv, r.ticket, verdict);
+    dpo_status s = launch_narrow(sr, after, r.ticket, verdict);
     uint32_t v = 0;
     if (s == DPO_OK) s = wait_verdict(verdict, r.ticket, sr.stream, &v);
     if (s != DPO_OK) return s;
@@ -580,8 +598,17 @@ dpo_status run_narrow_and_wide(Runtime& r, SetRun& sr, int64_t max_levels) {
       if (hipStreamSynchronize(sr.stream) != hipSuccess) return DPO_ERR_HIP;
       return code == V_DONE ? DPO_OK : (dpo_status)(-(int32_t)((v >> 4) & 15u));
     }
-    adv = code == V_WIDE ? 1u : 0u;
-    if (adv && (s = launch_step(sr, 0u)) != DPO_OK) return s;
+    after = AFTER_NONE;
+    if (code == V_TOP_DOWN) {
+      after = AFTER_STEP;
+      s = launch_step(sr, 0u);
+    } else if (code == V_BOTTOM_UP || code == V_CHECK) {
+      after = AFTER_BOTTOM_UP;
+      s = launch_bottom_up(r, sr, code == V_CHECK);
+      if (s == DPO_OK) s = launch_narrow(sr, after, 0u, nullptr);
+      if (s == DPO_OK) s = launch_bottom_up(r, sr, false);
+    }
+    if (s != DPO_OK) return s;
   }
   return DPO_ERR_TIMEOUT;
 }
@@ -627,10 +654,11 @@ dpo_status traverse(int problem, const dpo_csr* g, int32_t source, const dpo_opt
                   tm);
   if (s != DPO_OK) return s;
   if (tm && hipMemsetAsync(tm, 0, DPO_TIMING_BYTES, sr.stream) != hipSuccess) return DPO_ERR_HIP;
+  const bool narrow = use_narrow(sr, *o, st != nullptr, tm != nullptr);
+  sr.a.bottom_up = narrow && problem == PROB_BFS ? sr.a.hint : 0;
   s = start_single(r, sr, Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source});
   if (s != DPO_OK) return s;
-  s = use_narrow(sr, *o, st != nullptr, tm != nullptr) ? run_narrow_and_wide(r, sr, g->n)
-                                                   : run_to_completion(r, sr, g->n);
+  s = narrow ? run_narrow_and_wide(r, sr, g->n) : run_to_completion(r, sr, g->n);
   return s != DPO_OK ? s : read_stats(r, sr, st);
 }
 
@@ -747,6 +775,8 @@ dpo_status traverse_noalloc(int problem, const dpo_csr* g, int32_t source, const
   // the start kernel clears the state, the level sets, the group counters, the
   // outputs and the visited state, so nothing left in the array by an earlier
   // call is read
+  const bool narrow = use_narrow(sr, *o, false, false);
+  sr.a.bottom_up = narrow ? sr.a.hint : 0;
   s = start_single(r, sr, Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source});
   if (s != DPO_OK) return s;
   uint32_t flags[4] = {0, 0, 0, 0};  // base, done, error, levels_run
@@ -754,15 +784,15 @@ dpo_status traverse_noalloc(int problem, const dpo_csr* g, int32_t source, const
   uint32_t k = (uint32_t)sr.steps;
   uint32_t* no_flags = nullptr;  // no pinned memory here: the flags are copied
   // narrow levels run in one workgroup; a few wide ones are launched ahead of
-  // each look at the flags (those past the end find nothing to do)
-  const bool narrow = use_narrow(sr, *o, false, false);
+  // each look at the flags (what is not due finds nothing to do)
   const int ahead = narrow ? std::min(sr.steps, kStepsAhead) : sr.steps;
   const int64_t max_replays = (int64_t)g->n / ahead + 2;
-  if (narrow && (s = launch_narrow(sr, 0u, 0u, nullptr)) != DPO_OK) return s;
+  if (narrow && (s = launch_narrow(sr, AFTER_NONE, 0u, nullptr)) != DPO_OK) return s;
   for (int64_t rep = 0; rep < max_replays; ++rep) {
     for (int i = 0; i < ahead; ++i) {
+      if (sr.a.bottom_up && (s = launch_bottom_up(r, sr, true)) != DPO_OK) return s;
       if ((s = launch_step(sr, narrow ? 0u : (uint32_t)i)) != DPO_OK) return s;
-      if (narrow && (s = launch_narrow(sr, 1u, 0u, nullptr)) != DPO_OK) return s;
+      if (narrow && (s = launch_narrow(sr, AFTER_ANY, 0u, nullptr)) != DPO_OK) return s;
     }
     void* ap[] = {&st, &k, &no_flags};
     if (!narrow && hipLaunchKernel(advance_kernel_ptr(), dim3(1), dim3(64), ap, 0, sr.stream) != hipSuccess)

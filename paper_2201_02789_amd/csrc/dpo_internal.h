@@ -28,7 +28,7 @@ constexpr int HINT_AUTO_MIN_DEGREE = 8;  // DPO_HINT_AUTO: per-XCD copies from t
 // narrow levels (one workgroup, frontier in LDS)
 constexpr int NARROW_BLOCK = 1024;
 constexpr uint32_t NARROW_U = 8;              // edges per lane and batch
-constexpr uint32_t NARROW_WORDS = 38 * 1024;  // LDS words: bits, distances, frontier arrays
+constexpr uint32_t NARROW_WORDS = 36 * 1024;  // LDS words: bits, distances, frontier arrays
 constexpr uint32_t NARROW_FRONT = 8192;       // most frontier entries
 // Most edges of a narrow level.  One compute unit runs about 2.4 edges per
 // nanosecond when the visited bits (distances) are in its LDS, but makes only
@@ -44,7 +44,25 @@ constexpr int32_t NARROW_BITS = NARROW_WORDS - 4 * (NARROW_FRONT / 2);
 constexpr int32_t NARROW_DIST = 16384;
 constexpr uint32_t NONE = 0xFFFFFFFFu;        // no vertex
 constexpr uint32_t NARROW_LEVELS = 4096;      // most levels per launch (a few ms)
-enum { V_DONE = 1, V_WIDE = 2, V_MORE = 3, V_ERROR = 4 };  // how a narrow launch ended
+// How a narrow launch ended: the traversal done or failed, more narrow levels,
+// or a wide level, which goes top-down (a level step), bottom-up, or bottom-up
+// if the graph turns out symmetric.
+enum { V_DONE = 1, V_ERROR, V_MORE, V_TOP_DOWN, V_BOTTOM_UP, V_CHECK };
+// What a narrow launch follows: no level, a level step, a bottom-up level if
+// one was due, either of the two.
+enum { AFTER_NONE = 0, AFTER_STEP, AFTER_BOTTOM_UP, AFTER_ANY };
+
+// bottom-up levels (BFS)
+// A level goes bottom-up if its frontier has at least 1 / BU_ALPHA of the edges
+// not yet run, so that a vertex looks at about BU_ALPHA entries at most.
+// Measured (us, before the symmetry check was tuned): R-MAT of 70,001 vertices
+// 160 / 121 / 122 / 123 at 4 / 8 / 16 / 32, scale 22 620 / 606 / 582 / 590,
+// Erdos-Renyi of 2 M 518 / 512 / 512 / 515.
+constexpr uint32_t BU_ALPHA = 16;
+constexpr uint32_t BU_LANE = 32;    // edges a lane looks at before the wave shares its row
+constexpr uint32_t SYM_EDGES = 1024;  // symmetry check: least edges per wave
+constexpr uint32_t SYM_SAMPLES = 128;  // entries whose reverse is looked up first, if
+constexpr uint32_t SYM_SAMPLE_DEGREE = 32;  // the row it would be in is this short
 
 enum { PROB_BFS = 0, PROB_SSSP = 1 };
 enum { AGG_NONE = 0, AGG_WAVE = 1, AGG_BLOCK = 2, AGG_MULTI = 3, AGG_FLAT = 4 };
@@ -84,7 +102,12 @@ struct State {
   uint32_t levels_run;  // index of the last non-empty level + 1
   uint32_t vsel[2];     // probed visited buffer of levels with parity 0 / 1
   uint32_t vstale[2];   // BFS: the other bitmap missed folds (a one-copy level ran)
-  uint32_t pad[56];
+  uint32_t plan;        // single traversals: verdict of the last narrow launch
+  uint32_t symmetric;   // 0 not checked, 1 yes, 2 no
+  unsigned long long run_edges;  // edges of the levels so far (about)
+  unsigned long long sym_sum[8];  // symmetry check: shares of the signed sum
+  uint32_t asymmetric;  // symmetry check: an id out of range was met
+  uint32_t pad[33];
   LevelSet set[3];
 };
 
@@ -155,6 +178,7 @@ struct Args {
                                    // XCD), discoveries taken into bitmap 0 by the harvest;
                                    // SSSP: improvements queued by the harvest instead of
                                    // iteration stamps
+  int32_t bottom_up;               // wide BFS levels may go bottom-up (with Args::hint)
 };
 
 // timed: the instantiation that stamps its phases into Args::tm
@@ -166,6 +190,8 @@ const void* serial_kernel_ptr(int problem, int gran, bool timed = false);
 const void* harvest_kernel_ptr(int problem, bool timed = false);
 const void* init_kernel_ptr(int problem);
 const void* narrow_kernel_ptr(int problem, int32_t slots);
+const void* symmetry_kernel_ptr();
+const void* bottom_up_kernel_ptr();
 const void* start_kernel_ptr(int problem);
 const void* admit_kernel_ptr(int problem);
 const void* admit_sources_kernel_ptr();

@@ -216,18 +216,20 @@ struct Vis {
   uint32_t* own;          // BFS with per-XCD copies: this XCD's copy (= probe)
 };
 
-// BFS with per-XCD copies (Args::hint): bitmap 0 is the visited set.  On a
-// wide level (split) it does not change until the harvest kernel, and each XCD
+// BFS with per-XCD copies (Args::hint): bitmap c is the visited set (0, until a
+// bottom-up level leaves it in the other one).  On a wide level (split) it does
+// not change until the harvest kernel, and each XCD
 // (workgroup % 8) probes its own bitmap, which holds bitmap 0 as of the
 // level's start plus the vertices this XCD has found since, kept with plain
 // loads and stores that stay in its L2; a narrow level probes and claims
-// bitmap 0 with atomics and appends in place.
+// bitmap c with atomics and appends in place.
 template <int P>
 __device__ __forceinline__ Vis vis_of(const Args& a, uint32_t c, bool split) {
   if (P == PROB_BFS && a.hint) {
-    if (!split) return Vis{a.visit, a.visit, nullptr, false, nullptr};
+    uint32_t* all = a.visit + (size_t)c * (uint32_t)a.vwords;
+    if (!split) return Vis{all, all, nullptr, false, nullptr};
     uint32_t* own = a.visit + (size_t)(2u + (blockIdx.x & (NHINT - 1))) * (uint32_t)a.vwords;
-    return Vis{own, a.visit, nullptr, false, own};
+    return Vis{own, all, nullptr, false, own};
   }
   uint32_t* b0 = P == PROB_BFS ? a.visit : a.dist;
   uint32_t* b1 = P == PROB_BFS ? a.visit + a.vwords : a.dist2;
@@ -445,6 +447,18 @@ __device__ __forceinline__ void tm_write(const Args& a, const PhaseClock<ON>& pc
   }
 }
 
+// A level of a single traversal that the bottom-up kernel runs.  Uniform over a
+// launch: the symmetry check's sums are complete when its kernel ends.
+__device__ __forceinline__ bool found_symmetric(const State* st) {
+  unsigned long long sum = 0;
+  for (int i = 0; i < 8; ++i) sum += st->sym_sum[i];
+  return sum == 0 && !st->asymmetric;
+}
+
+__device__ __forceinline__ bool goes_bottom_up(const State* st) {
+  return st->plan == V_BOTTOM_UP || (st->plan == V_CHECK && found_symmetric(st));
+}
+
 // Append one aggregated grid to descriptor queue q (one lane).
 __device__ __forceinline__ void publish(const Args& a, LevelSet* ls, uint32_t q, uint32_t rec_base,
                                         uint32_t nrec, uint32_t total) {
@@ -535,7 +549,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
   if (TM) t_entry = realtime();
   PhaseClock<TM> pc;
   pc.start();
-  if (st->done || st->error) return;
+  if (st->done || st->error || goes_bottom_up(st)) return;
   const uint32_t L = st->base + step;
   LevelSet* prv = &st->set[(L + 2) % 3];  // fills of frontier L
   LevelSet* cur = &st->set[L % 3];        // this level: next-frontier fills, queues, groups
@@ -579,7 +593,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
     if (tid == 0) {
       st->levels_run = L + 1;
       cur->vmode = vc | (split ? 2u : 0u);  // for this level's child kernel
-      st->vsel[(L + 1) & 1] = vc ^ (split ? 1u : 0u);
+      st->vsel[(L + 1) & 1] = vc ^ (split && !(P == PROB_BFS && a.hint) ? 1u : 0u);
       st->vstale[(L + 1) & 1] = (P == PROB_BFS && !split) ? 1u : 0u;
     }
   }
@@ -601,7 +615,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
   // Fold into the copy not probed at this level: one atomic per frontier
   // entry, or, for BFS after a one-copy level or with more frontier entries
   // than bitmap words, one per non-zero word of the probed bitmap.  BFS with
-  // per-XCD copies: a wide level starts by copying bitmap 0 into every XCD's
+  // per-XCD copies: a wide level starts by copying bitmap vc into every XCD's
   // copy (each XCD's workgroups write their own copy), before pass 1 so that
   // pass 2 mostly probes complete copies; narrow levels keep no copy up to
   // date, which is why the next wide level copies it whole.
@@ -615,7 +629,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
     const uint32_t k = local ? blockIdx.x / NHINT : blockIdx.x;
     const uint32_t nk = local ? gridDim.x / NHINT : gridDim.x;
     for (uint32_t w = k * PB + tid; w < (uint32_t)a.vwords; w += nk * PB) {
-      const uint32_t cw = a.visit[w];
+      const uint32_t cw = a.visit[(size_t)vc * a.vwords + w];
       if (cw)
         for (uint32_t x = x0; x < x0 + nx; ++x) a.visit[(size_t)(2 + x) * a.vwords + w] = cw;
     }
@@ -1128,7 +1142,7 @@ __global__ __launch_bounds__(PB) void child_kernel(Args a, uint32_t step) {
   if (TM) t_entry = realtime();
   PhaseClock<TM> pc;
   pc.start();
-  if (st->done || st->error) return;
+  if (st->done || st->error || goes_bottom_up(st)) return;
   const uint32_t L = st->base + step;
   LevelSet* cur = &st->set[L % 3];
   int32_t* fout = (L & 1) ? a.front0 : a.front1;
@@ -1305,13 +1319,13 @@ __global__ __launch_bounds__(PB) void child_kernel(Args a, uint32_t step) {
 // The last kernel of a level step with found bytes (Args::hint).  SSSP: every
 // found vertex was improved at this level; it joins the next frontier once and
 // its byte is cleared for the next level.  BFS with per-XCD copies, after a
-// wide level: a found vertex that bitmap 0 lacks was discovered at this level.  It gets its level, its
-// bit in bitmap 0 and a place in the next frontier (in slot order, which also
+// wide level: a found vertex that the visited bitmap lacks was discovered at
+// this level.  It gets its level, its bit there and a place in the next frontier (in slot order, which also
 // makes the next level's row loads mostly consecutive).  One lane per slot: a
 // run of 64 slots is 64 found bytes and the two bitmap words they map to, which
 // the wave that reads them owns for the kernel.  Found bytes are never cleared within a
 // traversal: one set at an earlier level belongs to a vertex that the harvest
-// of that level put into bitmap 0.  Admission clears a query's found bytes,
+// of that level put into the bitmap.  Admission clears a query's found bytes,
 // and a serving engine clears all of them when it is created
 // (clear_found_kernel), so slots outside every admitted query hold none.  A
 // narrow level claimed and appended in place, and its harvest returns at once.
@@ -1326,10 +1340,11 @@ __global__ __launch_bounds__(PB) void harvest_kernel(Args a, uint32_t step) {
   if (TM) t_entry = realtime();
   PhaseClock<TM> pc;
   pc.start();
-  if (st->done || st->error) return;
+  if (st->done || st->error || goes_bottom_up(st)) return;
   const uint32_t L = st->base + step;
   LevelSet* cur = &st->set[L % 3];
   if (P == PROB_BFS && !(cur->vmode & 2u)) return;
+  uint32_t* seen = a.visit + (size_t)(cur->vmode & 1u) * (uint32_t)a.vwords;  // BFS
   int32_t* fout = (L & 1) ? a.front0 : a.front1;
   Stage s{s_stage[wave], 0u};
   const uint32_t n = (uint32_t)a.slots;
@@ -1344,7 +1359,7 @@ __global__ __launch_bounds__(PB) void harvest_kernel(Args a, uint32_t step) {
 #pragma unroll
     for (int k = 0; k < HU; ++k) {
       const uint32_t v = b + (uint32_t)k * 64u + (uint32_t)lane;
-      c[k] = (P == PROB_BFS && v < n) ? a.visit[v >> 5] : 0u;
+      c[k] = (P == PROB_BFS && v < n) ? seen[v >> 5] : 0u;
       f[k] = v < n && a.found[v] != 0;
     }
 #pragma unroll
@@ -1362,7 +1377,7 @@ __global__ __launch_bounds__(PB) void harvest_kernel(Args a, uint32_t step) {
         // lanes 0 and 32 own the words of the run's slots 0 .. 31 and 32 .. 63
         if ((lane & 31) == 0) {
           const uint32_t bits = (uint32_t)(m >> (lane & 32));
-          if (bits) a.visit[v >> 5] = c[k] | bits;
+          if (bits) seen[v >> 5] = c[k] | bits;
         }
       }
       stage_push(s, nw, (int32_t)v, a, cur, fout, lane);
@@ -1397,7 +1412,7 @@ struct NarrowLds {
   uint32_t words[NARROW_WORDS];
   uint32_t fpre[NQF + 2];
   uint32_t wsum[NARROW_BLOCK / 64], wrows[NARROW_BLOCK / 64];
-  unsigned long long heads[NARROW_BLOCK / 64][NARROW_U];  // per wave: row starts in its chunk
+  __align__(8) uint8_t heads[NARROW_BLOCK / 64][64 * NARROW_U];  // per wave: row starts in its chunk
   uint32_t cnt, bad;
 };
 
@@ -1414,6 +1429,25 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+}
+
+// Rows of 64 * NARROW_U consecutive edges, by a wave: heads[x - 1] is set if a
+// row begins at edge x > 0 of them, so that the marks below an edge's own place
+// count the rows begun up to it.
+__device__ __forceinline__ void clear_heads(uint8_t* heads, int lane) {
+  static_assert(NARROW_U == 8, "a lane clears 8 bytes");
+  ((unsigned long long*)heads)[lane] = 0;
+  wave_lds_sync();
+}
+
+// Row of edge u * 64 + lane; p: row of edge u * 64, less the one beginning
+// there, moved on to the next 64 edges.
+__device__ __forceinline__ uint32_t row_of(const uint8_t* heads, uint32_t u, int lane, uint32_t& p) {
+  const unsigned long long h = __ballot(heads[u * 64 + lane] != 0);
+  const uint32_t k = __builtin_amdgcn_mbcnt_hi((uint32_t)(h >> 32),
+                                               __builtin_amdgcn_mbcnt_lo((uint32_t)h, p));
+  p += (uint32_t)__popcll(h);
+  return k;
 }
 
 // One batch of a wave's edges (v: target, or NONE; nd: SSSP distance through
@@ -1465,11 +1499,11 @@ __device__ __forceinline__ void narrow_visit(const Args& a, uint32_t* s_bits, ui
   for (int u = 0; u < U; ++u) f[u] = x[u] == 0;
 }
 
-// adv: level steps run since the last launch (0 or 1).
+// after: what ran since the last launch (AFTER_*).
 // LDS: the visited bits (SSSP: the distances, and a bit for the vertices queued
 // at this level) are in LDS.
 template <int P, bool LDS>
-__global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t adv, uint32_t ticket,
+__global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t after, uint32_t ticket,
                                                               uint32_t* verdict) {
   __shared__ NarrowLds sh;
   constexpr uint32_t NB = NARROW_BLOCK, PER = NARROW_FRONT / NB, U = NARROW_U;
@@ -1480,6 +1514,10 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     if (tid == 0) post_verdict(verdict, ticket, st->error ? V_ERROR : V_DONE, st->error);
     return;
   }
+  const bool bottom_up = goes_bottom_up(st);
+  const bool adv = after == AFTER_BOTTOM_UP ? bottom_up : after != AFTER_NONE;
+  uint32_t symmetric = st->plan == V_CHECK ? (bottom_up ? 1u : 2u) : st->symmetric;
+  unsigned long long run_edges = st->run_edges;
   uint32_t L = st->base + adv;
   const uint32_t n = (uint32_t)a.q[0].n;
   if (tid == 0) sh.bad = 0;
@@ -1508,7 +1546,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
   uint32_t cur = 0, nxt = FC;         // offsets into s_front
   const uint32_t c = st->vsel[L & 1];
   // the copy this traversal's one-copy levels probe and update, and the other
-  uint32_t* vis = P == PROB_BFS ? a.visit + (a.hint ? 0u : c * (uint32_t)a.vwords)
+  uint32_t* vis = P == PROB_BFS ? a.visit + (size_t)c * (uint32_t)a.vwords
                                 : (c ? a.dist2 : a.dist);
   uint32_t* fold = c ? a.dist : a.dist2;  // SSSP
   const uint32_t L0 = L;
@@ -1621,6 +1659,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
         wide = true;
         break;
       }
+      run_edges += E;
 #pragma unroll
       for (uint32_t j = 0; j < PER; ++j) {
         if (deg[j] == 0) continue;
@@ -1631,28 +1670,25 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
         ++row;
       }
       lds_barrier();
-      // A wave runs chunks of 64 * U consecutive edges of the level.  A bit per
-      // edge that begins a row gives each edge its row by a count of the bits
-      // up to it: one LDS atomic per row instead of a search per edge.
-      unsigned long long* heads = sh.heads[wave];
+      // A wave runs chunks of 64 * U consecutive edges of the level.  A mark per
+      // edge that begins a row gives each edge its row by a count of the marks
+      // up to it: one LDS store per row instead of a search per edge.
+      uint8_t* heads = sh.heads[wave];
       for (uint32_t x0 = wave * 64 * U; x0 < E; x0 += NB * U) {
         const uint32_t p0 = wave_upper_search(R, x0, lane, [&](uint32_t k) { return s_off[k]; });
-        if (lane < (int)U) heads[lane] = 0;
-        wave_lds_sync();
+        clear_heads(heads, lane);
         for (uint32_t k = p0 + 1 + lane; k < R; k += 64) {
           const uint32_t x = s_off[k] - x0;
           if (x >= 64 * U) break;
-          atomicOr(&heads[x >> 6], 1ull << (x & 63));
+          heads[x - 1] = 1;
         }
         wave_lds_sync();
         bool valid[U];
         uint32_t ei[U], dv[U], p = p0;
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
-          const unsigned long long h = heads[u];
           const uint32_t x = x0 + u * 64 + lane;
-          const uint32_t k = p + lane_rank(h) + (uint32_t)(h >> lane & 1u);
-          p += (uint32_t)__popcll(h);
+          const uint32_t k = row_of(heads, u, lane, p);
           valid[u] = x < E;
           ei[u] = s_start[k] + x;
           dv[u] = 0;
@@ -1707,16 +1743,279 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     const uint32_t fill = (uint32_t)(&st->set[(L + 2) % 3].fcnt[NQF] - sets);
     for (uint32_t i = tid; i < 3 * sizeof(LevelSet) / 4; i += NB) sets[i] = i == fill ? F : 0u;
   }
+  uint32_t code = wide ? V_TOP_DOWN : V_MORE;
+  if (P == PROB_BFS && a.bottom_up && wide) {
+    // the level's edges, from the degrees of up to NB of its vertices
+    const int32_t* fin = (L & 1) ? a.front1 : a.front0;
+    uint32_t deg = 0, v = 0;
+    if (tid < F) {
+      const uint32_t i = F <= NB ? tid : (uint32_t)((uint64_t)tid * F / NB);
+      v = L == L0 ? (uint32_t)frontier_at(a, fin, sh.fpre, i)
+          : i < FC ? s_front[cur + i] : (uint32_t)fin[(size_t)NQF * a.fcap + i];
+      deg = (uint32_t)(a.rp[v + 1] - a.rp[v]);
+    }
+    const uint32_t incl = wave_incl_scan(deg, lane);
+    if (lane == 63) sh.wsum[wave] = incl;
+    __syncthreads();
+    unsigned long long E = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < NB / 64; ++w) E += sh.wsum[w];
+    if (F > NB) E = E * F / NB;
+    const unsigned long long left = (unsigned long long)a.m > run_edges ? a.m - run_edges : 0;
+    if (symmetric != 2 && E * BU_ALPHA >= left) {
+      code = V_BOTTOM_UP;
+      if (!symmetric) {
+        // The symmetry check reads the whole graph; on the directed graphs one
+        // meets, a few entries' missing reverses spare it.
+        bool missing = false;
+        if (tid < SYM_SAMPLES && deg) {
+          const uint32_t w = (uint32_t)a.col[(uint32_t)a.rp[v] + tid * 0x9E3779B1u % deg];
+          const uint32_t b = w < n ? (uint32_t)a.rp[w] : 0u, e = w < n ? (uint32_t)a.rp[w + 1] : 0u;
+          missing = e - b <= SYM_SAMPLE_DEGREE;
+          for (uint32_t x = b; x < e && missing; ++x) missing = (uint32_t)a.col[x] != v;
+        }
+        code = V_CHECK;
+        if (__syncthreads_or(missing)) {
+          symmetric = 2;
+          code = V_TOP_DOWN;
+        }
+      }
+    }
+    run_edges += E;
+  }
   if (tid == 0) {
     st->base = L;
+    st->plan = code;
+    st->symmetric = symmetric;
+    st->run_edges = run_edges;
     if (L != L0) {
       st->vsel[L & 1] = c;
       st->vstale[L & 1] = P == PROB_BFS ? 1u : 0u;
       st->levels_run = L;
     }
-    post_verdict(verdict, ticket, wide ? V_WIDE : V_MORE, 0);
+    post_verdict(verdict, ticket, code, 0);
   }
 }
+
+// ------------------------------------------------------------ bottom-up levels
+// Is the graph symmetric (every entry (u, v) as often as (v, u))?  A bottom-up
+// level looks for a parent of v along v's own row, which finds the edges into v
+// only then.  Nothing promises it, so the first level that would go bottom-up
+// is preceded by this pass over the adjacency: the sum over all entries of
+// h(u, v) where u < v and -h(v, u) where u > v, h a keyed mix, is zero modulo
+// 2^64 if the graph is symmetric, and otherwise as good as never (2^-62 for a
+// mix without structure; 2^-62 * k where k divides every surplus).  The key is
+// drawn anew for each call.  An id out of range counts as asymmetric.
+//
+// The mix is two 32 x 32 bit products, the second of the first's keyed halves:
+// it is not linear in either id and takes two quarter-rate instructions (two
+// 64-bit products take six).  Bound by its instructions and the adjacency
+// stream together: scale 22, 513 MB in 145 us, 3.5 TB/s.
+struct PairKey {
+  uint32_t k[4];
+};
+
+// +-h of the entry (u, v), added to sum; nothing for a loop
+__device__ __forceinline__ long long add_pair(long long sum, uint32_t u, uint32_t v,
+                                              const PairKey& key) {
+  const uint64_t x = (uint64_t)(min(u, v) + key.k[0]) * (max(u, v) ^ key.k[1]);
+  int32_t a = (int32_t)(((uint32_t)x ^ key.k[2]) >> 1);
+  a = u > v ? -a : a;
+  a = u == v ? 0 : a;
+  return sum + (long long)a * (int32_t)((uint32_t)(x >> 32) ^ key.k[3]);
+}
+
+// A wave runs an even share of the entries in slices of 64 * U, the next slice's
+// loads issued before a slice is summed; the rows come in windows of 64.
+__global__ __launch_bounds__(PB) void symmetry_kernel(Args a, PairKey key) {
+  constexpr uint32_t U = NARROW_U;
+  __shared__ uint32_t s_row[NW][64];
+  __shared__ __align__(8) uint8_t s_heads[NW][64 * U];
+  __shared__ unsigned long long s_sum[NW];
+  State* st = a.st;
+  if (st->done || st->error || st->plan != V_CHECK) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t n = (uint32_t)a.q[0].n, m = (uint32_t)a.m;
+  const uint32_t nw = gridDim.x * NW, gw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * NW + wave));
+  uint32_t x0 = (uint32_t)((uint64_t)gw * m / nw);
+  const uint32_t x1 = (uint32_t)((uint64_t)(gw + 1) * m / nw);
+  long long sum = 0;
+  if (x0 < x1) {
+    uint32_t r = wave_upper_search(n, x0, lane, [&](uint32_t p) { return (uint32_t)a.rp[p]; });
+    r = (uint32_t)__builtin_amdgcn_readfirstlane((int)r);
+    uint32_t top = 0;  // largest id
+    uint32_t v[U], ahead[U];
+    auto fetch = [&](uint32_t at, uint32_t (&t)[U]) {
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t x = at + u * 64u + (uint32_t)lane;
+        t[u] = x < x1 ? (uint32_t)__builtin_nontemporal_load(&a.col[x]) : 0u;
+      }
+    };
+    fetch(x0, ahead);
+    uint32_t b = (uint32_t)a.rp[min(r + lane, n)], e = (uint32_t)a.rp[min(r + lane + 1, n)];
+    bool fresh = true;  // the window is not in LDS yet
+    bool some = false;
+    uint32_t wend = 0;
+    while (x0 < x1 && r < n) {
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) v[u] = ahead[u];
+      const uint32_t send = min(x1 - x0, 64u * U) + x0;
+      fetch(send, ahead);
+      uint32_t lo = x0;
+      while (true) {
+        if (fresh) {
+          wend = (uint32_t)__builtin_amdgcn_readlane((int)e, 63);
+          some = e > b && e > lo;
+          const unsigned long long rows = __ballot(some);
+          if (some) s_row[wave][lane_rank(rows)] = r + lane;
+          wave_lds_sync();
+          fresh = false;
+        }
+        // the window's entries of the slice: [lo, hi)
+        const uint32_t hi = min(send, wend);
+        if (lo < hi) {
+          const uint32_t first = (uint32_t)__popcll(__ballot(some && b <= lo)) - 1u;
+          const bool begins = some && b > lo && b < hi;
+          const bool whole = lo == x0 && hi == x0 + 64u * U;
+          if (__any(begins)) {
+            clear_heads(s_heads[wave], lane);
+            if (begins) s_heads[wave][b - x0 - 1] = 1;
+            wave_lds_sync();
+            uint32_t p = first;
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+              uint32_t w = s_row[wave][row_of(s_heads[wave], u, lane, p)];
+              if (!whole && x0 + u * 64u + (uint32_t)lane - lo >= hi - lo) w = v[u];
+              sum = add_pair(sum, w, v[u], key);
+            }
+            wave_lds_sync();
+          } else {  // within one row
+            const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_row[wave][first]);
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+              const bool in = whole || x0 + u * 64u + (uint32_t)lane - lo < hi - lo;
+              sum = add_pair(sum, in ? row : v[u], v[u], key);
+            }
+          }
+          lo = hi;
+        }
+        if (wend >= send || r >= n) break;
+        r += 64;
+        b = (uint32_t)a.rp[min(r + lane, n)];
+        e = (uint32_t)a.rp[min(r + lane + 1, n)];
+        fresh = true;
+        wave_lds_sync();
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) top = max(top, v[u]);
+      if (lo < send) break;  // rows that end before the entries do
+      x0 = send;
+    }
+    const bool bad = __any(top >= n) || x0 < x1;
+    if (bad && lane == 0) atomicOr(&st->asymmetric, 1u);
+  }
+#pragma unroll
+  for (int d = 32; d; d >>= 1) sum += __shfl_down(sum, d, 64);
+  if (lane == 0) s_sum[wave] = (unsigned long long)sum;
+  __syncthreads();
+  if (tid == 0) {
+    unsigned long long all = 0;
+    for (int w = 0; w < NW; ++w) all += s_sum[w];
+    if (all) atomicAdd(&st->sym_sum[blockIdx.x & 7], all);
+  }
+}
+
+// A wide BFS level of a symmetric graph, bottom-up: a lane per vertex not yet
+// visited, which looks along its row for a visited neighbour; on a symmetric
+// graph that one is in the frontier (had it been visited earlier, so would the
+// vertex have been).  Where the frontier has a good part of the edges left the
+// first few entries of a row decide, and nothing is written but what is found:
+// no atomic, no found byte.  Reads one bitmap and writes the other, whole words
+// by the wave that owns them.  A vertex without edges counts as visited from
+// then on (no row names it).  Rows are read by their lane up to BU_LANE
+// entries, then by the wave together.  Bound by the lines its row heads lie in:
+// scale 22's growing, widest and next level take 59, 23 and 11 us where a level
+// step takes 270 (growing) and 540 (widest), so that with the check, once per
+// traversal, the traversal goes from 1083 to 484 us.
+__global__ __launch_bounds__(PB) void bottom_up_kernel(Args a) {
+  __shared__ int32_t s_stage[NW][STAGE];
+  __shared__ uint32_t s_bc[NW + 8];
+  constexpr int U = 4;
+  State* st = a.st;
+  if (st->done || st->error || !goes_bottom_up(st)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t L = st->base, n = (uint32_t)a.q[0].n;
+  LevelSet* cur = &st->set[L % 3];
+  int32_t* fout = (L & 1) ? a.front0 : a.front1;
+  const uint32_t c = st->vsel[L & 1];
+  const uint32_t* seen = a.visit + (size_t)c * (uint32_t)a.vwords;
+  uint32_t* next = a.visit + (size_t)(c ^ 1u) * (uint32_t)a.vwords;
+  // what the parent kernel does for the level after
+  if (blockIdx.x == 0) {
+    LevelSet* z = &st->set[(L + 1) % 3];
+    if (tid <= NQF) z->fcnt[tid] = 0;
+    if (tid < NQD) z->qctr[tid] = 0;
+    if (tid < NQD) z->cclaim[tid][0] = 0;
+    if (tid == 0) {
+      st->levels_run = L + 1;
+      st->vsel[(L + 1) & 1] = c ^ 1u;
+      st->vstale[(L + 1) & 1] = 1u;
+    }
+  }
+  for (int i = blockIdx.x * PB + tid; i < a.ngroups_cap; i += gridDim.x * PB) {
+    a.grp_packed[(L + 1) % 3 * a.ngroups_cap + i] = 0;
+    a.grp_done[(L + 1) % 3 * a.ngroups_cap + i] = 0;
+  }
+  Stage s{s_stage[wave], 0u};
+  for (uint32_t b = (blockIdx.x * NW + wave) * 64u; b < (uint32_t)a.slots; b += gridDim.x * PB) {
+    const uint32_t v = b + (uint32_t)lane;
+    const uint32_t word = v < (uint32_t)a.slots ? seen[v >> 5] : ~0u;
+    bool need = v < n && !(word >> (v & 31) & 1u);
+    uint32_t x = 0, e = 0;
+    if (need) {
+      x = (uint32_t)a.rp[v];
+      e = (uint32_t)a.rp[v + 1];
+    }
+    const bool alone = need && x == e;
+    bool found = false;
+    need = x < e;
+    for (uint32_t it = 0; it < BU_LANE / U && __any(need); ++it) {
+      uint32_t w[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) w[u] = need ? (uint32_t)a.col[min(x + u, e - 1)] : 0u;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t bit = w[u] & 31;
+        w[u] = need ? seen[w[u] >> 5] >> bit & 1u : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) found |= w[u] != 0;
+      x += U;
+      need = need && !found && x < e;
+    }
+    for (unsigned long long rest = __ballot(need); rest; rest &= rest - 1) {
+      const int k = __builtin_ctzll(rest);
+      const uint32_t y1 = (uint32_t)__builtin_amdgcn_readlane((int)e, k);
+      bool hit = false;
+      for (uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)x, k); y < y1 && !hit; y += 64 * U) {
+        uint32_t w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = (uint32_t)a.col[min(y + (uint32_t)(u * 64 + lane), y1 - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) hit |= seen[w[u] >> 5] >> (w[u] & 31) & 1u;
+        hit = __any(hit);
+      }
+      found |= hit && lane == k;
+    }
+    const unsigned long long add = __ballot(found || alone);
+    if ((lane & 31) == 0 && v < (uint32_t)a.slots) next[v >> 5] = word | (uint32_t)(add >> (lane & 32));
+    if (found) a.level[v] = (int32_t)L + 1;
+    stage_push(s, found, (int32_t)v, a, cur, fout, lane);
+  }
+  block_flush(s, a, cur, fout, tid, s_bc);
+}
+
 
 // ------------------------------------------------------------ init / admit / advance
 // Traversal-set start: level sets and counters cleared.  Queries are
@@ -1947,6 +2246,10 @@ const void* narrow_kernel_ptr(int problem, int32_t slots) {
   return slots / 32 <= NARROW_BITS ? (const void*)narrow_kernel<PROB_BFS, true>
                                    : (const void*)narrow_kernel<PROB_BFS, false>;
 }
+
+const void* symmetry_kernel_ptr() { return (const void*)symmetry_kernel; }
+
+const void* bottom_up_kernel_ptr() { return (const void*)bottom_up_kernel; }
 
 const void* start_kernel_ptr(int problem) {
   return problem == PROB_BFS ? (const void*)start_kernel<PROB_BFS>
