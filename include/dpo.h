@@ -82,7 +82,8 @@ typedef struct {
   int32_t agg;              /* dpo_agg (Sec. II-B, V-A)                             */
   int32_t agg_blocks;       /* k >= 2 for DPO_AGG_MULTIBLOCK (e.g. 4 or 16)         */
   int32_t child_block;      /* original child block size bDim in {64, 128, 256}    */
-  int32_t steps_per_replay; /* level steps per HIP-graph replay; 0 = 16.  A single
+  int32_t steps_per_replay; /* level steps per HIP-graph replay; 0 = 16 (batch
+                               calls 8).  A single
                                traversal that needs no replays (nested, aggregated,
                                without counters) launches its steps as they come
                                due instead; results are the same               */
@@ -132,16 +133,19 @@ typedef struct {
                                BFS without counters also runs wide levels
                                bottom-up (an unvisited vertex looks for a
                                visited neighbour) if it finds the graph
-                               symmetric.  Speed only.                          */
+                               symmetric; in a batch or a serving engine each
+                               query's.  Speed only.                            */
 } dpo_options;
 
 typedef enum {
   DPO_HINT_AUTO = 0,  /* on for single traversals (dpo_bfs, dpo_sssp and
                          their variants) and the serving engines when the graph
                          (the arena for an engine) has at least 8 directed
-                         entries per vertex; off for the batch calls and
-                         sparser graphs, where many narrow levels would each
-                         pay the extra kernel launch                           */
+                         entries per vertex, and then for a nested, aggregated
+                         BFS batch without counters whose queries have at least
+                         as many vertices as the arena; off for the other batch
+                         calls and sparser graphs, where many narrow levels
+                         would each pay the extra kernel launch                */
   DPO_HINT_ON = 1,
   DPO_HINT_OFF = 2
 } dpo_claim_hint;

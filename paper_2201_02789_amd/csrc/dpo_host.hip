@@ -24,6 +24,7 @@ namespace dpo {
 namespace {
 
 constexpr int kDefaultSteps = 16;
+constexpr int kBatchSteps = 8;  // a batch of skewed graphs is done in one or two such replays
 constexpr int kMaxCachedGraphs = 64;
 constexpr int kStepsAhead = 4;  // dpo_bfs_noalloc: level steps per look at the flags
 
@@ -230,7 +231,7 @@ dpo_status add_node(hipGraph_t graph, hipGraphNode_t* prev, const void* fn, int 
   return DPO_OK;
 }
 
-// K level steps (parent kernel, then child kernel unless flat, then the third
+// K level steps (BU_QUERIES: the tally and the bottom-up kernels first; parent kernel, then child kernel unless flat, then the third
 // kernel if any: SSSP's thresholded children, on the parent kernel's grid, or
 // BFS's harvest; then the fourth if any: SSSP's harvest) and the advance of the
 // level base, which reports to `flags` (host, pinned), as one instantiated
@@ -257,7 +258,15 @@ dpo_status get_exec(Runtime& r, const void* parent, const void* child, const voi
   for (int i = 0; i < steps && s == DPO_OK; ++i) {
     step_ids[i] = (uint32_t)i;
     void* params[] = {&a, &step_ids[i]};
-    s = add_node(graph, &prev, parent, pgrid, PB, params);
+    if (a.bottom_up == BU_QUERIES) {
+      s = add_node(graph, &prev, tally_kernel_ptr(), 2 * r.cu_count, PB, params);
+      if (s == DPO_OK)
+        s = add_node(graph, &prev, bottom_up_words_kernel_ptr(), r.cu_count, QB, params);
+      if (s == DPO_OK)
+        s = add_node(graph, &prev, bottom_up_queries_kernel_ptr(),
+                     persistent_grid(r, bottom_up_queries_kernel_ptr()), PB, params);
+    }
+    if (s == DPO_OK) s = add_node(graph, &prev, parent, pgrid, PB, params);
     if (s == DPO_OK && child) s = add_node(graph, &prev, child, cgrid, PB, params);
     if (s == DPO_OK && third) s = add_node(graph, &prev, third, tgrid, PB, params);
     if (s == DPO_OK && fourth) s = add_node(graph, &prev, fourth, fgrid, PB, params);
@@ -302,6 +311,7 @@ struct SetRun {
   const void* third = nullptr;
   const void* fourth = nullptr;
   int pgrid = 0, cgrid = 0, tgrid = 0, fgrid = 0, steps = kDefaultSteps;
+  int32_t n = 0;  // vertices of the graph (the arena)
   hipStream_t stream = nullptr;
   int32_t* qlist = nullptr;  // device: indices of the queries being admitted
 };
@@ -317,18 +327,24 @@ dpo_status prepare_set(Runtime& r, int problem, const dpo_csr* g, const dpo_opti
   if (ws_bytes < lay.total) return DPO_ERR_WORKSPACE;
   const int gran = gran_of(o);
   sr->problem = problem;
+  sr->n = g->n;
   sr->lay = lay;
-  // Found bytes and the harvest (BFS: with per-XCD copies): single traversals
-  // and the serving engine (not a batch call) on graphs whose average degree
-  // is at least HINT_AUTO_MIN_DEGREE, unless the options say otherwise.  The
-  // harvest adds a kernel launch to every level step; a graph of low average
-  // degree runs many narrow levels and rarely a wide one.
+  // Found bytes and the harvest (BFS: with per-XCD copies): single traversals,
+  // the serving engine and batches whose queries go bottom-up, on graphs whose
+  // average degree is at least HINT_AUTO_MIN_DEGREE, unless the options say
+  // otherwise.  The harvest adds a kernel launch to every level step; a graph of
+  // low average degree runs many narrow levels and rarely a wide one.
   const bool dense = g->m >= (int64_t)HINT_AUTO_MIN_DEGREE * g->n;
-  const bool hint = o.claim_hint == DPO_HINT_ON ||
-                    (o.claim_hint == DPO_HINT_AUTO && !batch_call && dense);
   const bool bfs = problem == PROB_BFS;
+  // Queries that go bottom-up by themselves: a serving engine, and a batch that
+  // is at least as large as its arena (the symmetry check reads all of it, and
+  // is about 8 times as fast per entry as a traversal).  They use found bytes.
+  const bool by_query = bfs && (batch_call ? slots >= g->n : nq > 1) && gran != AGG_FLAT &&
+                        gran != AGG_NONE && !count_stats && !tm;
+  const bool hint = o.claim_hint == DPO_HINT_ON ||
+                    (o.claim_hint == DPO_HINT_AUTO && (!batch_call || by_query) && dense);
   sr->parent = parent_kernel_ptr(problem, gran);
-  sr->child = gran == AGG_FLAT ? nullptr : child_kernel_ptr(problem, false, hint);
+  sr->child = gran == AGG_FLAT ? nullptr : child_kernel_ptr(problem, false, hint && !batch_call);
   sr->third = bfs ? (hint ? harvest_kernel_ptr(problem) : nullptr) : serial_kernel_ptr(problem, gran);
   sr->fourth = !bfs && hint ? harvest_kernel_ptr(problem) : nullptr;
   if (!sr->parent) return DPO_ERR_UNSUPPORTED;
@@ -373,18 +389,22 @@ dpo_status prepare_set(Runtime& r, int problem, const dpo_csr* g, const dpo_opti
   a.desc_cap = lay.desc_cap;
   a.fcap = lay.fcap;
   a.count_stats = count_stats ? 1 : 0;
+  static_assert(4 * MAX_QUERIES * 4 <= MAX_GRID * NSTAT * 8, "the tallies take the counters' place");
+  a.bottom_up = by_query && hint ? BU_QUERIES : BU_OFF;
+  a.tally = (uint32_t*)(base + lay.stats);
   sr->qlist = (int32_t*)(base + lay.qlist);
   sr->pgrid = persistent_grid(r, sr->parent);
   // the thresholded children's kernel walks the lists of the parent kernel's
   // workgroups: one grid for both, all of it resident in either
   if (sr->third && !bfs) sr->pgrid = std::min(sr->pgrid, persistent_grid(r, sr->third));
   sr->cgrid = sr->child ? persistent_grid(r, sr->child) : 0;
-  // the harvest: as many workgroups as its rounds need, at most the parent
-  // grid (a small graph's many narrow levels launch it empty)
-  const int hgrid = (int)std::min<int64_t>(sr->pgrid, cdiv(slots, (int64_t)PB * HARVEST_RUNS));
+  // the harvest: as many workgroups as its rounds need, at most those resident
+  // (a small graph's many narrow levels launch it empty)
+  const int hgrid = (int)std::min<int64_t>(persistent_grid(r, harvest_kernel_ptr(problem)),
+                                           cdiv(slots, (int64_t)PB * HARVEST_RUNS));
   sr->tgrid = !sr->third ? 0 : bfs ? hgrid : sr->pgrid;
   sr->fgrid = sr->fourth ? hgrid : 0;
-  sr->steps = o.steps_per_replay ? o.steps_per_replay : kDefaultSteps;
+  sr->steps = o.steps_per_replay ? o.steps_per_replay : batch_call ? kBatchSteps : kDefaultSteps;
   sr->stream = (hipStream_t)stream;
   if (tm) {
     sr->parent = parent_kernel_ptr(problem, gran, true);
@@ -472,6 +492,33 @@ dpo_status start_set(Runtime& r, SetRun& sr) {
   return DPO_OK;
 }
 
+// Symmetry check of the graph; vbase, ngraphs: of the graphs of an arena (device).
+dpo_status launch_symmetry(Runtime& r, SetRun& sr, const uint32_t* vbase = nullptr,
+                           uint32_t ngraphs = 0) {
+  uint32_t n = (uint32_t)sr.n;
+  uint32_t key[4] = {(uint32_t)r.keys(), (uint32_t)r.keys(), (uint32_t)r.keys(), (uint32_t)r.keys()};
+  void* p[] = {&sr.a, &n, key, &vbase, &ngraphs};
+  const int64_t grid = std::min<int64_t>(cdiv(sr.a.m, (int64_t)NW * SYM_EDGES), 8 * (int64_t)r.cu_count);
+  return hip_ok(hipLaunchKernel(symmetry_kernel_ptr(vbase != nullptr), dim3((unsigned)std::max<int64_t>(grid, 1)),
+                                dim3(PB), p, 0, sr.stream));
+}
+
+// The same for an arena, and its result into the state (BU_QUERIES).  An arena
+// of more graphs than the space behind the tallies holds stays unchecked, and
+// its queries top-down.
+dpo_status check_symmetry(Runtime& r, SetRun& sr, const int32_t* graph_vbase, int32_t ngraphs) {
+  uint32_t* vbase = sr.a.tally + 4 * sr.a.nq;
+  if ((size_t)(4 * sr.a.nq + ngraphs + 1) * 4 > (size_t)MAX_GRID * NSTAT * 8) return DPO_OK;
+  // (pageable memory: copied before the call returns)
+  if (hipMemcpyAsync(vbase, graph_vbase, (size_t)(ngraphs + 1) * 4, hipMemcpyHostToDevice, sr.stream) !=
+      hipSuccess)
+    return DPO_ERR_HIP;
+  dpo_status s = launch_symmetry(r, sr, vbase, (uint32_t)ngraphs);
+  void* p[] = {&sr.a.st};
+  return s != DPO_OK ? s
+                     : hip_ok(hipLaunchKernel(settle_symmetry_kernel_ptr(), dim3(1), dim3(64), p, 0, sr.stream));
+}
+
 // Start of a single traversal (one launch instead of init and admission).
 dpo_status start_single(Runtime& r, SetRun& sr, const Query& q) {
   Query Q = q;
@@ -532,16 +579,11 @@ dpo_status launch_narrow(SetRun& sr, uint32_t after, uint32_t ticket, uint32_t* 
                                 sr.stream));
 }
 
-// A bottom-up level, if one is due; check: the symmetry check first, if due.
+// A bottom-up level of a single traversal, if one is due; check: the symmetry
+// check first, if due.
 dpo_status launch_bottom_up(Runtime& r, SetRun& sr, bool check) {
-  if (check) {
-    uint32_t key[4] = {(uint32_t)r.keys(), (uint32_t)r.keys(), (uint32_t)r.keys(), (uint32_t)r.keys()};
-    void* p[] = {&sr.a, key};
-    const int64_t grid = std::min<int64_t>(cdiv(sr.a.m, (int64_t)NW * SYM_EDGES), 8 * (int64_t)r.cu_count);
-    if (hipLaunchKernel(symmetry_kernel_ptr(), dim3((unsigned)std::max<int64_t>(grid, 1)), dim3(PB), p,
-                        0, sr.stream) != hipSuccess)
-      return DPO_ERR_HIP;
-  }
+  dpo_status s = check ? launch_symmetry(r, sr) : DPO_OK;
+  if (s != DPO_OK) return s;
   void* p[] = {&sr.a};
   const int64_t grid = std::min<int64_t>(cdiv(sr.a.slots, PB), persistent_grid(r, bottom_up_kernel_ptr()));
   return hip_ok(hipLaunchKernel(bottom_up_kernel_ptr(), dim3((unsigned)grid), dim3(PB), p, 0, sr.stream));
@@ -655,7 +697,7 @@ dpo_status traverse(int problem, const dpo_csr* g, int32_t source, const dpo_opt
   if (s != DPO_OK) return s;
   if (tm && hipMemsetAsync(tm, 0, DPO_TIMING_BYTES, sr.stream) != hipSuccess) return DPO_ERR_HIP;
   const bool narrow = use_narrow(sr, *o, st != nullptr, tm != nullptr);
-  sr.a.bottom_up = narrow && problem == PROB_BFS ? sr.a.hint : 0;
+  sr.a.bottom_up = narrow && problem == PROB_BFS && sr.a.hint ? BU_SINGLE : BU_OFF;
   s = start_single(r, sr, Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source});
   if (s != DPO_OK) return s;
   s = narrow ? run_narrow_and_wide(r, sr, g->n) : run_to_completion(r, sr, g->n);
@@ -725,6 +767,8 @@ dpo_status traverse_batch(int problem, const dpo_arena* ar, const dpo_query* qs,
   for (int32_t i = 0; i < nq; ++i) hl[i] = i;
   if ((s = start_set(r, sr)) != DPO_OK) return s;
   if ((s = admit_all(r, sr, hq, hl, nq)) != DPO_OK) return s;
+  if (sr.a.bottom_up && (s = check_symmetry(r, sr, ar->graph_vbase, ar->ngraphs)) != DPO_OK)
+    return s;
   if ((s = run_to_completion(r, sr, slots)) != DPO_OK) return s;
   return read_stats(r, sr, st);
 }
@@ -776,7 +820,7 @@ dpo_status traverse_noalloc(int problem, const dpo_csr* g, int32_t source, const
   // outputs and the visited state, so nothing left in the array by an earlier
   // call is read
   const bool narrow = use_narrow(sr, *o, false, false);
-  sr.a.bottom_up = narrow ? sr.a.hint : 0;
+  sr.a.bottom_up = narrow && sr.a.hint ? BU_SINGLE : BU_OFF;
   s = start_single(r, sr, Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source});
   if (s != DPO_OK) return s;
   uint32_t flags[4] = {0, 0, 0, 0};  // base, done, error, levels_run
@@ -851,6 +895,8 @@ struct dpo_engine {
   int32_t* hlist = nullptr;   // pinned
   uint32_t* hflags = nullptr; // pinned
   int64_t max_n = 0;
+  int64_t served = 0;  // vertices of the queries admitted since the engine was last idle
+  bool checked = false;  // the arena's symmetry, since then
 };
 
 namespace dpo {
@@ -942,8 +988,18 @@ dpo_status engine_step(dpo_engine* e) {
     if (reset) {
       // nothing was running: restart the level sets (and their counters)
       if ((s = start_set(r, sr)) != DPO_OK) return s;
+      e->served = 0;
+      e->checked = false;
     }
     if ((s = admit(r, sr, e->hq, e->hlist, count, 0)) != DPO_OK) return s;
+    for (int32_t k = 0; k < count; ++k) e->served += e->hq[e->hlist[k]].n;
+    if (sr.a.bottom_up && !e->checked && e->served >= sr.n) {
+      // enough work for the check to pay (see prepare_set); the answer holds
+      // until the engine is idle
+      if ((s = check_symmetry(r, sr, e->vbase.data(), (int32_t)e->vbase.size() - 1)) != DPO_OK)
+        return s;
+      e->checked = true;
+    }
   }
   if (e->running > 0) {
     if (hipGraphLaunch(e->exec, sr.stream) != hipSuccess) return DPO_ERR_HIP;

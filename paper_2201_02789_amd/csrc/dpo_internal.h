@@ -22,7 +22,7 @@ constexpr int ADMIT_CHUNK = 4096;  // output slots initialised per admit workgro
 constexpr int PRECHECK_MIN = 32;   // claim candidates per 512-lane batch above which
                                    // a coherent load precedes the atomics
 constexpr int NHINT = 8;           // BFS per-XCD visited copies (Args::hint), one per XCD
-constexpr int HARVEST_RUNS = 4;    // harvest kernel: 64-slot runs per wave and round
+constexpr int HARVEST_RUNS = 8;    // harvest kernel: 64-slot runs per wave and round
 constexpr int HINT_AUTO_MIN_DEGREE = 8;  // DPO_HINT_AUTO: per-XCD copies from this average
                                          // degree (m / n) up
 // narrow levels (one workgroup, frontier in LDS)
@@ -59,6 +59,15 @@ enum { AFTER_NONE = 0, AFTER_STEP, AFTER_BOTTOM_UP, AFTER_ANY };
 // 160 / 121 / 122 / 123 at 4 / 8 / 16 / 32, scale 22 620 / 606 / 582 / 590,
 // Erdos-Renyi of 2 M 518 / 512 / 512 / 515.
 constexpr uint32_t BU_ALPHA = 16;
+// Several queries: frontier entries from which a level's edges are tallied, and
+// edges from which a query may go bottom-up (fewer are run top-down in less
+// time than the tally and the bottom-up kernel take).
+constexpr uint32_t TALLY_MIN = 8192;
+constexpr uint32_t TALLY_SAMPLE = 1 << 17;  // of them read, about
+constexpr uint32_t BU_QUERY_EDGES = 1 << 14;
+constexpr uint32_t BU_GROUP = 16;  // queries of one graph run together (bits of a word)
+constexpr int QB = 1024;           // workgroup that lists them
+constexpr uint32_t BU_SORT = QB;   // queries it puts in order of their graphs
 constexpr uint32_t BU_LANE = 32;    // edges a lane looks at before the wave shares its row
 constexpr uint32_t SYM_EDGES = 1024;  // symmetry check: least edges per wave
 constexpr uint32_t SYM_SAMPLES = 128;  // entries whose reverse is looked up first, if
@@ -106,7 +115,7 @@ struct State {
   uint32_t symmetric;   // 0 not checked, 1 yes, 2 no
   unsigned long long run_edges;  // edges of the levels so far (about)
   unsigned long long sym_sum[8];  // symmetry check: shares of the signed sum
-  uint32_t asymmetric;  // symmetry check: an id out of range was met
+  uint32_t asymmetric;  // symmetry check: met an id out of range
   uint32_t pad[33];
   LevelSet set[3];
 };
@@ -178,8 +187,16 @@ struct Args {
                                    // XCD), discoveries taken into bitmap 0 by the harvest;
                                    // SSSP: improvements queued by the harvest instead of
                                    // iteration stamps
-  int32_t bottom_up;               // wide BFS levels may go bottom-up (with Args::hint)
+  int32_t bottom_up;               // wide BFS levels may go bottom-up (with Args::hint):
+                                   // BU_SINGLE as the narrow kernel plans, BU_QUERIES each
+                                   // query's by its tallied edges
+  uint32_t* tally;                 // BU_QUERIES: [nq] each: edges of the frontier at an even
+                                   // level, at an odd one, of all levels tallied, of the graph;
+                                   // then the arena's graph_vbase for the symmetry check (all
+                                   // in the place of Args::stats, whose counters are off)
 };
+
+enum { BU_OFF = 0, BU_SINGLE = 1, BU_QUERIES = 2 };
 
 // timed: the instantiation that stamps its phases into Args::tm
 const void* parent_kernel_ptr(int problem, int gran, bool timed = false);
@@ -190,8 +207,12 @@ const void* serial_kernel_ptr(int problem, int gran, bool timed = false);
 const void* harvest_kernel_ptr(int problem, bool timed = false);
 const void* init_kernel_ptr(int problem);
 const void* narrow_kernel_ptr(int problem, int32_t slots);
-const void* symmetry_kernel_ptr();
+const void* symmetry_kernel_ptr(bool arena);
 const void* bottom_up_kernel_ptr();
+const void* tally_kernel_ptr();
+const void* bottom_up_words_kernel_ptr();
+const void* bottom_up_queries_kernel_ptr();
+const void* settle_symmetry_kernel_ptr();
 const void* start_kernel_ptr(int problem);
 const void* admit_kernel_ptr(int problem);
 const void* admit_sources_kernel_ptr();

@@ -459,6 +459,17 @@ __device__ __forceinline__ bool goes_bottom_up(const State* st) {
   return st->plan == V_BOTTOM_UP || (st->plan == V_CHECK && found_symmetric(st));
 }
 
+// Does query q go bottom-up at level L?  Its frontier's edges against those it
+// has not run, as for a single traversal (BU_ALPHA).  The tallies do not change
+// between the tally kernel of a level and the next level's.
+__device__ __forceinline__ bool query_goes_bottom_up(const Args& a, uint32_t q, uint32_t L) {
+  const uint32_t* t = a.tally;
+  const uint32_t nq = (uint32_t)a.nq, E = t[(L & 1) * nq + q];
+  if (E < BU_QUERY_EDGES) return false;
+  const uint32_t before = t[2 * nq + q] - E, m = t[3 * nq + q];
+  return (uint64_t)E * BU_ALPHA >= (m > before ? m - before : 0u);
+}
+
 // Append one aggregated grid to descriptor queue q (one lane).
 __device__ __forceinline__ void publish(const Args& a, LevelSet* ls, uint32_t q, uint32_t rec_base,
                                         uint32_t nrec, uint32_t total) {
@@ -521,6 +532,24 @@ __device__ __forceinline__ Parent load_parent(const Args& a, const int32_t* fin,
   return p;
 }
 
+// Multi-block groups: virtual block vb of the level's nvb is through; true for
+// its group's last one (one lane), which publishes the group's grid.
+__device__ __forceinline__ bool group_block_done(const Args& a, uint32_t vb, uint32_t nvb, uint32_t L) {
+  const uint32_t g = vb / (uint32_t)a.k;
+  const uint32_t in_group = min((uint32_t)a.k, nvb - g * (uint32_t)a.k);
+  return atomicAdd(&a.grp_done[(L % 3) * a.ngroups_cap + g], 1u) == in_group - 1;
+}
+
+__device__ __forceinline__ void publish_group(const Args& a, LevelSet* ls, uint32_t vb, uint32_t L,
+                                              uint32_t& descs) {
+  const uint32_t g = vb / (uint32_t)a.k;
+  const unsigned long long tot = atomicAdd(&a.grp_packed[(L % 3) * a.ngroups_cap + g], 0ull);
+  const uint32_t nrec = (uint32_t)(tot >> 32);
+  if (nrec == 0) return;
+  publish(a, ls, g % NQD, g * (uint32_t)a.k * PB, nrec, (uint32_t)tot);
+  ++descs;
+}
+
 // ------------------------------------------------------------ parent kernel
 // Pass 1 reads each frontier entry once, decides it (threshold), aggregates
 // the launching ones and writes their records (block barriers) and lists the
@@ -539,6 +568,11 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
   __shared__ uint32_t s_bc[NW + 8];
   __shared__ unsigned long long s_stats[NSTAT];
   __shared__ uint32_t s_live[MAX_QUERIES / 32];  // queries seen at this level
+  __shared__ uint32_t s_up[P == PROB_BFS ? MAX_QUERIES / 32 : 1];  // queries that go bottom-up
+  // virtual blocks with entries of others (wrapping round: a bit too many only
+  // costs its block's time)
+  constexpr int SOME_WORDS = P == PROB_BFS ? 32 : 1;
+  __shared__ uint32_t s_some[SOME_WORDS];
   __shared__ uint32_t s_ser[2];                  // serial list: length, next entry
   __shared__ uint32_t s_soff[NW][64];            // per wave: scanned child sizes of a group
   __shared__ uint32_t s_lpre[PH == PH_SERIAL ? MAX_GRID + 1 : 1];  // prefix of list lengths
@@ -582,7 +616,9 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
   }
   // visited copies of this level (every workgroup derives the same choice)
   const uint32_t vc = st->vsel[L & 1];
-  const bool split = F >= (uint32_t)a.split_min;
+  // (found bytes of queries that go bottom-up are harvested on split levels)
+  const bool by_query = P == PROB_BFS && a.bottom_up == BU_QUERIES && st->symmetric == 1 && F >= TALLY_MIN;
+  const bool split = F >= (uint32_t)a.split_min || by_query;
   const bool stale = st->vstale[L & 1] != 0;
   const Vis vis = vis_of<P>(a, vc, split);
   if (PH != PH_SERIAL && blockIdx.x == 0) {
@@ -597,6 +633,9 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
       st->vstale[(L + 1) & 1] = (P == PROB_BFS && !split) ? 1u : 0u;
     }
   }
+  if (P == PROB_BFS && a.bottom_up == BU_QUERIES)
+    for (int i = blockIdx.x * PB + tid; i < a.nq; i += gridDim.x * PB)
+      a.tally[((L + 1) & 1) * a.nq + i] = 0;
   if (G == AGG_MULTI && PH != PH_SERIAL) {
     const uint32_t nz = (L + 1) % 3;
     for (int i = blockIdx.x * PB + tid; i < a.ngroups_cap; i += gridDim.x * PB) {
@@ -604,6 +643,12 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
       a.grp_done[nz * a.ngroups_cap + i] = 0;
     }
   }
+
+  if (by_query)
+    for (int i = tid; i < (a.nq + 63) / 64 * 64; i += PB) {
+      const unsigned long long m = __ballot(i < a.nq && query_goes_bottom_up(a, (uint32_t)i, L));
+      if ((lane & 31) == 0) s_up[i >> 5] = (uint32_t)(m >> (lane & 32));
+    }
 
   Stage s{s_stage[wave], 0u};
   Counters cn{0, 0, 0, 0, 0, 0, 0};
@@ -640,6 +685,36 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
   int32_t e = 0, end = 0;     // this lane's serial child: edges [e, end)
   Elem ctx{0, 0, 0, 0, 0u};
 
+  // Queries that go bottom-up: their entries are not this kernel's, and only
+  // noted as live.  Which of the workgroup's virtual blocks hold others is found
+  // first, four at a time, because a level has most entries when most queries go
+  // bottom-up (512 queries: 13 M entries in 40 rounds of dependent loads and
+  // barriers otherwise).
+  auto goes_up = [&](uint32_t i) {
+    const uint32_t q = (uint32_t)a.qmap[(uint32_t)frontier_at(a, fin, s_fpre, i) >> 5];
+    const bool up = s_up[q >> 5] >> (q & 31) & 1u;
+    if (up && !(s_live[q >> 5] >> (q & 31) & 1u)) atomicOr(&s_live[q >> 5], 1u << (q & 31));
+    return up;
+  };
+  if (by_query) {
+    for (int i = tid; i < SOME_WORDS; i += PB) s_some[P == PROB_BFS ? i : 0] = 0;
+    __syncthreads();
+    const uint32_t rounds = blockIdx.x < nvb ? (nvb - 1 - blockIdx.x) / gridDim.x + 1 : 0;
+    for (uint32_t r = 0; r < rounds; r += 4) {
+      uint32_t bits = 0;
+#pragma unroll
+      for (uint32_t c = 0; c < 4; ++c) {
+        const uint64_t i = ((uint64_t)blockIdx.x + (uint64_t)(r + c) * gridDim.x) * PB + tid;
+        if (r + c < rounds && i < F && !goes_up((uint32_t)i)) bits |= 1u << c;
+      }
+#pragma unroll
+      for (uint32_t c = 0; c < 4; ++c)
+        if (__any(bits >> c & 1u) && lane == 0)
+          atomicOr(&s_some[P == PROB_BFS ? (r + c) / 32 % SOME_WORDS : 0], 1u << ((r + c) & 31));
+    }
+    __syncthreads();
+  }
+
   // ---- pass 1: every frontier entry once.  Threshold, coarsened grid size,
   // aggregation and launch records; thresholded parents go to this
   // workgroup's serial list for pass 2.
@@ -648,14 +723,24 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
     int32_t start = 0, deg = 0, q = 0, slot = 0;
     uint32_t du = 0, cg = 0;
     bool launch = false, ser = false;
-    if (i < F) {
+    if (by_query) {
+      const uint32_t r = (vb - blockIdx.x) / gridDim.x;
+      if (!(s_some[P == PROB_BFS ? r / 32 % SOME_WORDS : 0] >> (r & 31) & 1u)) {
+        // nothing here for this kernel, but its group still counts the block
+        if (G == AGG_MULTI && tid == 0 && group_block_done(a, vb, nvb, L))
+          publish_group(a, cur, vb, L, cn.desc);
+        continue;
+      }
+    }
+    const bool mine = i < F && !(by_query && goes_up(i));
+    if (mine) {
       const Parent p = load_parent<P>(a, fin, s_fpre, i, L);
       start = p.start;
       deg = p.deg;
       q = (int32_t)p.q;
       slot = p.slot;
       ++cn.front;
-      atomicOr(&s_live[p.q >> 5], 1u << (p.q & 31));
+      if (!(s_live[p.q >> 5] >> (p.q & 31) & 1u)) atomicOr(&s_live[p.q >> 5], 1u << (p.q & 31));
       if (P == PROB_SSSP) {
         du = vis.probe[slot];
         // PH_LIST runs before any relaxation of its level, so this is the
@@ -781,7 +866,6 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
           const uint32_t g = vb / (uint32_t)a.k;
           const uint32_t seg = g * (uint32_t)a.k * PB;
           unsigned long long* gp = &a.grp_packed[(L % 3) * a.ngroups_cap + g];
-          uint32_t* gd = &a.grp_done[(L % 3) * a.ngroups_cap + g];
           if (tid == 0) {
             unsigned long long old = 0;
             if (nrec_b)
@@ -798,19 +882,9 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
           // the group's last block to finish "launches" the aggregated grid;
           // its packed-counter add returned before this increment was issued
           bool last_block = false;
-          if (tid == 0) {
-            const uint32_t in_group = min((uint32_t)a.k, nvb - g * (uint32_t)a.k);
-            last_block = atomicAdd(gd, 1u) == in_group - 1;
-          }
+          if (tid == 0) last_block = group_block_done(a, vb, nvb, L);
           pc.mark(TP_AGG);
-          if (last_block) {
-            const unsigned long long tot = atomicAdd(gp, 0ull);
-            const uint32_t nrec_g = (uint32_t)(tot >> 32);
-            if (nrec_g) {
-              publish(a, cur, g % NQD, seg, nrec_g, (uint32_t)tot);
-              ++cn.desc;
-            }
-          }
+          if (last_block) publish_group(a, cur, vb, L, cn.desc);
           pc.mark(TP_LAUNCH);
           __syncthreads();  // s_scan / s_bc reuse
         }
@@ -1321,9 +1395,8 @@ __global__ __launch_bounds__(PB) void child_kernel(Args a, uint32_t step) {
 // its byte is cleared for the next level.  BFS with per-XCD copies, after a
 // wide level: a found vertex that the visited bitmap lacks was discovered at
 // this level.  It gets its level, its bit there and a place in the next frontier (in slot order, which also
-// makes the next level's row loads mostly consecutive).  One lane per slot: a
-// run of 64 slots is 64 found bytes and the two bitmap words they map to, which
-// the wave that reads them owns for the kernel.  Found bytes are never cleared within a
+// makes the next level's row loads mostly consecutive).  A wave owns the found
+// bytes and the bitmap bytes of 512 slots at a time.  Found bytes are never cleared within a
 // traversal: one set at an earlier level belongs to a vertex that the harvest
 // of that level put into the bitmap.  Admission clears a query's found bytes,
 // and a serving engine clears all of them when it is created
@@ -1351,35 +1424,28 @@ __global__ __launch_bounds__(PB) void harvest_kernel(Args a, uint32_t step) {
   // BFS: a single traversal has one level value; with several queries it is
   // looked up per found vertex
   const int32_t lv1 = P == PROB_BFS ? (int32_t)(L + 1) - a.q[0].lstart : 0;
-  // HU runs of 64 slots per wave and round, all their loads issued first
-  constexpr int HU = HARVEST_RUNS;
-  for (uint32_t b = (blockIdx.x * NW + wave) * (64u * HU); b < n; b += gridDim.x * PB * HU) {
-    uint32_t c[HU];
-    bool f[HU];
-#pragma unroll
-    for (int k = 0; k < HU; ++k) {
-      const uint32_t v = b + (uint32_t)k * 64u + (uint32_t)lane;
-      c[k] = (P == PROB_BFS && v < n) ? seen[v >> 5] : 0u;
-      f[k] = v < n && a.found[v] != 0;
+  // A lane reads the found bytes of 8 slots and, for BFS, their byte of the
+  // bitmap; the runs of 64 slots with something new are then spread over the
+  // wave, a lane per slot.
+  const uint8_t* seen8 = (const uint8_t*)seen;
+  for (uint32_t b = (blockIdx.x * NW + wave) * 512u; b < n; b += gridDim.x * PB * 8) {
+    const uint32_t v8 = b + (uint32_t)lane * 8u;
+    uint32_t bits = 0;
+    if (v8 < n) {  // (n is a multiple of 32)
+      const unsigned long long f = *(const unsigned long long*)(a.found + v8);
+      bits = (uint32_t)((f * 0x0102040810204080ull) >> 56);  // byte j (0 or 1) -> bit j
+      if (P == PROB_BFS) bits &= ~(uint32_t)seen8[v8 >> 3];
+      else if (f) *(unsigned long long*)(a.found + v8) = 0;
     }
-#pragma unroll
-    for (int k = 0; k < HU; ++k) {
-      const uint32_t v = b + (uint32_t)k * 64u + (uint32_t)lane;
-      if (P == PROB_SSSP) {
-        if (f[k]) a.found[v] = 0;
-        stage_push(s, f[k], (int32_t)v, a, cur, fout, lane);
-        continue;
-      }
-      const bool nw = f[k] && !((c[k] >> (v & 31)) & 1u);
-      const unsigned long long m = __ballot(nw);
-      if (m) {  // wave-uniform
-        if (nw) a.level[v] = a.nq == 1 ? lv1 : (int32_t)(L + 1) - a.q[a.qmap[v >> 5]].lstart;
-        // lanes 0 and 32 own the words of the run's slots 0 .. 31 and 32 .. 63
-        if ((lane & 31) == 0) {
-          const uint32_t bits = (uint32_t)(m >> (lane & 32));
-          if (bits) seen[v >> 5] = c[k] | bits;
-        }
-      }
+    const unsigned long long some = __ballot(bits != 0);
+    if (some == 0) continue;
+    if (P == PROB_BFS && bits) ((uint8_t*)seen)[v8 >> 3] = (uint8_t)(seen8[v8 >> 3] | bits);
+    for (uint32_t k = 0; k < 8; ++k) {
+      if (!(some >> (8 * k) & 0xFFull)) continue;
+      const uint32_t v = b + k * 64u + (uint32_t)lane;
+      const bool nw = (uint32_t)__shfl((int)bits, (int)(8 * k) + (lane >> 3), 64) >> (lane & 7) & 1u;
+      if (P == PROB_BFS && nw)
+        a.level[v] = a.nq == 1 ? lv1 : (int32_t)(L + 1) - a.q[a.qmap[v >> 5]].lstart;
       stage_push(s, nw, (int32_t)v, a, cur, fout, lane);
     }
   }
@@ -1827,15 +1893,21 @@ __device__ __forceinline__ long long add_pair(long long sum, uint32_t u, uint32_
 
 // A wave runs an even share of the entries in slices of 64 * U, the next slice's
 // loads issued before a slice is summed; the rows come in windows of 64.
-__global__ __launch_bounds__(PB) void symmetry_kernel(Args a, PairKey key) {
+// ARENA: `vbase` holds the first vertex of each of `ngraphs` graphs (and n after
+// them), and an entry that leaves its row's graph counts as asymmetric too: a
+// bottom-up level might pass it by, where a top-down one reports it.
+template <bool ARENA>
+__global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, PairKey key,
+                                                      const uint32_t* vbase, uint32_t ngraphs) {
   constexpr uint32_t U = NARROW_U;
   __shared__ uint32_t s_row[NW][64];
+  __shared__ uint32_t s_lo[ARENA ? NW : 1][64], s_n[ARENA ? NW : 1][64];  // its graph's vertices
   __shared__ __align__(8) uint8_t s_heads[NW][64 * U];
   __shared__ unsigned long long s_sum[NW];
   State* st = a.st;
-  if (st->done || st->error || st->plan != V_CHECK) return;
+  if (st->done || st->error || (st->plan != V_CHECK && a.bottom_up != BU_QUERIES)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint32_t n = (uint32_t)a.q[0].n, m = (uint32_t)a.m;
+  const uint32_t m = (uint32_t)a.m;
   const uint32_t nw = gridDim.x * NW, gw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * NW + wave));
   uint32_t x0 = (uint32_t)((uint64_t)gw * m / nw);
   const uint32_t x1 = (uint32_t)((uint64_t)(gw + 1) * m / nw);
@@ -1843,7 +1915,11 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, PairKey key) {
   if (x0 < x1) {
     uint32_t r = wave_upper_search(n, x0, lane, [&](uint32_t p) { return (uint32_t)a.rp[p]; });
     r = (uint32_t)__builtin_amdgcn_readfirstlane((int)r);
-    uint32_t top = 0;  // largest id
+    uint32_t top = 0;     // largest id
+    bool leaves = false;  // an entry leaves its graph
+    uint32_t g0 = 0, g1 = 0;  // vertices of the lane's row's graph, as of the last window
+    bool one = true;          // the window's rows are of one graph,
+    uint32_t u0 = 0, un = 0;  // with these vertices
     uint32_t v[U], ahead[U];
     auto fetch = [&](uint32_t at, uint32_t (&t)[U]) {
 #pragma unroll
@@ -1869,6 +1945,25 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, PairKey key) {
           some = e > b && e > lo;
           const unsigned long long rows = __ballot(some);
           if (some) s_row[wave][lane_rank(rows)] = r + lane;
+          if (ARENA && some) {
+            if (r + lane >= g1) {
+              uint32_t g = 0, end = ngraphs;
+              while (end - g > 1) {
+                const uint32_t mid = (g + end) >> 1;
+                if (vbase[mid] <= r + lane) g = mid; else end = mid;
+              }
+              g0 = vbase[g];
+              g1 = vbase[g + 1];
+            }
+            s_lo[wave][lane_rank(rows)] = g0;
+            s_n[wave][lane_rank(rows)] = g1 - g0;
+          }
+          if (ARENA && rows) {
+            const int l = __builtin_ctzll(rows);
+            u0 = (uint32_t)__builtin_amdgcn_readlane((int)g0, l);
+            un = (uint32_t)__builtin_amdgcn_readlane((int)g1, l) - u0;
+            one = __all(!some || g0 == u0);
+          }
           wave_lds_sync();
           fresh = false;
         }
@@ -1885,8 +1980,11 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, PairKey key) {
             uint32_t p = first;
 #pragma unroll
             for (uint32_t u = 0; u < U; ++u) {
-              uint32_t w = s_row[wave][row_of(s_heads[wave], u, lane, p)];
-              if (!whole && x0 + u * 64u + (uint32_t)lane - lo >= hi - lo) w = v[u];
+              const uint32_t k = row_of(s_heads[wave], u, lane, p);
+              uint32_t w = s_row[wave][k];
+              const bool in = whole || x0 + u * 64u + (uint32_t)lane - lo < hi - lo;
+              if (!in) w = v[u];
+              if (ARENA && !one) leaves |= in && v[u] - s_lo[wave][k] >= s_n[wave][k];
               sum = add_pair(sum, w, v[u], key);
             }
             wave_lds_sync();
@@ -1895,7 +1993,15 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, PairKey key) {
 #pragma unroll
             for (uint32_t u = 0; u < U; ++u) {
               const bool in = whole || x0 + u * 64u + (uint32_t)lane - lo < hi - lo;
+              if (ARENA && !one) leaves |= in && v[u] - s_lo[wave][first] >= s_n[wave][first];
               sum = add_pair(sum, in ? row : v[u], v[u], key);
+            }
+          }
+          if (ARENA && one) {  // the usual case, without the lookups
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+              const bool in = whole || x0 + u * 64u + (uint32_t)lane - lo < hi - lo;
+              leaves |= in && v[u] - u0 >= un;
             }
           }
           lo = hi;
@@ -1912,7 +2018,7 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, PairKey key) {
       if (lo < send) break;  // rows that end before the entries do
       x0 = send;
     }
-    const bool bad = __any(top >= n) || x0 < x1;
+    const bool bad = __any(top >= n || leaves) || x0 < x1;
     if (bad && lane == 0) atomicOr(&st->asymmetric, 1u);
   }
 #pragma unroll
@@ -2016,6 +2122,310 @@ __global__ __launch_bounds__(PB) void bottom_up_kernel(Args a) {
   block_flush(s, a, cur, fout, tid, s_bc);
 }
 
+
+// ------------------------------------------------- bottom-up levels, by query
+// Several queries (a batch, a serving engine) are at different points of their
+// traversals, so each goes bottom-up or top-down by itself: the tally kernel
+// adds up the edges of each query's frontier, the bottom-up kernel runs the
+// queries that qualify and leaves what it finds as found bytes, the parent
+// kernel passes over their entries, and the level's harvest takes the found
+// bytes of both.
+//
+// Tally: the degrees of a sample of the frontier, 64 consecutive entries of
+// every `stride` * 64 so that about TALLY_SAMPLE are read.  The entries of a
+// wave are mostly one query's (the harvest appends in slot order): they are
+// summed by the wave, else in LDS.
+__global__ __launch_bounds__(PB) void tally_kernel(Args a, uint32_t step) {
+  __shared__ uint32_t s_fpre[NQF + 2];
+  __shared__ uint32_t s_edges[MAX_QUERIES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const State* st = a.st;
+  if (st->done || st->error || st->symmetric != 1) return;
+  const uint32_t L = st->base + step;
+  const LevelSet* prv = &st->set[(L + 2) % 3];
+  if (tid < 64) {
+    const uint32_t incl = wave_incl_scan(min(prv->fcnt[lane], (uint32_t)a.fcap), lane);
+    s_fpre[lane + 1] = incl;
+    if (lane == 0) s_fpre[0] = 0;
+    if (lane == 63) s_fpre[NQF + 1] = incl + prv->fcnt[NQF];
+  }
+  for (int i = tid; i < a.nq; i += PB) s_edges[i] = 0;
+  __syncthreads();
+  const uint32_t F = s_fpre[NQF + 1];
+  if (F < TALLY_MIN || F > (uint32_t)a.slots) return;
+  const int32_t* fin = (L & 1) ? a.front1 : a.front0;
+  const uint32_t stride = ceil_div(F, TALLY_SAMPLE);
+  for (uint32_t c = blockIdx.x * NW + wave; c * stride * 64u < F; c += gridDim.x * NW) {
+    const uint32_t i = c * stride * 64u + (uint32_t)lane;
+    uint32_t q = NONE, deg = 0;
+    if (i < F) {
+      const uint32_t slot = (uint32_t)frontier_at(a, fin, s_fpre, i);
+      q = (uint32_t)a.qmap[slot >> 5];
+      const int32_t v = a.q[q].vbase + ((int32_t)slot - a.q[q].slot0);
+      deg = (uint32_t)(a.rp[v + 1] - a.rp[v]) * stride;
+    }
+    const uint32_t q0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)q);
+    if (__all(q == q0 || q == NONE)) {
+      const uint32_t sum = __shfl(wave_incl_scan(deg, lane), 63, 64);
+      if (lane == 0) atomicAdd(&s_edges[q0], sum);
+    } else if (q != NONE) {
+      atomicAdd(&s_edges[q], deg);
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < a.nq; i += PB)
+    if (s_edges[i]) {
+      atomicAdd(&a.tally[(L & 1) * a.nq + i], s_edges[i]);
+      atomicAdd(&a.tally[2 * a.nq + i], s_edges[i]);
+    }
+}
+
+// The bottom-up level of the queries that qualify runs queries of one graph
+// together, up to BU_GROUP of them: per vertex a word with a bit per query of
+// the group, set if that query has visited it, so that one load of a
+// neighbour's word answers for all of them and a row is read once.  With one
+// bitmap per query, 512 queries over 64 graphs made 100 M random probes on the
+// growing level, 490 us at the chip's rate for random loads; now that level
+// takes 41 us for the words and 253 for the rows, 1.5 ms top-down (2.6 for the
+// widest, now 146), and the batch 5.93 -> 2.00 ms.
+//
+// The first of its two kernels lists the qualifying queries by graph, then
+// their groups with their runs of 64 vertices (scanned; every workgroup for
+// itself, the first one for the second kernel), and writes the words.  Lists
+// and words lie where the parent kernel will put the level's records.
+struct UpLists {
+  const uint16_t* query;  // qualifying queries
+  const uint16_t* first;  // first of them of each group, and their number
+  const uint32_t* run;    // first run of each group, and the number of runs
+  const uint32_t* count;  // groups
+};
+
+__device__ __forceinline__ UpLists up_lists(const Args& a) {
+  uint32_t* t = (uint32_t*)a.rec_q;  // (a query has at least 32 slots)
+  return UpLists{(const uint16_t*)(t + 1 + a.nq + 1), (const uint16_t*)(t + 1 + a.nq + 1) + a.nq + 1,
+                 t + 1, t};
+}
+
+// Words of a group, by vertex of its graph; slot0: of its first query.
+__device__ __forceinline__ uint16_t* up_words(const Args& a, uint32_t slot0) {
+  return (uint16_t*)(a.rec + slot0);
+}
+
+__global__ __launch_bounds__(QB) void bottom_up_words_kernel(Args a, uint32_t step) {
+  __shared__ uint16_t s_list[MAX_QUERIES + 1], s_first[MAX_QUERIES + 1];
+  __shared__ uint32_t s_pre[MAX_QUERIES + 1];
+  constexpr int NW = QB / 64;
+  __shared__ uint32_t s_sum[3][NW];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const State* st = a.st;
+  if (st->done || st->error || st->symmetric != 1) return;
+  const uint32_t L = st->base + step;
+  uint32_t count = 0;
+  for (int q0 = 0; q0 < a.nq; q0 += QB) {
+    const int q = q0 + tid;
+    const bool on = q < a.nq && query_goes_bottom_up(a, (uint32_t)q, L);
+    const unsigned long long m = __ballot(on);
+    if (lane == 0) s_sum[0][wave] = (uint32_t)__popcll(m);
+    __syncthreads();
+    uint32_t c = count + lane_rank(m);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (w < wave) c += s_sum[0][w];
+      count += s_sum[0][w];
+    }
+    if (on) {
+      s_list[c] = (uint16_t)q;
+      s_pre[c] = (uint32_t)a.q[q].vbase;
+    }
+    __syncthreads();
+  }
+  const UpLists up = up_lists(a);
+  if (count == 0) {
+    if (blockIdx.x == 0 && tid == 0) *(uint32_t*)up.count = 0;
+    return;
+  }
+  if (count <= BU_SORT) {  // a batch has a graph's queries together, an engine does not
+    uint32_t rank = 0, q = 0;
+    if ((uint32_t)tid < count) {
+      const uint32_t vb = s_pre[tid];
+      q = s_list[tid];
+      for (uint32_t k = 0; k < count; ++k) rank += s_pre[k] < vb || (s_pre[k] == vb && k < (uint32_t)tid);
+    }
+    __syncthreads();
+    if ((uint32_t)tid < count) s_list[rank] = (uint16_t)q;
+    __syncthreads();
+  }
+  uint32_t groups = 0, runs = 0, since = 0;  // since: where the graph's queries begin in the list
+  for (uint32_t k0 = 0; k0 < count; k0 += QB) {
+    const uint32_t k = k0 + (uint32_t)tid;
+    int32_t vb = 0, n = 0;
+    bool other = false;
+    if (k < count) {
+      vb = a.q[s_list[k]].vbase;
+      n = a.q[s_list[k]].n;
+      other = k == 0 || vb != a.q[s_list[k - 1]].vbase;
+    }
+    uint32_t from = other ? k : 0u;  // max-scanned
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(from, d, 64);
+      if (lane >= d) from = max(from, y);
+    }
+    if (lane == 63) s_sum[0][wave] = from;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (w < wave) from = max(from, s_sum[0][w]);
+    }
+    from = max(from, since);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) since = max(since, s_sum[0][w]);
+    const bool begins = k < count && (k - from) % BU_GROUP == 0;
+    const uint32_t r = begins ? ceil_div((uint32_t)n, 64u) : 0u;
+    const unsigned long long m = __ballot(begins);
+    const uint32_t incl = wave_incl_scan(r, lane);
+    if (lane == 63) {
+      s_sum[1][wave] = (uint32_t)__popcll(m);
+      s_sum[2][wave] = incl;
+    }
+    __syncthreads();
+    uint32_t g = groups + lane_rank(m), x = runs + incl - r;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (w < wave) {
+        g += s_sum[1][w];
+        x += s_sum[2][w];
+      }
+      groups += s_sum[1][w];
+      runs += s_sum[2][w];
+    }
+    if (begins) {
+      s_first[g] = (uint16_t)k;
+      s_pre[g] = x;
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    s_first[groups] = (uint16_t)count;
+    s_pre[groups] = runs;
+  }
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    for (uint32_t k = tid; k < count; k += QB) ((uint16_t*)up.query)[k] = s_list[k];
+    for (uint32_t g = tid; g <= groups; g += QB) {
+      ((uint16_t*)up.first)[g] = s_first[g];
+      ((uint32_t*)up.run)[g] = s_pre[g];
+    }
+    if (tid == 0) *(uint32_t*)up.count = groups;
+  }
+  const uint32_t nw = gridDim.x * NW, gw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * NW + wave));
+  uint32_t t = (uint32_t)((uint64_t)gw * runs / nw);
+  const uint32_t t1 = (uint32_t)((uint64_t)(gw + 1) * runs / nw);
+  if (t >= t1) return;
+  uint32_t g = wave_upper_search(groups, t, lane, [&](uint32_t p) { return s_pre[p]; });
+  for (; t < t1; ++g) {
+    const uint32_t k0 = s_first[g], nk = s_first[g + 1] - k0, tg = s_pre[g], te = min(t1, s_pre[g + 1]);
+    const uint32_t slot0 = (uint32_t)lane < nk ? (uint32_t)a.q[s_list[k0 + lane]].slot0 : 0u;
+    const uint32_t n = (uint32_t)a.q[s_list[k0]].n;
+    uint16_t* words = up_words(a, (uint32_t)__builtin_amdgcn_readlane((int)slot0, 0));
+    for (; t < te; ++t) {
+      const uint32_t v = (t - tg) * 64u + (uint32_t)lane;
+      uint32_t w = 0;
+      for (uint32_t j = 0; j < nk; ++j) {
+        const uint32_t* seen = a.visit + ((uint32_t)__builtin_amdgcn_readlane((int)slot0, j) >> 5);
+        if (v < n) w |= (seen[v >> 5] >> (v & 31) & 1u) << j;
+      }
+      if (v < n) words[v] = (uint16_t)w;
+    }
+  }
+}
+
+// The second: as bottom_up_kernel, but the visited bitmaps stay as they are and
+// what is found goes to the found bytes.
+__global__ __launch_bounds__(PB) void bottom_up_queries_kernel(Args a, uint32_t step) {
+  constexpr int U = 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const State* st = a.st;
+  if (st->done || st->error || st->symmetric != 1) return;
+  const UpLists up = up_lists(a);
+  const uint32_t groups = *up.count;
+  if (groups == 0) return;
+  const uint32_t runs = up.run[groups];
+  const uint32_t nw = gridDim.x * NW, gw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * NW + wave));
+  uint32_t t = (uint32_t)((uint64_t)gw * runs / nw);
+  const uint32_t t1 = (uint32_t)((uint64_t)(gw + 1) * runs / nw);
+  if (t >= t1) return;
+  uint32_t g = wave_upper_search(groups, t, lane, [&](uint32_t p) { return up.run[p]; });
+  for (; t < t1; ++g) {
+    g = (uint32_t)__builtin_amdgcn_readfirstlane((int)g);
+    const uint32_t k0 = up.first[g], nk = up.first[g + 1] - k0, tg = up.run[g], te = min(t1, up.run[g + 1]);
+    const Query Q = a.q[up.query[k0]];
+    const uint32_t n = (uint32_t)Q.n;
+    // first slot of the group's queries, a lane each
+    const uint32_t slot0 = (uint32_t)lane < nk ? (uint32_t)a.q[up.query[k0 + lane]].slot0 : 0u;
+    const uint16_t* words = up_words(a, (uint32_t)Q.slot0);
+    const uint32_t all = (1u << nk) - 1u;
+    for (; t < te; ++t) {
+      const uint32_t v = (t - tg) * 64u + (uint32_t)lane;  // vertex of the graph
+      uint32_t need = v < n ? all & ~(uint32_t)words[v] : 0u, found = 0;  // a bit per query
+      uint32_t x = 0, e = 0;
+      if (need) {
+        x = (uint32_t)a.rp[Q.vbase + v];
+        e = (uint32_t)a.rp[Q.vbase + v + 1];
+      }
+      // a vertex without edges counts as visited from now on (no row names it)
+      const unsigned long long alone = __ballot(need && x == e);
+      if (alone) {
+        const uint32_t bits = (uint32_t)(alone >> (lane & 32));
+        for (uint32_t j = 0; j < nk; ++j) {
+          uint32_t* seen = a.visit + ((uint32_t)__builtin_amdgcn_readlane((int)slot0, j) >> 5);
+          if ((lane & 31) == 0 && bits) seen[v >> 5] |= bits;
+        }
+      }
+      if (x >= e) need = 0;
+      for (uint32_t it = 0; it < BU_LANE / U && __any(need != 0); ++it) {
+        uint32_t w[U], hit = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          w[u] = need ? min((uint32_t)(a.col[min(x + u, e - 1)] - Q.vbase), n - 1) : 0u;
+#pragma unroll
+        for (int u = 0; u < U; ++u) hit |= need ? (uint32_t)words[w[u]] : 0u;
+        found |= hit & need;
+        need &= ~found;
+        x += U;
+        if (x >= e) need = 0;
+      }
+      for (unsigned long long rest = __ballot(need != 0); rest; rest &= rest - 1) {
+        const int l = __builtin_ctzll(rest);
+        const uint32_t y1 = (uint32_t)__builtin_amdgcn_readlane((int)e, l);
+        const uint32_t asked = (uint32_t)__builtin_amdgcn_readlane((int)need, l);
+        uint32_t want = asked;
+        for (uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)x, l); y < y1 && want; y += 64 * U) {
+          uint32_t w[U], hit = 0;
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            w[u] = min((uint32_t)(a.col[min(y + (uint32_t)(u * 64 + lane), y1 - 1)] - Q.vbase), n - 1);
+#pragma unroll
+          for (int u = 0; u < U; ++u) hit |= (uint32_t)words[w[u]];
+#pragma unroll
+          for (int d = 1; d < 64; d <<= 1) hit |= (uint32_t)__shfl_xor((int)hit, d, 64);
+          want &= ~(uint32_t)__builtin_amdgcn_readfirstlane((int)hit);
+        }
+        if (lane == l) found |= asked & ~want;
+      }
+      if (__any(found != 0))
+        for (uint32_t j = 0; j < nk; ++j)
+          if (found >> j & 1u) a.found[(uint32_t)__builtin_amdgcn_readlane((int)slot0, j) + v] = 1;
+    }
+  }
+}
+
+// After a symmetry check that the host asked for (several queries).
+__global__ void settle_symmetry_kernel(State* st) {
+  if (threadIdx.x || blockIdx.x) return;
+  st->symmetric = found_symmetric(st) ? 1u : 2u;
+  st->plan = 0;
+}
 
 // ------------------------------------------------------------ init / admit / advance
 // Traversal-set start: level sets and counters cleared.  Queries are
@@ -2164,6 +2574,11 @@ __global__ void admit_sources_kernel(Args a, const int32_t* list, int32_t count)
     Query* Q = &a.q[list[k]];
     Q->lstart = (int32_t)L;
     Q->last = (int32_t)L;
+    if (a.bottom_up == BU_QUERIES) {
+      const int32_t q = list[k];
+      for (int i = 0; i < 3; ++i) a.tally[i * a.nq + q] = 0;
+      a.tally[3 * a.nq + q] = (uint32_t)(a.rp[Q->vbase + Q->n] - a.rp[Q->vbase]);
+    }
     const uint32_t pos = atomicAdd(&ls->fcnt[NQF], 1u);
     if (pos < (uint32_t)a.slots) fin[(size_t)NQF * a.fcap + pos] = Q->slot0 + Q->src;
     else set_error(st, ERR_CAPACITY);
@@ -2247,9 +2662,19 @@ const void* narrow_kernel_ptr(int problem, int32_t slots) {
                                    : (const void*)narrow_kernel<PROB_BFS, false>;
 }
 
-const void* symmetry_kernel_ptr() { return (const void*)symmetry_kernel; }
+const void* symmetry_kernel_ptr(bool arena) {
+  return arena ? (const void*)symmetry_kernel<true> : (const void*)symmetry_kernel<false>;
+}
 
 const void* bottom_up_kernel_ptr() { return (const void*)bottom_up_kernel; }
+
+const void* tally_kernel_ptr() { return (const void*)tally_kernel; }
+
+const void* bottom_up_words_kernel_ptr() { return (const void*)bottom_up_words_kernel; }
+
+const void* bottom_up_queries_kernel_ptr() { return (const void*)bottom_up_queries_kernel; }
+
+const void* settle_symmetry_kernel_ptr() { return (const void*)settle_symmetry_kernel; }
 
 const void* start_kernel_ptr(int problem) {
   return problem == PROB_BFS ? (const void*)start_kernel<PROB_BFS>
