@@ -462,26 +462,16 @@ dpo_status launch_admit(SetRun& sr, int32_t* hlist, int32_t count, int32_t reset
 }
 
 // Start the queries hlist[0 .. count) whose records are already in hq (host,
-// pinned; hlist has room for 2 * count + 1 entries): upload those records,
-// the index list and the workgroup prefix, then the admit kernels.
-dpo_status admit(Runtime& r, SetRun& sr, const Query* hq, int32_t* hlist, int32_t count,
-                 int32_t reset) {
-  (void)r;
+// pinned; hlist has room for 2 * count + 1 entries): upload the table of nq
+// records, the index list and the workgroup prefix, then the admit kernels.  (The
+// records of running queries are the device's own, as of the end of its last
+// replay: one upload of all costs less than one for each new record.)
+dpo_status admit(SetRun& sr, const Query* hq, int32_t nq, int32_t* hlist, int32_t count) {
   if (count <= 0) return DPO_OK;
-  for (int32_t k = 0; k < count; ++k)
-    if (hipMemcpyAsync(sr.a.q + hlist[k], hq + hlist[k], sizeof(Query), hipMemcpyHostToDevice,
-                       sr.stream) != hipSuccess)
-      return DPO_ERR_HIP;
-  return launch_admit(sr, hlist, count, reset, admit_prefix(hq, hlist, count));
-}
-
-// Batch start: the whole table in one upload, then the admit kernels.
-dpo_status admit_all(Runtime& r, SetRun& sr, const Query* hq, int32_t* hlist, int32_t nq) {
-  (void)r;
   if (hipMemcpyAsync(sr.a.q, hq, (size_t)nq * sizeof(Query), hipMemcpyHostToDevice, sr.stream) !=
       hipSuccess)
     return DPO_ERR_HIP;
-  return launch_admit(sr, hlist, nq, 0, admit_prefix(hq, hlist, nq));
+  return launch_admit(sr, hlist, count, 0, admit_prefix(hq, hlist, count));
 }
 
 dpo_status start_set(Runtime& r, SetRun& sr) {
@@ -766,7 +756,7 @@ dpo_status traverse_batch(int problem, const dpo_arena* ar, const dpo_query* qs,
   int32_t* hl = r.host_list;
   for (int32_t i = 0; i < nq; ++i) hl[i] = i;
   if ((s = start_set(r, sr)) != DPO_OK) return s;
-  if ((s = admit_all(r, sr, hq, hl, nq)) != DPO_OK) return s;
+  if ((s = admit(sr, hq, nq, hl, nq)) != DPO_OK) return s;
   if (sr.a.bottom_up && (s = check_symmetry(r, sr, ar->graph_vbase, ar->ngraphs)) != DPO_OK)
     return s;
   if ((s = run_to_completion(r, sr, slots)) != DPO_OK) return s;
@@ -894,6 +884,9 @@ struct dpo_engine {
   dpo::Query* hq = nullptr;   // pinned mirror of the device query table
   int32_t* hlist = nullptr;   // pinned
   uint32_t* hflags = nullptr; // pinned
+  uint4* hretire = nullptr;   // pinned: queries being retired, then their workgroup prefix
+  std::vector<int32_t> hretire_pre;
+  hipEvent_t retired = nullptr;
   int64_t max_n = 0;
   int64_t served = 0;  // vertices of the queries admitted since the engine was last idle
   bool checked = false;  // the arena's symmetry, since then
@@ -932,7 +925,26 @@ void slots_free(dpo_engine* e, int64_t start, int64_t len) {
   }
 }
 
-dpo_status engine_step(dpo_engine* e) {
+// Copies the results of the queries in e->hretire to their callers; the event
+// marks the end of it.  The list goes where the level steps put their records
+// (a query has at least 32 slots, of 16 bytes each there).
+dpo_status launch_retire(dpo_engine* e, int32_t count, int32_t groups) {
+  SetRun& sr = e->sr;
+  uint4* list = (uint4*)sr.a.rec;
+  int32_t* pre = (int32_t*)(list + count);
+  std::memcpy(e->hretire + count, e->hretire_pre.data(), (size_t)count * 4);
+  if (hipMemcpyAsync(list, e->hretire, (size_t)count * 20, hipMemcpyHostToDevice, sr.stream) != hipSuccess)
+    return DPO_ERR_HIP;
+  const char* slots = e->out_arena;
+  void* p[] = {&slots, &list, &pre, &count};
+  if (hipLaunchKernel(retire_kernel_ptr(), dim3((unsigned)groups), dim3(PB), p, 0, sr.stream) != hipSuccess)
+    return DPO_ERR_HIP;
+  return hip_ok(hipEventRecord(e->retired, sr.stream));
+}
+
+// Retires, admits and launches; retired: queries whose results launch_retire
+// copies.
+dpo_status engine_enqueue(dpo_engine* e, int32_t& retired) {
   Runtime& r = rt();
   SetRun& sr = e->sr;
   dpo_status s = DPO_OK;
@@ -943,22 +955,21 @@ dpo_status engine_step(dpo_engine* e) {
     // queries without frontier entries at the last level run have finished
     const int32_t last_level = (int32_t)e->hflags[0] - 1;
     const bool all_done = e->hflags[1] != 0;
-    int32_t retired = 0;
+    int64_t groups = 0;
     for (int32_t q = 0; q < e->max_queries; ++q) {
       Running& ru = e->run[q];
       if (!ru.used || !(all_done || e->hq[q].last < last_level)) continue;
-      const size_t bytes = (size_t)ru.n * 4;
-      if (hipMemcpyAsync(ru.out, e->out_arena + ru.slot0 * 4, bytes, hipMemcpyDeviceToDevice,
-                         sr.stream) != hipSuccess)
-        return DPO_ERR_HIP;
+      const uint64_t out = (uint64_t)ru.out;
+      e->hretire[retired] = uint4{(uint32_t)out, (uint32_t)(out >> 32), (uint32_t)ru.slot0, (uint32_t)ru.n};
+      e->hretire_pre[retired++] = (int32_t)groups;
+      groups += cdiv(ru.n, ADMIT_CHUNK);
       slots_free(e, ru.slot0, ru.footprint);
       e->completed.push_back(ru.ticket);
       ru = Running{};
       e->free_q.push_back(q);
       --e->running;
-      ++retired;
     }
-    if (retired && hipStreamSynchronize(sr.stream) != hipSuccess) return DPO_ERR_HIP;
+    if (retired && (s = launch_retire(e, retired, (int32_t)groups)) != DPO_OK) return s;
   }
   // admit in arrival order while a table entry and the footprint fit
   int32_t count = 0;
@@ -991,7 +1002,7 @@ dpo_status engine_step(dpo_engine* e) {
       e->served = 0;
       e->checked = false;
     }
-    if ((s = admit(r, sr, e->hq, e->hlist, count, 0)) != DPO_OK) return s;
+    if ((s = admit(sr, e->hq, e->max_queries, e->hlist, count)) != DPO_OK) return s;
     for (int32_t k = 0; k < count; ++k) e->served += e->hq[e->hlist[k]].n;
     if (sr.a.bottom_up && !e->checked && e->served >= sr.n) {
       // enough work for the check to pay (see prepare_set); the answer holds
@@ -1009,6 +1020,15 @@ dpo_status engine_step(dpo_engine* e) {
     e->inflight = true;
   }
   return DPO_OK;
+}
+
+dpo_status engine_step(dpo_engine* e) {
+  int32_t retired = 0;
+  const dpo_status s = engine_enqueue(e, retired);
+  // the retired queries' results are with their callers before dpo_engine_poll
+  // can report them; admission and the next replay were enqueued behind them
+  if (retired && hipEventSynchronize(e->retired) != hipSuccess) return DPO_ERR_HIP;
+  return s;
 }
 
 }  // namespace
@@ -1063,12 +1083,15 @@ dpo_status dpo_engine_create(const dpo_arena* arena, int32_t kind, const dpo_opt
                   ws_bytes, stream, false, &e->sr);
   void* p = nullptr;
   if (s == DPO_OK &&
-      hipHostMalloc(&p, 64 + (size_t)max_queries * (sizeof(Query) + 8) + 4, hipHostMallocDefault) !=
+      hipHostMalloc(&p, 64 + (size_t)max_queries * (20 + sizeof(Query) + 8) + 4, hipHostMallocDefault) !=
           hipSuccess)
     s = DPO_ERR_HIP;
+  if (s == DPO_OK) s = hip_ok(hipEventCreateWithFlags(&e->retired, hipEventDisableTiming));
   if (s == DPO_OK) {
     e->hflags = (uint32_t*)p;
-    e->hq = (Query*)((char*)p + 64);
+    e->hretire = (uint4*)((char*)p + 64);
+    e->hretire_pre.resize(max_queries);
+    e->hq = (Query*)((char*)e->hretire + (size_t)max_queries * 20);
     e->hlist = (int32_t*)(e->hq + max_queries);
     std::memset(e->hq, 0, (size_t)max_queries * sizeof(Query));
     s = get_exec(r, e->sr.parent, e->sr.child, e->sr.third, e->sr.fourth, e->sr.pgrid,
@@ -1090,6 +1113,7 @@ dpo_status dpo_engine_create(const dpo_arena* arena, int32_t kind, const dpo_opt
   if (s == DPO_OK && hipStreamSynchronize(e->sr.stream) != hipSuccess) s = DPO_ERR_HIP;
   if (s != DPO_OK) {
     if (e->exec) (void)hipGraphExecDestroy(e->exec);
+    if (e->retired) (void)hipEventDestroy(e->retired);
     if (p) (void)hipHostFree(p);
     delete e;
     return s;
@@ -1137,6 +1161,7 @@ void dpo_engine_destroy(dpo_engine* e) {
   if (!e) return;
   if (e->inflight) (void)hipStreamSynchronize(e->sr.stream);
   if (e->exec) (void)hipGraphExecDestroy(e->exec);
+  if (e->retired) (void)hipEventDestroy(e->retired);
   if (e->hflags) (void)hipHostFree(e->hflags);
   delete e;
 }

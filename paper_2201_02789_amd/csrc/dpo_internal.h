@@ -216,6 +216,7 @@ const void* settle_symmetry_kernel_ptr();
 const void* start_kernel_ptr(int problem);
 const void* admit_kernel_ptr(int problem);
 const void* admit_sources_kernel_ptr();
+const void* retire_kernel_ptr();
 const void* clear_found_kernel_ptr();
 const void* advance_kernel_ptr();
 

@@ -106,3 +106,28 @@ def test_an_entry_that_leaves_its_graph_is_reported():
     with pytest.raises(dpo.DpoError) as e:
         dpo.dpo_bfs_batch(da, qs, [opts], out, ws)
     assert e.value.status == dpo.DPO_ERR_ARG
+
+
+def test_engine_results_of_every_size_reach_unaligned_outputs():
+    """Queries that finish together, of sizes around the copy's chunk (4,096
+    slots), into outputs 4 bytes past a 16-byte boundary; nothing is written
+    past their ends."""
+    sizes = [1, 2, 63, 4095, 4096, 4097, 8193]
+    gs = [gg.path_graph(2) if n == 2 else gg.star_graph(n) if n > 2 else gg.from_edges(1, []) for n in sizes]
+    ar, vbase = gg.pack_arena(gs)
+    da = dpo.DeviceArena(ar, vbase)
+    eng = dpo.Engine(da, "bfs", [dpo.Options()], max_queries=16, max_slots=1 << 16)
+    outs = []
+    for k, n in enumerate(sizes):
+        buf = torch.full((n + 9,), -5, dtype=torch.int32, device="cuda")
+        outs.append(buf)
+        eng.submit(k, n - 1, buf[1:n + 1])
+    for _ in range(100):
+        if eng.step() == (0, 0):
+            break
+    assert len(eng.poll()) == len(sizes)
+    for k, n in enumerate(sizes):
+        host = outs[k].cpu().numpy()
+        assert np.array_equal(host[1:n + 1], oracle.bfs(gs[k], n - 1)[0]), n
+        assert host[0] == -5 and (host[n + 1:] == -5).all(), n
+    eng.close()
