@@ -86,6 +86,19 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Keeps the compiler from moving the first use of a loaded value up into the
+// branch that loads it.  Where a batch's loads (or atomics) are predicated, it
+// does that whenever a use is needed on that branch only, and each of them then
+// waits for its own round trip before the next is issued.
+__device__ __forceinline__ void pin(uint32_t& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void pin(int32_t& x) { asm volatile("" : "+v"(x)); }
+
+template <int U, typename T>
+__device__ __forceinline__ void pin(T (&x)[U]) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) pin(x[u]);
+}
+
 __device__ __forceinline__ void set_error(State* st, uint32_t code) {
   atomicCAS(&st->error, 0u, code);
 }
@@ -270,6 +283,7 @@ __device__ __forceinline__ void visit_batch(const Args& a, const Vis& vis, const
     uint32_t word[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) word[u] = sl[u] >= 0 ? pb[(uint32_t)sl[u] >> 5] : ~0u;
+    pin(word);
     // Per-XCD copies (wide level): a candidate records itself in its XCD's
     // copy and in the found bytes, both plain stores, and nothing else: no
     // atomic, no level, no append.  The harvest kernel after the level takes
@@ -306,6 +320,7 @@ __device__ __forceinline__ void visit_batch(const Args& a, const Vis& vis, const
       for (int u = 0; u < U; ++u)
         if (sl[u] >= 0 && !(word[u] & (1u << (sl[u] & 31))))
           word[u] = coherent_load(&cb[(uint32_t)sl[u] >> 5]);
+      pin(word);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -313,6 +328,7 @@ __device__ __forceinline__ void visit_batch(const Args& a, const Vis& vis, const
       if (sl[u] >= 0 && !(word[u] & bit)) word[u] = atomicOr(&cb[(uint32_t)sl[u] >> 5], bit);
       else word[u] = ~0u;
     }
+    pin(word);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (!(word[u] & (1u << (sl[u] & 31)))) {
@@ -332,6 +348,7 @@ __device__ __forceinline__ void visit_batch(const Args& a, const Vis& vis, const
       nd[u] = sum < c[u].du ? 0xFFFFFFFFu : sum;
       cur[u] = sl[u] >= 0 ? dp[sl[u]] : 0u;
     }
+    pin(cur);
     uint32_t ncand = 0;
     if (vis.split) {
 #pragma unroll
@@ -342,12 +359,14 @@ __device__ __forceinline__ void visit_batch(const Args& a, const Vis& vis, const
 #pragma unroll
       for (int u = 0; u < U; ++u)
         if (sl[u] >= 0 && nd[u] < cur[u]) cur[u] = coherent_load(&dl[sl[u]]);
+      pin(cur);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (sl[u] >= 0 && nd[u] < cur[u]) cur[u] = atomicMin(&dl[sl[u]], nd[u]);
       else cur[u] = 0u;
     }
+    pin(cur);
     // Found bytes (Args::hint): an improved vertex is recorded with a plain
     // byte store and queued once by the harvest kernel after the level, so an
     // improving lane waits for no atomic after its atomicMin.
@@ -361,11 +380,13 @@ __device__ __forceinline__ void visit_batch(const Args& a, const Vis& vis, const
     uint32_t stamp[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) stamp[u] = (pre && nd[u] < cur[u]) ? coherent_load(&a.visit[sl[u]]) : 0u;
+    pin(stamp);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (nd[u] < cur[u] && stamp[u] != it) stamp[u] = atomicExch(&a.visit[sl[u]], it);
       else stamp[u] = it;
     }
+    pin(stamp);
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (stamp[u] != it) out[u] = sl[u];
@@ -690,8 +711,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
   // first, four at a time, because a level has most entries when most queries go
   // bottom-up (512 queries: 13 M entries in 40 rounds of dependent loads and
   // barriers otherwise).
-  auto goes_up = [&](uint32_t i) {
-    const uint32_t q = (uint32_t)a.qmap[(uint32_t)frontier_at(a, fin, s_fpre, i) >> 5];
+  auto goes_up = [&](uint32_t q) {
     const bool up = s_up[q >> 5] >> (q & 31) & 1u;
     if (up && !(s_live[q >> 5] >> (q & 31) & 1u)) atomicOr(&s_live[q >> 5], 1u << (q & 31));
     return up;
@@ -701,12 +721,20 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
     __syncthreads();
     const uint32_t rounds = blockIdx.x < nvb ? (nvb - 1 - blockIdx.x) / gridDim.x + 1 : 0;
     for (uint32_t r = 0; r < rounds; r += 4) {
-      uint32_t bits = 0;
+      uint32_t bits = 0, q[4];
+      int32_t slot[4];
 #pragma unroll
       for (uint32_t c = 0; c < 4; ++c) {
         const uint64_t i = ((uint64_t)blockIdx.x + (uint64_t)(r + c) * gridDim.x) * PB + tid;
-        if (r + c < rounds && i < F && !goes_up((uint32_t)i)) bits |= 1u << c;
+        slot[c] = r + c < rounds && i < F ? frontier_at(a, fin, s_fpre, (uint32_t)i) : -1;
       }
+      pin(slot);
+#pragma unroll
+      for (uint32_t c = 0; c < 4; ++c) q[c] = slot[c] >= 0 ? (uint32_t)a.qmap[(uint32_t)slot[c] >> 5] : 0u;
+      pin(q);
+#pragma unroll
+      for (uint32_t c = 0; c < 4; ++c)
+        if (slot[c] >= 0 && !goes_up(q[c])) bits |= 1u << c;
 #pragma unroll
       for (uint32_t c = 0; c < 4; ++c)
         if (__any(bits >> c & 1u) && lane == 0)
@@ -732,7 +760,8 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
         continue;
       }
     }
-    const bool mine = i < F && !(by_query && goes_up(i));
+    const bool mine =
+        i < F && !(by_query && goes_up((uint32_t)a.qmap[(uint32_t)frontier_at(a, fin, s_fpre, i) >> 5]));
     if (mine) {
       const Parent p = load_parent<P>(a, fin, s_fpre, i, L);
       start = p.start;
@@ -1032,6 +1061,8 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
             v[u] = x < total ? a.col[ei] : -1;
             w[u] = (P == PROB_SSSP && x < total) ? a.w[ei] : 0u;
           }
+          pin(v);
+          if (P == PROB_SSSP) pin(w);
           visit_batch<P, U>(a, vis, v, w, c, L, out);
 #pragma unroll
           for (int u = 0; u < U; ++u) stage_push(s, out[u] >= 0, out[u], a, cur, fout, lane);
@@ -1080,6 +1111,8 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
           w[r] = (P == PROB_SSSP && e + r < end) ? a.w[e + r] : 0u;
           c[r] = ctx;
         }
+        pin(v);
+        if (P == PROB_SSSP) pin(w);
         visit_batch<P, U>(a, vis, v, w, c, L, out);
 #pragma unroll
         for (int r = 0; r < U; ++r) stage_push(s, out[r] >= 0, out[r], a, cur, fout, lane);
@@ -1340,6 +1373,8 @@ __global__ __launch_bounds__(PB) void child_kernel(Args a, uint32_t step) {
               }
             }
           }
+          pin(v);
+          if (P == PROB_SSSP) pin(w);
           if (a.count_stats) {  // edges run (lane 0 keeps the wave's count)
   #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -2090,13 +2125,13 @@ __global__ __launch_bounds__(PB) void bottom_up_kernel(Args a) {
       uint32_t w[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) w[u] = need ? (uint32_t)a.col[min(x + u, e - 1)] : 0u;
+      pin(w);
+      uint32_t words[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t bit = w[u] & 31;
-        w[u] = need ? seen[w[u] >> 5] >> bit & 1u : 0u;
-      }
+      for (int u = 0; u < U; ++u) words[u] = need ? seen[w[u] >> 5] : 0u;
+      pin(words);
 #pragma unroll
-      for (int u = 0; u < U; ++u) found |= w[u] != 0;
+      for (int u = 0; u < U; ++u) found |= (words[u] >> (w[u] & 31) & 1u) != 0;
       x += U;
       need = need && !found && x < e;
     }
@@ -2387,9 +2422,13 @@ __global__ __launch_bounds__(PB) void bottom_up_queries_kernel(Args a, uint32_t 
         uint32_t w[U], hit = 0;
 #pragma unroll
         for (int u = 0; u < U; ++u)
-          w[u] = need ? min((uint32_t)(a.col[min(x + u, e - 1)] - Q.vbase), n - 1) : 0u;
+          w[u] = need ? (uint32_t)a.col[min(x + u, e - 1)] : (uint32_t)Q.vbase;
+        pin(w);
 #pragma unroll
-        for (int u = 0; u < U; ++u) hit |= need ? (uint32_t)words[w[u]] : 0u;
+        for (int u = 0; u < U; ++u) w[u] = need ? words[min(w[u] - (uint32_t)Q.vbase, n - 1)] : 0u;
+        pin(w);
+#pragma unroll
+        for (int u = 0; u < U; ++u) hit |= w[u];
         found |= hit & need;
         need &= ~found;
         x += U;
