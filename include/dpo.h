@@ -141,11 +141,12 @@ typedef enum {
   DPO_HINT_AUTO = 0,  /* on for single traversals (dpo_bfs, dpo_sssp and
                          their variants) and the serving engines when the graph
                          (the arena for an engine) has at least 8 directed
-                         entries per vertex, and then for a nested, aggregated
-                         BFS batch without counters whose queries have at least
-                         as many vertices as the arena; off for the other batch
-                         calls and sparser graphs, where many narrow levels
-                         would each pay the extra kernel launch                */
+                         entries per vertex, and then for SSSP batches and for
+                         nested, aggregated BFS batches without counters whose
+                         queries have at least as many vertices as the arena;
+                         off for other BFS batches and sparser graphs, where
+                         many narrow levels would each pay the extra kernel
+                         launch                                                */
   DPO_HINT_ON = 1,
   DPO_HINT_OFF = 2
 } dpo_claim_hint;

@@ -36,12 +36,16 @@ constexpr uint32_t NARROW_FRONT = 8192;       // most frontier entries
 // takes 30 to 50 us (16 us on a road-like graph) however few its edges are.
 constexpr uint32_t NARROW_EDGES = 1 << 17;
 constexpr uint32_t NARROW_FAR_EDGES = 1 << 12;
-// Bitmap words (BFS) and distances (SSSP) that go to LDS, beside half of
-// NARROW_FRONT frontier entries or more.  SSSP with global distances has no
-// narrow form: one compute unit makes its probes and atomics more slowly than
-// level steps do (a 77,357-vertex road-like graph 12.6 ms against 9.9).
+// Bitmap words that go to LDS, beside half of NARROW_FRONT frontier entries or
+// more.
 constexpr int32_t NARROW_BITS = NARROW_WORDS - 4 * (NARROW_FRONT / 2);
-constexpr int32_t NARROW_DIST = 16384;
+// Solo SSSP: vertices whose distances fit LDS beside 3,500 frontier entries or
+// more, and entries up to which one compute unit is faster than level steps
+// (us, solo / level steps: 16,384 vertices and 480,000 entries 560 / 500).
+constexpr int32_t SOLO_VERTICES = 16384;
+constexpr int32_t SOLO_EDGES = 1 << 18;
+constexpr uint32_t SOLO_WORDS = 34 * 1024;
+constexpr uint32_t SOLO_FRONT = 4096;
 constexpr uint32_t NONE = 0xFFFFFFFFu;        // no vertex
 constexpr uint32_t NARROW_LEVELS = 4096;      // most levels per launch (a few ms)
 // How a narrow launch ended: the traversal done or failed, more narrow levels,
@@ -164,6 +168,7 @@ struct Args {
   uint32_t* sercnt;                // [MAX_GRID] listed thresholded parents per workgroup
   unsigned long long* tm;          // phase-timing rows (timed kernels only)
   int32_t slots;                   // total output slots (sum of the queries' n)
+  int32_t n;                       // CSR arena vertices
   int32_t m;                       // CSR arena entries
   int32_t nq;
   int32_t CB;
@@ -206,7 +211,8 @@ const void* child_kernel_ptr(int problem, bool timed = false, bool nt = false);
 const void* serial_kernel_ptr(int problem, int gran, bool timed = false);
 const void* harvest_kernel_ptr(int problem, bool timed = false);
 const void* init_kernel_ptr(int problem);
-const void* narrow_kernel_ptr(int problem, int32_t slots);
+const void* narrow_kernel_ptr(int32_t slots);
+const void* solo_kernel_ptr();
 const void* symmetry_kernel_ptr(bool arena);
 const void* bottom_up_kernel_ptr();
 const void* tally_kernel_ptr();

@@ -1499,11 +1499,9 @@ __global__ __launch_bounds__(PB) void harvest_kernel(Args a, uint32_t step) {
 // ms; R-MAT of 4,096 vertices 238 -> 81 us.  What is left is latency: 0.7 us
 // per load and about 0.25 us per barrier.
 //
-// BFS keeps the visited bitmap in LDS too when it fits beside the frontier, so
-// that a claim is an LDS atomic; else it claims the global bitmap as a one-copy
-// level does.  SSSP runs here on graphs whose distances fit LDS: atomicMin
-// there, a bit per vertex so that the frontier takes an improved one once, and
-// no work for a parent that has been improved (and queued) again meanwhile.
+// The visited bitmap is in LDS too when it fits beside the frontier, so that a
+// claim is an LDS atomic; else the kernel claims the global bitmap as a one-copy
+// level does.  (SSSP on small graphs: solo_kernel.)
 //
 // The kernel leaves what a level step expects (frontier, level sets, group
 // counters, visited copies) when a level is wide: more frontier entries than
@@ -1551,59 +1549,36 @@ __device__ __forceinline__ uint32_t row_of(const uint8_t* heads, uint32_t u, int
   return k;
 }
 
-// One batch of a wave's edges (v: target, or NONE; nd: SSSP distance through
-// the edge): f[u] = v[u] joins the next frontier.  All probes are issued before
-// any atomic, all atomics before any use, so their round trips overlap.
-template <int P, bool LDS>
-__device__ __forceinline__ void narrow_visit(const Args& a, uint32_t* s_bits, uint32_t* s_dist,
-                                             uint32_t* vis, const uint32_t (&v)[NARROW_U],
-                                             const uint32_t (&nd)[NARROW_U], uint32_t L,
+// One batch of a wave's edges (v: target, or NONE): f[u] = v[u] joins the next
+// frontier.  All probes are issued before any atomic, all atomics before any
+// use, so their round trips overlap.
+template <bool LDS>
+__device__ __forceinline__ void narrow_visit(const Args& a, uint32_t* s_bits, uint32_t* vis,
+                                             const uint32_t (&v)[NARROW_U], uint32_t L,
                                              bool (&f)[NARROW_U]) {
   constexpr int U = NARROW_U;
   uint32_t x[U];
-  if (P == PROB_BFS) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      x[u] = ~0u;
-      if (v[u] != NONE) x[u] = LDS ? s_bits[v[u] >> 5] : vis[v[u] >> 5];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t bit = 1u << (v[u] & 31);
-      if (x[u] & bit) x[u] = ~0u;
-      else x[u] = LDS ? atomicOr(&s_bits[v[u] >> 5], bit) : atomicOr(&vis[v[u] >> 5], bit);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      f[u] = !(x[u] & (1u << (v[u] & 31)));
-      if (f[u]) a.level[v[u]] = (int32_t)L + 1;
-    }
-    return;
-  }
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    x[u] = 0;
-    if (v[u] != NONE) x[u] = s_dist[v[u]];
-  }
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    if (nd[u] < x[u]) x[u] = atomicMin(&s_dist[v[u]], nd[u]);
-    else x[u] = 0;
+    x[u] = ~0u;
+    if (v[u] != NONE) x[u] = LDS ? s_bits[v[u] >> 5] : vis[v[u] >> 5];
   }
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const uint32_t bit = 1u << (v[u] & 31);
-    if (nd[u] < x[u]) x[u] = atomicOr(&s_bits[v[u] >> 5], bit) & bit;
-    else x[u] = 1;
+    if (x[u] & bit) x[u] = ~0u;
+    else x[u] = LDS ? atomicOr(&s_bits[v[u] >> 5], bit) : atomicOr(&vis[v[u] >> 5], bit);
   }
 #pragma unroll
-  for (int u = 0; u < U; ++u) f[u] = x[u] == 0;
+  for (int u = 0; u < U; ++u) {
+    f[u] = !(x[u] & (1u << (v[u] & 31)));
+    if (f[u]) a.level[v[u]] = (int32_t)L + 1;
+  }
 }
 
 // after: what ran since the last launch (AFTER_*).
-// LDS: the visited bits (SSSP: the distances, and a bit for the vertices queued
-// at this level) are in LDS.
-template <int P, bool LDS>
+// LDS: the visited bits are in LDS.
+template <bool LDS>
 __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t after, uint32_t ticket,
                                                               uint32_t* verdict) {
   __shared__ NarrowLds sh;
@@ -1632,32 +1607,25 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
   }
   __syncthreads();
   uint32_t F = sh.fpre[NQF + 1];
-  // LDS: the bits, the distances, then frontier arrays of FC entries each
-  constexpr uint32_t ARR = P == PROB_BFS ? 4 : 5;
-  const uint32_t nbits = LDS ? (uint32_t)a.vwords : 0u, ndist = P == PROB_SSSP ? n : 0u;
-  const uint32_t FC = min((uint32_t)NARROW_FRONT, (NARROW_WORDS - nbits - ndist) / ARR);
+  // LDS: the bits, then frontier arrays of FC entries each
+  const uint32_t nbits = LDS ? (uint32_t)a.vwords : 0u;
+  const uint32_t FC = min((uint32_t)NARROW_FRONT, (NARROW_WORDS - nbits) / 4);
   constexpr uint32_t max_edges = LDS ? NARROW_EDGES : NARROW_FAR_EDGES;
   const uint32_t max_front = min(FC, max_edges);
   uint32_t* s_bits = sh.words;
-  uint32_t* s_dist = sh.words + nbits;
-  uint32_t* s_front = sh.words + nbits + ndist;  // two of FC: this level's, the next one's
+  uint32_t* s_front = sh.words + nbits;  // two of FC: this level's, the next one's
   uint32_t* s_start = s_front + 2 * FC;
   uint32_t* s_off = s_front + 3 * FC;
-  uint32_t* s_slot = s_front + 4 * FC;  // SSSP
   uint32_t cur = 0, nxt = FC;         // offsets into s_front
   const uint32_t c = st->vsel[L & 1];
-  // the copy this traversal's one-copy levels probe and update, and the other
-  uint32_t* vis = P == PROB_BFS ? a.visit + (size_t)c * (uint32_t)a.vwords
-                                : (c ? a.dist2 : a.dist);
-  uint32_t* fold = c ? a.dist : a.dist2;  // SSSP
+  // the copy this traversal's one-copy levels probe and update
+  uint32_t* vis = a.visit + (size_t)c * (uint32_t)a.vwords;
   const uint32_t L0 = L;
   bool wide = F > max_front;
-  const bool held = F != 0 && !wide;  // loaded into LDS
-  if (held) {
+  if (F != 0 && !wide) {
     const int32_t* fin = (L & 1) ? a.front1 : a.front0;
     for (uint32_t i = tid; i < F; i += NB) s_front[i] = (uint32_t)frontier_at(a, fin, sh.fpre, i);
-    for (uint32_t i = tid; i < nbits; i += NB) s_bits[i] = P == PROB_BFS ? vis[i] : 0u;
-    for (uint32_t i = tid; i < ndist; i += NB) s_dist[i] = vis[i];
+    for (uint32_t i = tid; i < nbits; i += NB) s_bits[i] = vis[i];
   }
   __syncthreads();
   while (F != 0 && !wide) {
@@ -1673,7 +1641,6 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
         const uint32_t v = s_front[cur + i];
         start[j] = (uint32_t)a.rp[v];
         deg[j] = (uint32_t)a.rp[v + 1];
-        if (P == PROB_SSSP) atomicAnd(&s_bits[v >> 5], ~(1u << (v & 31)));  // may be queued again
       }
     }
     if (tid == 0) sh.cnt = 0;
@@ -1687,24 +1654,19 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     int32_t* fout = (L & 1) ? a.front0 : a.front1;
     // runs a batch of edges, and appends what joins the next frontier: to LDS,
     // what does not fit to the overflow queue
-    auto edges = [&](const bool (&valid)[U], const uint32_t (&ei)[U], const uint32_t (&dv)[U]) {
-      uint32_t v[U], nd[U];
+    auto edges = [&](const bool (&valid)[U], const uint32_t (&ei)[U]) {
+      uint32_t v[U];
       bool f[U];
 #pragma unroll
-      for (uint32_t u = 0; u < U; ++u) {
-        v[u] = valid[u] ? (uint32_t)a.col[ei[u]] : NONE;
-        nd[u] = (P == PROB_SSSP && valid[u]) ? a.w[ei[u]] : 0u;
-      }
+      for (uint32_t u = 0; u < U; ++u) v[u] = valid[u] ? (uint32_t)a.col[ei[u]] : NONE;
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u) {
         if (v[u] >= n && valid[u]) {
           sh.bad = 1;
           v[u] = NONE;
         }
-        const uint32_t sum = dv[u] + nd[u];  // saturating, as in visit_batch
-        nd[u] = v[u] == NONE || sum < dv[u] ? 0xFFFFFFFFu : sum;
       }
-      narrow_visit<P, LDS>(a, s_bits, s_dist, vis, v, nd, L, f);
+      narrow_visit<LDS>(a, s_bits, vis, v, L, f);
       unsigned long long m[U];
       uint32_t total = 0, base = 0;
 #pragma unroll
@@ -1729,14 +1691,13 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
       // degrees and no search for an edge's row
       if (__any(deg[0] != 0)) {
         bool valid[U];
-        uint32_t ei[U], dv[U];
+        uint32_t ei[U];
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
           valid[u] = u < deg[0];
           ei[u] = start[0] + u;
-          dv[u] = P == PROB_SSSP && valid[u] ? s_dist[s_front[cur + tid]] : 0u;
         }
-        edges(valid, ei, dv);
+        edges(valid, ei);
       }
     } else {
       // the non-empty rows and their scanned degrees, in LDS
@@ -1766,7 +1727,6 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
         if (deg[j] == 0) continue;
         s_start[row] = start[j] - run;  // edge x of the level is start + x
         s_off[row] = run;
-        if (P == PROB_SSSP) s_slot[row] = s_front[cur + tid * per + j];
         run += deg[j];
         ++row;
       }
@@ -1785,21 +1745,15 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
         }
         wave_lds_sync();
         bool valid[U];
-        uint32_t ei[U], dv[U], p = p0;
+        uint32_t ei[U], p = p0;
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
           const uint32_t x = x0 + u * 64 + lane;
           const uint32_t k = row_of(heads, u, lane, p);
           valid[u] = x < E;
           ei[u] = s_start[k] + x;
-          dv[u] = 0;
-          if (P == PROB_SSSP && valid[u]) {
-            const uint32_t s = s_slot[k];
-            valid[u] = !(s_bits[s >> 5] >> (s & 31) & 1u);  // else queued again
-            dv[u] = s_dist[s];
-          }
         }
-        edges(valid, ei, dv);
+        edges(valid, ei);
         wave_lds_sync();  // heads is cleared by the next chunk
       }
     }
@@ -1814,12 +1768,6 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     if (L - L0 >= NARROW_LEVELS) break;
   }
   __syncthreads();
-  if (held)
-    for (uint32_t i = tid; i < ndist; i += NB) {
-      const uint32_t d = s_dist[i];
-      vis[i] = d;
-      fold[i] = d;
-    }
   if (F == 0 || sh.bad) {
     const uint32_t err = sh.bad ? (uint32_t)ERR_ARG : 0u;
     if (tid == 0) {
@@ -1834,8 +1782,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     int32_t* fin = (L & 1) ? a.front1 : a.front0;
     for (uint32_t i = tid; i < min(F, FC); i += NB)
       fin[(size_t)NQF * a.fcap + i] = (int32_t)s_front[cur + i];
-    if (P == PROB_BFS)
-      for (uint32_t i = tid; i < nbits; i += NB) vis[i] = s_bits[i];
+    for (uint32_t i = tid; i < nbits; i += NB) vis[i] = s_bits[i];
     for (uint32_t i = tid; i < (uint32_t)a.ngroups_cap; i += NB) {
       a.grp_packed[(L % 3) * a.ngroups_cap + i] = 0;
       a.grp_done[(L % 3) * a.ngroups_cap + i] = 0;
@@ -1845,7 +1792,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     for (uint32_t i = tid; i < 3 * sizeof(LevelSet) / 4; i += NB) sets[i] = i == fill ? F : 0u;
   }
   uint32_t code = wide ? V_TOP_DOWN : V_MORE;
-  if (P == PROB_BFS && a.bottom_up && wide) {
+  if (a.bottom_up && wide) {
     // the level's edges, from the degrees of up to NB of its vertices
     const int32_t* fin = (L & 1) ? a.front1 : a.front0;
     uint32_t deg = 0, v = 0;
@@ -1891,10 +1838,237 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     st->run_edges = run_edges;
     if (L != L0) {
       st->vsel[L & 1] = c;
-      st->vstale[L & 1] = P == PROB_BFS ? 1u : 0u;
+      st->vstale[L & 1] = 1u;
       st->levels_run = L;
     }
     post_verdict(verdict, ticket, code, 0);
+  }
+}
+
+// ------------------------------------------------------------ solo traversals
+// SSSP on a small graph in one workgroup, from the source to the last level,
+// distances and frontier in LDS.  On such a graph a level step is four kernels
+// of 5 to 25 us whose relaxations meet on a few hubs; here a level is two
+// dependent loads, and then about 1.3 edges a cycle, bound by the compute unit's
+// instructions (about 45 a wave and 64 edges).  8,191 vertices, 204,000 entries:
+// 422 -> 376 us.  Frontier entries past what LDS holds go to the overflow queues
+// and are run in passes.
+struct SoloLds {
+  uint32_t words[SOLO_WORDS];
+  unsigned long long rows[NARROW_BLOCK / 64][64];  // per wave: {row start, distance} of a window
+  __align__(8) uint8_t heads[NARROW_BLOCK / 64][64 * NARROW_U];
+  uint32_t wsum[NARROW_BLOCK / 64], wrows[NARROW_BLOCK / 64];
+  uint32_t cnt, bad;
+};
+
+// Writes its output and its verdict and needs nothing of the workspace but the
+// overflow queues.
+__global__ __launch_bounds__(NARROW_BLOCK) void solo_kernel(Args a, uint32_t src, uint32_t ticket,
+                                                            uint32_t* verdict) {
+  __shared__ SoloLds sh;
+  constexpr uint32_t NB = NARROW_BLOCK, PER = SOLO_FRONT / NB, U = NARROW_U;
+  const uint32_t tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const uint32_t n = (uint32_t)a.n, nbits = (n + 31) / 32;
+  const uint32_t FC = min((uint32_t)SOLO_FRONT, (SOLO_WORDS - nbits - n) / 5);
+  uint32_t* s_dist = sh.words;
+  uint32_t* s_bits = s_dist + n;       // queued for the next level
+  uint32_t* s_front = s_bits + nbits;  // two of FC: this level's, the next one's
+  uint32_t* s_start = s_front + 2 * FC;
+  uint32_t* s_off = s_front + 3 * FC;
+  uint32_t* s_slot = s_front + 4 * FC;
+  for (uint32_t i = tid; i < n; i += NB) s_dist[i] = i == src ? 0u : 0xFFFFFFFFu;
+  for (uint32_t i = tid; i < nbits; i += NB) s_bits[i] = 0;
+  if (tid == 0) {
+    s_front[0] = src;
+    sh.bad = 0;
+    sh.cnt = 0;
+  }
+  __syncthreads();
+  uint32_t cur = 0, nxt = FC, F = 1;
+  for (uint32_t L = 0; F != 0 && L <= n; ++L) {
+    uint32_t* spill_in = (uint32_t*)((L & 1) ? a.front1 : a.front0) + (size_t)NQF * a.fcap;
+    uint32_t* spill_out = (uint32_t*)((L & 1) ? a.front0 : a.front1) + (size_t)NQF * a.fcap;
+    // appends what a batch found
+    auto append = [&](const bool (&f)[U], const uint32_t (&v)[U]) {
+      bool any = false;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) any |= f[u];
+      if (!__any(any)) return;
+      unsigned long long m[U];
+      uint32_t total = 0, base = 0;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        m[u] = __ballot(f[u]);
+        total += (uint32_t)__popcll(m[u]);
+      }
+      if (lane == 0) base = atomicAdd(&sh.cnt, total);
+      base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t pos = base + lane_rank(m[u]);
+        base += (uint32_t)__popcll(m[u]);
+        if (!f[u]) continue;
+        if (pos < FC) s_front[nxt + pos] = v[u];
+        else if (pos < n) spill_out[pos] = v[u];
+      }
+    };
+    // edges ei[u] of rows at distance du[u] (all ones: none); all loads, then
+    // all probes, then all atomics
+    auto edges = [&](const uint32_t (&ei)[U], const uint32_t (&du)[U]) {
+      uint32_t v[U], nd[U], x[U];
+      bool f[U];
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const bool on = du[u] != 0xFFFFFFFFu;
+        v[u] = on ? (uint32_t)a.col[ei[u]] : 0u;
+        nd[u] = on ? a.w[ei[u]] : 0u;
+      }
+      pin(v);
+      pin(nd);
+      bool bad = false;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t sum = du[u] + nd[u];  // saturating, as in visit_batch
+        nd[u] = sum < du[u] ? 0xFFFFFFFFu : sum;
+        bad |= v[u] >= n;
+        x[u] = s_dist[min(v[u], n - 1)];
+      }
+      if (bad) sh.bad = 1;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        if (nd[u] < x[u] && v[u] < n) x[u] = atomicMin(&s_dist[v[u]], nd[u]);
+        else x[u] = 0;
+      }
+      pin(x);
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t bit = 1u << (v[u] & 31);
+        if (nd[u] < x[u]) x[u] = atomicOr(&s_bits[v[u] >> 5], bit) & bit;
+        else x[u] = 1;
+      }
+      pin(x);
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) f[u] = x[u] == 0;
+      append(f, v);
+    };
+    for (uint32_t done = 0; done < F; done += FC) {
+      const uint32_t count = min(F - done, FC);
+      if (done) {
+        for (uint32_t i = tid; i < count; i += NB) s_front[cur + i] = spill_in[done + i];
+        __syncthreads();
+      }
+      // rows of this thread's entries [tid * per, tid * per + per)
+      const uint32_t per = ceil_div(count, NB);
+      uint32_t start[PER], deg[PER], sum = 0, rows = 0;
+      bool big = count > NB;
+#pragma unroll
+      for (uint32_t j = 0; j < PER; ++j) {
+        const uint32_t i = tid * per + j;
+        start[j] = deg[j] = 0;
+        if (j < per && i < count) {
+          const uint32_t v = s_front[cur + i];
+          start[j] = (uint32_t)a.rp[v];
+          deg[j] = (uint32_t)a.rp[v + 1];
+          atomicAnd(&s_bits[v >> 5], ~(1u << (v & 31)));  // may be queued again
+        }
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < PER; ++j) {
+        deg[j] -= start[j];
+        sum += deg[j];
+        rows += deg[j] != 0;
+        big |= deg[j] > U;
+      }
+      if (!__syncthreads_or(big)) {
+        // one short row per thread, which it runs itself
+        if (__any(deg[0] != 0)) {
+          const uint32_t d = deg[0] ? s_dist[s_front[cur + tid]] : 0xFFFFFFFFu;
+          uint32_t ei[U], du[U];
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) {
+            ei[u] = start[0] + u;
+            du[u] = u < deg[0] ? d : 0xFFFFFFFFu;
+          }
+          edges(ei, du);
+        }
+      } else {
+        // the non-empty rows and their scanned degrees
+        const uint32_t incl = wave_incl_scan(sum, lane), rincl = wave_incl_scan(rows, lane);
+        if (lane == 63) {
+          sh.wsum[wave] = incl;
+          sh.wrows[wave] = rincl;
+        }
+        lds_barrier();
+        uint32_t run = incl - sum, E = 0, row = rincl - rows, R = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < NB / 64; ++w) {
+          if (w < (uint32_t)wave) {
+            run += sh.wsum[w];
+            row += sh.wrows[w];
+          }
+          E += sh.wsum[w];
+          R += sh.wrows[w];
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < PER; ++j) {
+          if (deg[j] == 0) continue;
+          s_start[row] = start[j] - run;  // edge x of the pass is start + x
+          s_off[row] = run;
+          s_slot[row] = s_front[cur + tid * per + j];
+          run += deg[j];
+          ++row;
+        }
+        lds_barrier();
+        // a wave runs chunks of 64 * U edges, their rows in windows of 64
+        uint8_t* heads = sh.heads[wave];
+        unsigned long long* info = sh.rows[wave];
+        for (uint32_t x0 = wave * 64 * U; x0 < E; x0 += NB * U) {
+          const uint32_t hi = min(x0 + 64 * U, E);
+          uint32_t p0 = wave_upper_search(R, x0, lane, [&](uint32_t k) { return s_off[k]; });
+          for (uint32_t lo = x0; lo < hi; p0 += 64) {
+            const uint32_t k = p0 + (uint32_t)lane;
+            const uint32_t off = k < R ? s_off[k] : E;
+            const uint32_t end = min(hi, p0 + 64 < R ? s_off[p0 + 64] : E);
+            clear_heads(heads, lane);
+            if (off < end) {
+              // a parent improved (and queued) again meanwhile does no work now
+              const uint32_t v = s_slot[k];
+              const uint32_t d = s_bits[v >> 5] >> (v & 31) & 1u ? 0xFFFFFFFFu : s_dist[v];
+              info[lane] = (unsigned long long)d << 32 | s_start[k];
+              if (off > lo) heads[off - lo - 1] = 1;
+            }
+            wave_lds_sync();
+            uint32_t ei[U], du[U], p = 0;
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+              const uint32_t x = lo + u * 64 + lane;
+              const unsigned long long r = info[row_of(heads, u, lane, p)];
+              ei[u] = (uint32_t)r + x;
+              du[u] = x < end ? (uint32_t)(r >> 32) : 0xFFFFFFFFu;
+            }
+            edges(ei, du);
+            wave_lds_sync();  // heads and rows are rewritten by the next window
+            lo = end;
+          }
+        }
+      }
+      // (with a spilled frontier the next pass or level reads what this one
+      // stored globally)
+      __syncthreads();
+    }
+    F = sh.cnt;
+    const uint32_t t = cur;
+    cur = nxt;
+    nxt = t;
+    lds_barrier();
+    if (tid == 0) sh.cnt = 0;
+    lds_barrier();
+  }
+  for (uint32_t i = tid; i < n; i += NB) a.dist[i] = s_dist[i];
+  if (tid == 0) {
+    const uint32_t err = sh.bad ? (uint32_t)ERR_ARG : F ? (uint32_t)ERR_TIMEOUT : 0u;
+    post_verdict(verdict, ticket, err ? V_ERROR : V_DONE, err);
   }
 }
 
@@ -2719,12 +2893,11 @@ const void* child_kernel_ptr(int problem, bool timed, bool nt) {
 
 const void* init_kernel_ptr(int) { return (const void*)init_kernel; }
 
-const void* narrow_kernel_ptr(int problem, int32_t slots) {
-  if (problem == PROB_SSSP)
-    return slots <= NARROW_DIST ? (const void*)narrow_kernel<PROB_SSSP, true> : nullptr;
-  return slots / 32 <= NARROW_BITS ? (const void*)narrow_kernel<PROB_BFS, true>
-                                   : (const void*)narrow_kernel<PROB_BFS, false>;
+const void* narrow_kernel_ptr(int32_t slots) {
+  return slots / 32 <= NARROW_BITS ? (const void*)narrow_kernel<true> : (const void*)narrow_kernel<false>;
 }
+
+const void* solo_kernel_ptr() { return (const void*)solo_kernel; }
 
 const void* symmetry_kernel_ptr(bool arena) {
   return arena ? (const void*)symmetry_kernel<true> : (const void*)symmetry_kernel<false>;
