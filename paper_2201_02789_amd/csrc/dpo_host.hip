@@ -316,6 +316,8 @@ struct SetRun {
   int32_t* qlist = nullptr;  // device: indices of the queries being admitted
 };
 
+bool dense_graph(const dpo_csr& g) { return g.m >= (int64_t)HINT_AUTO_MIN_DEGREE * g.n; }
+
 // tm: phase-timing rows; non-null selects the timed instantiations of the
 // level kernels, run at the grid sizes of the product ones (same schedule).
 dpo_status prepare_set(Runtime& r, int problem, const dpo_csr* g, const dpo_options& o,
@@ -334,7 +336,7 @@ dpo_status prepare_set(Runtime& r, int problem, const dpo_csr* g, const dpo_opti
   // and BFS batches whose queries go bottom-up, on graphs whose average degree is at least HINT_AUTO_MIN_DEGREE, unless the options say
   // otherwise.  The harvest adds a kernel launch to every level step; a graph of
   // low average degree runs many narrow levels and rarely a wide one.
-  const bool dense = g->m >= (int64_t)HINT_AUTO_MIN_DEGREE * g->n;
+  const bool dense = dense_graph(*g);
   const bool bfs = problem == PROB_BFS;
   // Queries that go bottom-up by themselves: a serving engine, and a batch that
   // is at least as large as its arena (the symmetry check reads all of it, and
@@ -703,6 +705,16 @@ dpo_status traverse(int problem, const dpo_csr* g, int32_t source, const dpo_opt
   sr.a.bottom_up = narrow && sr.a.hint ? BU_SINGLE : BU_OFF;
   s = start_single(r, sr, Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source});
   if (s != DPO_OK) return s;
+  if (any && problem == PROB_SSSP && g->n <= NEAR_VERTICES && !dense_graph(*g)) {
+    uint32_t* verdict = r.host_flags + 8;
+    uint32_t src = (uint32_t)source;
+    void* p[] = {&sr.a, &src, &verdict};
+    if (hipLaunchKernel(near_kernel_ptr(), dim3(1), dim3(NARROW_BLOCK), p, 0, sr.stream) != hipSuccess ||
+        hipStreamSynchronize(sr.stream) != hipSuccess)
+      return DPO_ERR_HIP;
+    const uint32_t code = *verdict & 15u;
+    if (code != V_TOP_DOWN) return code == V_DONE ? DPO_OK : (dpo_status)(-(int32_t)((*verdict >> 4) & 15u));
+  }
   s = narrow ? run_narrow_and_wide(r, sr, g->n) : run_to_completion(r, sr, g->n);
   return s != DPO_OK ? s : read_stats(r, sr, st);
 }

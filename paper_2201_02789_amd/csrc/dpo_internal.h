@@ -46,6 +46,14 @@ constexpr int32_t SOLO_VERTICES = 16384;
 constexpr int32_t SOLO_EDGES = 1 << 18;
 constexpr uint32_t SOLO_WORDS = 34 * 1024;
 constexpr uint32_t SOLO_FRONT = 4096;
+// near-far SSSP: frontier entries, vertices (two bits each in LDS), edges of a
+// round, average weights by which the bound moves (a 301 x 257 road-like graph
+// takes 4.15 / 3.73 / 3.85 / 4.69 / 7.5 ms at 4 / 8 / 16 / 32 / 64)
+constexpr uint32_t NEAR_WORDS = 36 * 1024;
+constexpr uint32_t NEAR_FRONT = 4096;
+constexpr int32_t NEAR_VERTICES = (NEAR_WORDS - 5 * NEAR_FRONT) / 2 * 32;
+constexpr uint32_t NEAR_EDGES = 1 << 14;
+constexpr uint32_t NEAR_STEP = 8;
 constexpr uint32_t NONE = 0xFFFFFFFFu;        // no vertex
 constexpr uint32_t NARROW_LEVELS = 4096;      // most levels per launch (a few ms)
 // How a narrow launch ended: the traversal done or failed, more narrow levels,
@@ -212,6 +220,7 @@ const void* serial_kernel_ptr(int problem, int gran, bool timed = false);
 const void* harvest_kernel_ptr(int problem, bool timed = false);
 const void* init_kernel_ptr(int problem);
 const void* narrow_kernel_ptr(int32_t slots);
+const void* near_kernel_ptr();
 const void* solo_kernel_ptr();
 const void* symmetry_kernel_ptr(bool arena);
 const void* bottom_up_kernel_ptr();
