@@ -26,7 +26,6 @@ namespace {
 constexpr int kDefaultSteps = 16;
 constexpr int kBatchSteps = 8;  // a batch of skewed graphs is done in one or two such replays
 constexpr int kMaxCachedGraphs = 64;
-constexpr int kStepsAhead = 4;  // dpo_bfs_noalloc: level steps per look at the flags
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -620,22 +619,35 @@ dpo_status wait_verdict(const uint32_t* verdict, uint32_t ticket, hipStream_t st
   }
 }
 
+// The verdict from a copy of the state (on the stack: no pinned memory).
+dpo_status copy_verdict(SetRun& sr, uint32_t* out) {
+  uint32_t head[offsetof(State, plan) / 4 + 1];
+  if (hipMemcpyAsync(head, sr.a.st, sizeof(head), hipMemcpyDeviceToHost, sr.stream) != hipSuccess ||
+      hipStreamSynchronize(sr.stream) != hipSuccess)
+    return DPO_ERR_HIP;
+  const uint32_t done = head[offsetof(State, done) / 4], error = head[offsetof(State, error) / 4];
+  *out = error << 4 | (error ? V_ERROR : done ? V_DONE : head[offsetof(State, plan) / 4]);
+  return DPO_OK;
+}
+
 // A single traversal: narrow levels in one launch, then a wide one.  The host
 // learns from the narrow kernel's verdict which kernels that takes.  Bottom-up
 // levels follow each other more often than not: two are launched at a time, the
 // second of which finds out by itself whether it is due.
-dpo_status run_narrow_and_wide(Runtime& r, SetRun& sr, int64_t max_levels) {
-  uint32_t* verdict = r.host_flags + 8;
+// verdict: pinned word for it, or nullptr where none may be allocated; the state
+// is copied then, which takes about 15 us each time.
+dpo_status run_narrow_and_wide(Runtime& r, SetRun& sr, int64_t max_levels, uint32_t* verdict) {
   uint32_t after = AFTER_NONE;
   for (int64_t rep = 0; rep < max_levels + 2; ++rep) {
     r.ticket = (r.ticket + 1) & 0xFFFFFFu;
     dpo_status s = launch_narrow(sr, after, r.ticket, verdict);
     uint32_t v = 0;
-    if (s == DPO_OK) s = wait_verdict(verdict, r.ticket, sr.stream, &v);
+    if (s == DPO_OK)
+      s = verdict ? wait_verdict(verdict, r.ticket, sr.stream, &v) : copy_verdict(sr, &v);
     if (s != DPO_OK) return s;
     const uint32_t code = v & 15u;
     if (code == V_DONE || code == V_ERROR) {
-      if (hipStreamSynchronize(sr.stream) != hipSuccess) return DPO_ERR_HIP;
+      if (verdict && hipStreamSynchronize(sr.stream) != hipSuccess) return DPO_ERR_HIP;
       return code == V_DONE ? DPO_OK : (dpo_status)(-(int32_t)((v >> 4) & 15u));
     }
     after = AFTER_NONE;
@@ -715,7 +727,7 @@ dpo_status traverse(int problem, const dpo_csr* g, int32_t source, const dpo_opt
     const uint32_t code = *verdict & 15u;
     if (code != V_TOP_DOWN) return code == V_DONE ? DPO_OK : (dpo_status)(-(int32_t)((*verdict >> 4) & 15u));
   }
-  s = narrow ? run_narrow_and_wide(r, sr, g->n) : run_to_completion(r, sr, g->n);
+  s = narrow ? run_narrow_and_wide(r, sr, g->n, r.host_flags + 8) : run_to_completion(r, sr, g->n);
   return s != DPO_OK ? s : read_stats(r, sr, st);
 }
 
@@ -838,23 +850,17 @@ dpo_status traverse_noalloc(int problem, const dpo_csr* g, int32_t source, const
   sr.a.bottom_up = narrow && sr.a.hint ? BU_SINGLE : BU_OFF;
   s = start_single(r, sr, Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source});
   if (s != DPO_OK) return s;
+  if (narrow) return run_narrow_and_wide(r, sr, g->n, nullptr);
   uint32_t flags[4] = {0, 0, 0, 0};  // base, done, error, levels_run
+  const int64_t max_replays = (int64_t)g->n / sr.steps + 2;
   State* st = sr.a.st;
   uint32_t k = (uint32_t)sr.steps;
   uint32_t* no_flags = nullptr;  // no pinned memory here: the flags are copied
-  // narrow levels run in one workgroup; a few wide ones are launched ahead of
-  // each look at the flags (what is not due finds nothing to do)
-  const int ahead = narrow ? std::min(sr.steps, kStepsAhead) : sr.steps;
-  const int64_t max_replays = (int64_t)g->n / ahead + 2;
-  if (narrow && (s = launch_narrow(sr, AFTER_NONE, 0u, nullptr)) != DPO_OK) return s;
   for (int64_t rep = 0; rep < max_replays; ++rep) {
-    for (int i = 0; i < ahead; ++i) {
-      if (sr.a.bottom_up && (s = launch_bottom_up(r, sr, true)) != DPO_OK) return s;
-      if ((s = launch_step(sr, narrow ? 0u : (uint32_t)i)) != DPO_OK) return s;
-      if (narrow && (s = launch_narrow(sr, AFTER_ANY, 0u, nullptr)) != DPO_OK) return s;
-    }
+    for (int i = 0; i < sr.steps; ++i)
+      if ((s = launch_step(sr, (uint32_t)i)) != DPO_OK) return s;
     void* ap[] = {&st, &k, &no_flags};
-    if (!narrow && hipLaunchKernel(advance_kernel_ptr(), dim3(1), dim3(64), ap, 0, sr.stream) != hipSuccess)
+    if (hipLaunchKernel(advance_kernel_ptr(), dim3(1), dim3(64), ap, 0, sr.stream) != hipSuccess)
       return DPO_ERR_HIP;
     if (hipMemcpyAsync(flags, st, sizeof(flags), hipMemcpyDeviceToHost, sr.stream) != hipSuccess ||
         hipStreamSynchronize(sr.stream) != hipSuccess)

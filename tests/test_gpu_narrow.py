@@ -38,8 +38,8 @@ GRAPHS = [
     ("stars-8191", lambda: _stars(8191, 2), 0),
     ("stars-8192", lambda: _stars(8192, 2), 0),
     ("stars-8193", lambda: _stars(8193, 2), 0),
-    ("stars-4095", lambda: _stars(4095, 1), 0),
-    ("stars-4097", lambda: _stars(4097, 1), 0),
+    ("stars-8191-1", lambda: _stars(4095, 1), 0),
+    ("stars-8193-1", lambda: _stars(4097, 1), 0),
     ("stars-131071", lambda: _stars(131071, 1), 0),
     ("stars-131073", lambda: _stars(131073, 1), 0),
     ("road", lambda: gg.road_like(150, 170, 3), 11),
