@@ -7,6 +7,16 @@ namespace dpo {
 
 constexpr int PB = 256;          // parent workgroup: 256 frontier entries per virtual block
 constexpr int NW = PB / 64;      // wave64s per workgroup
+// A parent wave has as many frontier entries as have this many edges on the
+// graph's average, if there are workgroups for it.  A wave runs the thresholded
+// children of its entries 512 edges at a time, one batch after another, so a
+// frontier of a few hundred entries in blocks of PB is a handful of waves with
+// 2,000 edges each while the rest of the chip has none.  Whole BFS calls (us;
+// Erdos-Renyi, vertices/average degree), full blocks -> at 384: 2 M/30 432 -> 386,
+// 1 M/16 322 -> 307, 100 K/64 205 -> 159, 250 K/8 257 -> 262; R-MAT of 1 M, degree 32,
+// 248 -> 240.  At 768 2 M/30 takes 390 and 100 K/64 174; at 192 250 K/8 takes 292:
+// blocks of few edges cost more than they spread.
+constexpr int SPREAD_EDGES = 384;
 constexpr int STAGE = 512;       // LDS slots per wave for next-frontier staging
 constexpr int NQD = 8;           // descriptor queues (one per XCD: queue = virtual block % 8)
 constexpr int NQF = 64;          // frontier queues (queue = workgroup % 64), plus one overflow
@@ -69,9 +79,9 @@ enum { AFTER_NONE = 0, AFTER_STEP, AFTER_BOTTOM_UP };
 // bottom-up levels (BFS)
 // A level goes bottom-up if its frontier has at least 1 / BU_ALPHA of the edges
 // not yet run, so that a vertex looks at about BU_ALPHA entries at most.
-// Measured (us, before the symmetry check was tuned): R-MAT of 70,001 vertices
-// 160 / 121 / 122 / 123 at 4 / 8 / 16 / 32, scale 22 620 / 606 / 582 / 590,
-// Erdos-Renyi of 2 M 518 / 512 / 512 / 515.
+// Measured (us, worst of three seeds) at 8 / 16 / 32 / 64: Erdos-Renyi of 2 M
+// 386 / 382 / 382 / 584, a batch of 512 1,860 / 1,824 / 1,903 / 2,085; R-MAT of
+// scale 22 618 / 472 / 472.
 constexpr uint32_t BU_ALPHA = 16;
 // Several queries: frontier entries from which a level's edges are tallied, and
 // edges from which a query may go bottom-up (fewer are run top-down in less

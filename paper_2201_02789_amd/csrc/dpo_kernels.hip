@@ -561,13 +561,14 @@ __device__ __forceinline__ bool group_block_done(const Args& a, uint32_t vb, uin
   return atomicAdd(&a.grp_done[(L % 3) * a.ngroups_cap + g], 1u) == in_group - 1;
 }
 
-__device__ __forceinline__ void publish_group(const Args& a, LevelSet* ls, uint32_t vb, uint32_t L,
-                                              uint32_t& descs) {
+// epb: frontier entries per virtual block
+__device__ __forceinline__ void publish_group(const Args& a, LevelSet* ls, uint32_t vb, uint32_t epb,
+                                              uint32_t L, uint32_t& descs) {
   const uint32_t g = vb / (uint32_t)a.k;
   const unsigned long long tot = atomicAdd(&a.grp_packed[(L % 3) * a.ngroups_cap + g], 0ull);
   const uint32_t nrec = (uint32_t)(tot >> 32);
   if (nrec == 0) return;
-  publish(a, ls, g % NQD, g * (uint32_t)a.k * PB, nrec, (uint32_t)tot);
+  publish(a, ls, g % NQD, g * (uint32_t)a.k * epb, nrec, (uint32_t)tot);
   ++descs;
 }
 
@@ -673,7 +674,23 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
 
   Stage s{s_stage[wave], 0u};
   Counters cn{0, 0, 0, 0, 0, 0, 0};
-  const uint32_t nvb = ceil_div(F, PB);
+  // Frontier entries per virtual block, and per wave of it: PB and 64, or fewer
+  // where that would leave workgroups of the grid without a block while waves
+  // have more than SPREAD_EDGES edges on average.  The groups, lists and records
+  // of a level are sized for slots / PB blocks of PB entries, so never more
+  // blocks than that.  A run that counts or times grids keeps blocks of PB
+  // parents, and so does SSSP, whose thresholded parents are shared out evenly
+  // after the lists are complete (spread as well, a batch of 64 took 2 % longer:
+  // more and smaller grids).
+  uint32_t epb = PB;
+  if (P == PROB_BFS && PH == PH_BOTH && !TM && !a.count_stats) {
+    const uint32_t most = min(gridDim.x, (uint32_t)a.slots / PB);
+    while ((uint64_t)epb * (uint32_t)a.m > (uint64_t)SPREAD_EDGES * NW * (uint32_t)a.n &&
+           epb > (uint32_t)NW && ceil_div(F, epb / 2) <= most)
+      epb /= 2;
+  }
+  const uint32_t epw = epb / NW;
+  const uint32_t nvb = ceil_div(F, epb);
   // thresholded parents listed by this workgroup
   if (tid == 0) s_ser[0] = PH == PH_SERIAL ? a.sercnt[blockIdx.x] : 0u;
   __syncthreads();
@@ -725,8 +742,10 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
       int32_t slot[4];
 #pragma unroll
       for (uint32_t c = 0; c < 4; ++c) {
-        const uint64_t i = ((uint64_t)blockIdx.x + (uint64_t)(r + c) * gridDim.x) * PB + tid;
-        slot[c] = r + c < rounds && i < F ? frontier_at(a, fin, s_fpre, (uint32_t)i) : -1;
+        const uint64_t i =
+            ((uint64_t)blockIdx.x + (uint64_t)(r + c) * gridDim.x) * epb + wave * epw + lane;
+        const bool in = r + c < rounds && (uint32_t)lane < epw && i < F;
+        slot[c] = in ? frontier_at(a, fin, s_fpre, (uint32_t)i) : -1;
       }
       pin(slot);
 #pragma unroll
@@ -747,7 +766,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
   // aggregation and launch records; thresholded parents go to this
   // workgroup's serial list for pass 2.
   for (uint32_t vb = blockIdx.x; vb < (PH == PH_SERIAL ? 0u : nvb); vb += gridDim.x) {
-    const uint32_t i = vb * PB + tid;
+    const uint32_t i = (uint32_t)lane < epw ? vb * epb + wave * epw + lane : F;
     int32_t start = 0, deg = 0, q = 0, slot = 0;
     uint32_t du = 0, cg = 0;
     bool launch = false, ser = false;
@@ -756,7 +775,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
       if (!(s_some[P == PROB_BFS ? r / 32 % SOME_WORDS : 0] >> (r & 31) & 1u)) {
         // nothing here for this kernel, but its group still counts the block
         if (G == AGG_MULTI && tid == 0 && group_block_done(a, vb, nvb, L))
-          publish_group(a, cur, vb, L, cn.desc);
+          publish_group(a, cur, vb, epb, L, cn.desc);
         continue;
       }
     }
@@ -828,7 +847,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
       } else if (G == AGG_WAVE) {
         const unsigned long long m = __ballot(launch);
         const uint32_t nrec = (uint32_t)__popcll(m);
-        const uint32_t seg = vb * PB + wave * 64;
+        const uint32_t seg = vb * epb + wave * epw;
         if (m && nrec < (uint32_t)a.agg_threshold) {
           // too few participants (Sec. V-B): each parent launches its own grid
           if (launch) put_record<P>(a, seg + lane_rank(m), start, deg, 0u, du, q, slot);
@@ -868,7 +887,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
           total_b += s_scan[NW + w];
         }
         if (G == AGG_BLOCK) {
-          const uint32_t seg = vb * PB;
+          const uint32_t seg = vb * epb;
           if (nrec_b < (uint32_t)a.agg_threshold) {
             // too few participants (Sec. V-B): each parent launches its own grid
             const uint32_t r = seg + roff + lane_rank(m);
@@ -893,7 +912,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
           __syncthreads();  // s_scan reuse
         } else {  // AGG_MULTI: group of k consecutive virtual blocks (Sec. V-A)
           const uint32_t g = vb / (uint32_t)a.k;
-          const uint32_t seg = g * (uint32_t)a.k * PB;
+          const uint32_t seg = g * (uint32_t)a.k * epb;
           unsigned long long* gp = &a.grp_packed[(L % 3) * a.ngroups_cap + g];
           if (tid == 0) {
             unsigned long long old = 0;
@@ -913,7 +932,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
           bool last_block = false;
           if (tid == 0) last_block = group_block_done(a, vb, nvb, L);
           pc.mark(TP_AGG);
-          if (last_block) publish_group(a, cur, vb, L, cn.desc);
+          if (last_block) publish_group(a, cur, vb, epb, L, cn.desc);
           pc.mark(TP_LAUNCH);
           __syncthreads();  // s_scan / s_bc reuse
         }
