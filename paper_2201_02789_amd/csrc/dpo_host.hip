@@ -366,6 +366,8 @@ dpo_status prepare_set(Runtime& r, int problem, const dpo_csr* g, const dpo_opti
   a.visit = (uint32_t*)(base + lay.visit);
   // SSSP with found bytes has no iteration stamps: the bytes overlap them
   a.found = (uint8_t*)(base + lay.visit + found_offset(slots));
+  // in front of them, where BFS has its bitmaps
+  a.bound = !bfs && hint && slots >= BOUND_MIN_SLOTS ? (uint8_t*)(base + lay.visit) : nullptr;
   a.dist2 = problem == PROB_SSSP ? (uint32_t*)(base + lay.dist2) : nullptr;
   a.vwords = (int32_t)cdiv(slots, 32);
   a.rec = (int4*)(base + lay.rec);

@@ -29,6 +29,12 @@ constexpr int PH_SERIAL = 2;  // pass 2 of the listed parents (after the child k
 constexpr uint32_t GROUP_EDGES = 1024;  // wave-run serial children: edges per group (about)
 constexpr int MAX_QUERIES = 4096;  // per-query tables are staged in LDS
 constexpr int ADMIT_CHUNK = 4096;  // output slots initialised per admit workgroup
+// SSSP bounds are kept from this many slots on: more distances than an XCD's L2
+// holds (4 MiB), while their bytes fit, so that fewer reads miss it (scale 21, the
+// widest level's child grids: 11.0 M -> 6.5 M misses).  Off / on (us): R-MAT of
+// 1 M vertices 1,656 / 1,706, of 2 M 1,860 / 1,820; 24 queries served in 4 M slots
+// 2,334 / 2,213.  What remains is the rate of random accesses.
+constexpr int64_t BOUND_MIN_SLOTS = 1 << 20;
 constexpr int PRECHECK_MIN = 32;   // claim candidates per 512-lane batch above which
                                    // a coherent load precedes the atomics
 constexpr int NHINT = 8;           // BFS per-XCD visited copies (Args::hint), one per XCD
@@ -177,6 +183,8 @@ struct Args {
   uint8_t* found;                  // [vwords * 32] bytes (Args::hint), set for the vertices
                                    // a level's child bodies find (BFS: wide levels) or
                                    // improve (SSSP); read by the harvest kernel
+  uint8_t* bound;                  // SSSP with found bytes on many slots: [vwords * 32] a byte
+                                   // above which no sum improves the vertex; else null
   int4* rec;                       // [slots] launch records {row start, deg, offset, parent dist}
   int32_t* rec_q;                  // [slots] query of each record
   int32_t* rec_slot;               // [slots] SSSP: slot of each record's parent

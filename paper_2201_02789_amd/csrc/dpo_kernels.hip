@@ -255,6 +255,15 @@ __device__ __forceinline__ uint32_t coherent_load(const uint32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// SSSP bounds (Args::bound): a byte per vertex, not decreasing in the distance:
+// three bits below the leading one (exact up to 16, then eight steps an octave).
+// A sum whose byte is above that of any distance the vertex has had is above
+// that distance itself.
+__device__ __forceinline__ uint32_t bound_of(uint32_t d) {
+  const int32_t b = (int32_t)(__float_as_uint((float)d) >> 20) - (127 << 3);
+  return (uint32_t)min(max(b, 0), 255);
+}
+
 // Child body for U neighbours per lane (v < 0: none), all probes issued before
 // any atomic so that the U round trips overlap.  BFS: probe, then claim the
 // unvisited ones and write their level (per-XCD copies: record them as found).
@@ -346,8 +355,20 @@ __device__ __forceinline__ void visit_batch(const Args& a, const Vis& vis, const
       // no wrapped sum can undercut the true one
       const uint32_t sum = c[u].du + w[u];
       nd[u] = sum < c[u].du ? 0xFFFFFFFFu : sum;
-      cur[u] = sl[u] >= 0 ? dp[sl[u]] : 0u;
     }
+    // Most edges improve nothing, and most of those miss by far: a byte per
+    // vertex, which each L2 holds for all of them, tells before the distance is
+    // read.
+    if (a.bound) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) cur[u] = sl[u] >= 0 ? a.bound[sl[u]] : 0u;
+      pin(cur);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (sl[u] >= 0 && bound_of(nd[u]) > cur[u]) sl[u] = -1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) cur[u] = sl[u] >= 0 ? dp[sl[u]] : 0u;
     pin(cur);
     uint32_t ncand = 0;
     if (vis.split) {
@@ -803,6 +824,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
         // (the copy lacks just the frontier's improvements): a plain store
         if (PH == PH_LIST) vis.fold[slot] = du;
         else atomicMin(&vis.fold[slot], du);
+        if (a.bound) a.bound[slot] = (uint8_t)bound_of(du);
       } else if (entry_fold) {
         atomicOr(&vis.fold[(uint32_t)slot >> 5], 1u << (slot & 31));
       }
@@ -2992,6 +3014,8 @@ __global__ __launch_bounds__(PB) void start_kernel(Args a, Query Q) {
     uint32_t* f = (uint32_t*)a.found;
     for (uint32_t i = gid; i < (uint32_t)a.vwords * 8u; i += gsz) f[i] = 0u;
   }
+  if (P == PROB_SSSP && a.bound)
+    for (uint32_t i = gid; i < (uint32_t)a.vwords * 8u; i += gsz) ((uint32_t*)a.bound)[i] = ~0u;
   for (uint32_t i = gid; i < 3u * (uint32_t)a.ngroups_cap; i += gsz) {
     a.grp_packed[i] = 0;
     a.grp_done[i] = 0;
@@ -3058,6 +3082,8 @@ __global__ __launch_bounds__(PB) void admit_kernel(Args a, const int32_t* list, 
     } else if (a.hint) {  // SSSP: nothing found yet
       uint32_t* f = (uint32_t*)(a.found + (size_t)(s0 / 32 + i) * 32);
       for (int k = 0; k < 8; ++k) f[k] = 0u;
+      if (a.bound)
+        for (int k = 0; k < 8; ++k) ((uint32_t*)a.bound)[(size_t)(s0 / 32 + i) * 8 + k] = ~0u;
     }
   }
   if (reset) {
