@@ -1,10 +1,23 @@
 // Host driver and C ABI of the nested-parallel BFS / SSSP library.
 //
-// A traversal is: one init kernel, then HIP-graph replays of K captured level
-// steps (the step kernel reads its level, frontier and counters from the
-// workspace, so one instantiated graph serves every call with the same
-// arguments), with one stream synchronisation per replay to read the done
-// flag.  Instantiated graphs are cached by their exact kernel arguments.
+// Who runs what:
+//   dpo_bfs           start kernel; then narrow levels in one workgroup (the
+//                     narrow kernel runs as many as follow each other) and wide
+//                     ones as a level step or a bottom-up level, as the narrow
+//                     kernel's verdict says, which the host polls in pinned
+//                     memory (run_narrow_and_wide)
+//   dpo_bfs_noalloc   the same, the verdict read from a copy of the state
+//   dpo_sssp          small graphs: the solo kernel alone; sparse graphs up to
+//                     NEAR_VERTICES: the near-far kernel alone, unless a level
+//                     outgrows it; others: start kernel and replays
+//   batches, engines  init and admit kernels, the symmetry check (BFS by
+//                     found bytes), replays
+//   counters, phase timing, the flat and the one-grid-per-parent form: replays
+// A replay is a HIP graph of K captured level steps and the advance kernel,
+// which writes the level and the done flag to pinned memory.  The kernels read
+// their level, frontier and counters from the workspace, so one instantiated
+// graph serves every call with the same arguments; graphs are cached by their
+// exact kernel arguments.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -1,12 +1,19 @@
 // Device code: level-synchronous nested-parallel BFS / SSSP for gfx950.
 //
-// Each level is two kernels, the parent kernel and the child kernel; for SSSP
+// A level step is two kernels, the parent kernel and the child kernel; for SSSP
 // the parent kernel's second pass (the thresholded children) runs as a third
-// kernel after the child kernel, and with found bytes (single traversals, the
-// serving engine) a harvest kernel ends the level.
+// kernel after the child kernel, and with found bytes (Args::hint) a harvest
+// kernel ends the level.  Levels for which that is not the shortest way are run
+// by other kernels, each described where it stands: narrow BFS levels by one
+// workgroup (narrow_kernel), wide ones of a symmetric graph bottom-up
+// (bottom_up_kernel; queries of a batch or engine: tally_kernel,
+// bottom_up_words_kernel, bottom_up_queries_kernel; symmetry_kernel checks the
+// graph), whole SSSP traversals of small graphs (solo_kernel) and of sparse ones
+// (near_kernel) by one workgroup.
 //
 // Parent kernel: the parent grid.  Workgroups (256 lanes = 4 wave64) take
-// virtual parent blocks of 256 frontier entries in a grid-stride loop; lane i
+// virtual parent blocks of 256 frontier entries (fewer when a BFS frontier would
+// leave workgroups without one) in a grid-stride loop; lane i
 // is the parent thread of frontier vertex u with child-thread count deg(u)
 // (Sec. III-D):
 //
@@ -44,12 +51,13 @@
 // Child body: BFS probes a visited bitmap (one bit per output slot,
 // L2-resident), claims v in a second bitmap and writes its level; SSSP relaxes
 // a second distance array with atomicMin and queues v once per iteration
-// through an iteration stamp, or, for single traversals and the serving
-// engine, records v as found and leaves the queueing to the harvest kernel.
-// The probed and the updated copies swap every level.  BFS single traversals and the serving engine instead give each XCD a
-// probed copy of its own on wide levels and record discoveries as bytes, which
-// a third kernel, the harvest, turns into levels and the next frontier (Vis,
-// vis_of, harvest_kernel).
+// through an iteration stamp, or, with found bytes (single traversals, batches
+// and engines of dense graphs), records v as found and leaves the queueing to
+// the harvest kernel.
+// The probed and the updated copies swap every level.  BFS with found bytes
+// instead gives each XCD a probed copy of its own on wide levels and records
+// discoveries as bytes, which the harvest kernel turns into levels and the next
+// frontier (Vis, vis_of, harvest_kernel).
 //
 // Queries: a launch may carry many traversals ("queries") over graphs packed
 // in one CSR arena.  Query q owns the output slots [slot0, slot0 + n) (slot0 a
@@ -370,8 +378,14 @@ __device__ __forceinline__ void visit_batch(const Args& a, const Vis& vis, const
 #pragma unroll
     for (int u = 0; u < U; ++u) cur[u] = sl[u] >= 0 ? dp[sl[u]] : 0u;
     pin(cur);
+    // Many candidates: the claim array first, with coherent loads, so that an
+    // atomic is issued only for what is still an improvement.  Found bytes on few
+    // slots: no lane waits for the atomic then, and that round trip costs more than
+    // it saves (us, with / without: Erdos-Renyi of 1 M vertices, degree 16, 1,890 /
+    // 1,675, R-MAT of 250 K 820 / 792, a batch of 64 796 / 782; at scale 21, where
+    // the atomics leave L2, 1,860 / 1,884).
     uint32_t ncand = 0;
-    if (vis.split) {
+    if (vis.split && (!a.hint || a.bound)) {
 #pragma unroll
       for (int u = 0; u < U; ++u) ncand += (uint32_t)__popcll(__ballot(sl[u] >= 0 && nd[u] < cur[u]));
     }
@@ -1477,10 +1491,11 @@ __global__ __launch_bounds__(PB) void child_kernel(Args a, uint32_t step) {
 // found vertex was improved at this level; it joins the next frontier once and
 // its byte is cleared for the next level.  BFS with per-XCD copies, after a
 // wide level: a found vertex that the visited bitmap lacks was discovered at
-// this level.  It gets its level, its bit there and a place in the next frontier (in slot order, which also
-// makes the next level's row loads mostly consecutive).  A wave owns the found
-// bytes and the bitmap bytes of 512 slots at a time.  Found bytes are never cleared within a
-// traversal: one set at an earlier level belongs to a vertex that the harvest
+// this level.  It gets its level, its bit there and a place in the next frontier
+// (in slot order, which also makes the next level's row loads mostly
+// consecutive).  A wave owns the found bytes and the bitmap bytes of 512 slots at
+// a time.  Found bytes are never cleared within a traversal: one set at an
+// earlier level belongs to a vertex that the harvest
 // of that level put into the bitmap.  Admission clears a query's found bytes,
 // and a serving engine clears all of them when it is created
 // (clear_found_kernel), so slots outside every admitted query hold none.  A
