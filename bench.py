@@ -227,8 +227,10 @@ class Certifier:
 
 
 def reached_stats(dpo, torch, wl, dg, opts):
-    """(m_r, n_r, stats) per source from one untimed run with counters, and
-    how many sources' results pass their edge certificates."""
+    """(m_r, n_r, stats) per source from one untimed run with counters (level
+    steps only), and how many sources' results pass their edge certificates:
+    those of one more call without counters, whose kernels are the timed ones,
+    which must also equal the first's."""
     out = torch.empty(dg.n, dtype=torch.int32, device="cuda")
     ws = dpo.alloc_workspace(dg, opts)
     deg = torch.diff(dg.row_ptr).to(torch.int64)
@@ -236,20 +238,25 @@ def reached_stats(dpo, torch, wl, dg, opts):
     res, passed = [], 0
     for s in wl.sources:
         if wl.kind == "bfs":
-            st = dpo.dpo_bfs(dg, int(s), opts, out, ws, stats=True)
+            call, st = dpo.dpo_bfs, dpo.dpo_bfs(dg, int(s), opts, out, ws, stats=True)
             reached = out >= 0
         else:
-            st = dpo.dpo_sssp(dg, int(s), opts, out, ws, stats=True)
+            call, st = dpo.dpo_sssp, dpo.dpo_sssp(dg, int(s), opts, out, ws, stats=True)
             reached = out != -1  # 0xFFFFFFFF as int32
-        passed += int(cert(wl.kind, int(s), out))
+        counted = out.clone()
+        call(dg, int(s), opts, out, ws)
+        passed += int(cert(wl.kind, int(s), out) and torch.equal(out, counted))
         res.append((int(deg[reached].sum()), int(reached.sum()), st))
     del cert
     return res, passed
 
 
-# the kernels of a level step (SSSP runs parent_kernel twice; single
-# traversals add the harvest)
-LEVEL_KERNELS = ("parent_kernel", "child_kernel", "harvest_kernel")
+# the kernels that run levels: a level step's (SSSP runs parent_kernel twice;
+# single traversals add the harvest) and those that run narrow levels, bottom-up
+# ones (with the symmetry check before the first) and whole SSSP traversals
+LEVEL_KERNELS = ("parent_kernel", "child_kernel", "harvest_kernel", "narrow_kernel", "bottom_up",
+                 "symmetry_kernel", "solo_kernel", "near_kernel")
+START_KERNELS = ("init_kernel", "start_kernel")  # one per traversal set
 KERNEL_SOURCES = ["paper_2201_02789_amd/csrc/dpo_kernels.hip",
                   "paper_2201_02789_amd/csrc/dpo_host.hip",
                   "paper_2201_02789_amd/csrc/dpo_internal.h"]
@@ -565,7 +572,7 @@ def summarize_counters(args, d):
         inits = 0
         for r in csv.DictReader(open(files[0])):
             n = _short(r["Kernel_Name"])
-            if n == "init_kernel":
+            if n.startswith(START_KERNELS):
                 inits += 1
             if n.startswith(LEVEL_KERNELS):
                 c = agg.setdefault(n, {})
@@ -621,7 +628,7 @@ def summarize_profiles(args, d):
     for t0, t1, n in rows:
         c, tot = stats.get(n, (0, 0))
         stats[n] = (c + 1, tot + (t1 - t0))
-    traversals = sum(1 for _, _, n in rows if n == "init_kernel")
+    traversals = sum(1 for _, _, n in rows if n.startswith(START_KERNELS))
     step_ns = sum(t1 - t0 for t0, t1, n in rows if n.startswith(step))
     launches = traversals * launches_per
     kernel_us = step_ns / launches / 1e3
@@ -639,7 +646,7 @@ def summarize_profiles(args, d):
     sf, sw = copy_scale("copy_fetch", "FETCH_SIZE"), copy_scale("copy_write", "WRITE_SIZE")
     fetch = [(n, v) for n, v in per_dispatch("fetch", "FETCH_SIZE") if n.startswith(step)]
     write = [(n, v) for n, v in per_dispatch("write", "WRITE_SIZE") if n.startswith(step)]
-    trav_pmc = sum(1 for n, _ in per_dispatch("fetch", "FETCH_SIZE") if n == "init_kernel")
+    trav_pmc = sum(1 for n, _ in per_dispatch("fetch", "FETCH_SIZE") if n.startswith(START_KERNELS))
     launches_pmc = trav_pmc * launches_per
     fetch_b = sum(v for _, v in fetch) * 1024 * sf / launches_pmc
     write_b = sum(v for _, v in write) * 1024 * sw / launches_pmc
@@ -653,7 +660,7 @@ def summarize_profiles(args, d):
     alg = line["roofline"]["algorithmic_bytes_per_launch"]
     # the library's kernels (torch's kernels of the untimed result certificates
     # and the calibration kernel of the probe roofline are left out)
-    ours = LEVEL_KERNELS + ("init_kernel", "admit", "advance", "clear_found", "__amd_rocclr")
+    ours = LEVEL_KERNELS + START_KERNELS + ("admit", "advance", "clear_found", "__amd_rocclr")
     top = sorted(((n, v) for n, v in stats.items() if n.startswith(ours)), key=lambda kv: -kv[1][1])[:8]
     md = [f"# {args.workload}: kernel time and HBM traffic ({label})", "",
           "Commands (MI355X, from the repository root, after `export TMPDIR=/tmp`):", "",
@@ -788,8 +795,10 @@ def workload_line(args, dpo, torch, name, steps, warmup, with_cpu, with_baseline
     gteps = steps * edges_step / (total_ms * 1e-3) / 1e9
     log(f"[bench] T+C+A: {gteps:.2f} GTEPS, {t_step_ms.mean():.3f} ms/step, wall {wall:.3f}s")
 
-    # roofline of the level-step kernel: algorithmic bytes per launch / mean
-    # launch duration, both per traversal divided by its launch count
+    # roofline of the level step: algorithmic bytes per launch / mean launch
+    # duration, both per traversal divided by its launch count.  The count is
+    # that of the level steps; the timed calls run narrow and bottom-up levels
+    # by other kernels, so only the quotient of the two is a rate.
     launches = np.array([r[2]["levels"] + 1 for r in rs], dtype=np.float64)
     bytes_call = algorithmic_bytes(wl.kind, m_r, n_r)
     mean_call_ms = per_call.mean(axis=0)
@@ -808,7 +817,8 @@ def workload_line(args, dpo, torch, name, steps, warmup, with_cpu, with_baseline
     # second roofline: the child body's dependent random probes (BFS: the
     # n-bit visited bitmap; SSSP: the n-word distance array), one per edge
     # run, against the rate the chip sustains for random 4-byte loads from a
-    # table of that size (measured here, 8 loads in flight per lane)
+    # table of that size (measured here, 8 loads in flight per lane).  A BFS
+    # whose wide levels go bottom-up probes fewer, so its share may pass 1.
     probed_bytes = wl.g.n // 8 if wl.kind == "bfs" else 4 * wl.g.n
     table = 1 << max(12, int(np.ceil(np.log2(max(probed_bytes, 1)))))
     ceiling = random_load_rate(torch, table)
