@@ -607,7 +607,8 @@ bool any_kernel(const dpo_options& o, bool stats, bool timed) {
 dpo_status launch_solo(SetRun& sr, int32_t source, uint32_t* verdict) {
   uint32_t src = (uint32_t)source, ticket = 0;
   void* p[] = {&sr.a, &src, &ticket, &verdict};
-  return hip_ok(hipLaunchKernel(solo_kernel_ptr(), dim3(1), dim3(NARROW_BLOCK), p, 0, sr.stream));
+  return hip_ok(hipLaunchKernel(solo_kernel_ptr(sr.a.m >= SOLO_FAR_EDGES), dim3(1), dim3(NARROW_BLOCK),
+                                p, 0, sr.stream));
 }
 
 // Waits for the verdict of narrow launch `ticket`.  The word is polled: a

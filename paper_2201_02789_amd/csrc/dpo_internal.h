@@ -58,10 +58,15 @@ constexpr uint32_t NARROW_FAR_EDGES = 1 << 13;
 // more.
 constexpr int32_t NARROW_BITS = NARROW_WORDS - 4 * (NARROW_FRONT / 2);
 // Solo SSSP: vertices whose distances fit LDS beside 3,500 frontier entries or
-// more, and entries up to which one compute unit is faster than level steps
-// (us, solo / level steps: 16,384 vertices and 480,000 entries 560 / 500).
+// more, and entries up to which one compute unit is faster than level steps on
+// any graph (us, solo / level steps, 16,383 vertices and about 450,000 entries:
+// R-MAT 631 / 531, Erdos-Renyi 454 / 633).
 constexpr int32_t SOLO_VERTICES = 16384;
 constexpr int32_t SOLO_EDGES = 1 << 18;
+// Entries from which solo SSSP keeps a bound: below, a level takes as long
+// whatever its edges, and the bound's levels are more (us, without / with: 64,000
+// entries 272 / 294, 80,000 207 / 202, 93,000 277 / 243, 104,000 201 / 165).
+constexpr int32_t SOLO_FAR_EDGES = 88 << 10;
 constexpr uint32_t SOLO_WORDS = 34 * 1024;
 constexpr uint32_t SOLO_FRONT = 4096;
 // near-far SSSP: frontier entries, vertices (two bits each in LDS), edges of a
@@ -241,7 +246,7 @@ const void* harvest_kernel_ptr(int problem, bool timed = false);
 const void* init_kernel_ptr(int problem);
 const void* narrow_kernel_ptr(int32_t slots);
 const void* near_kernel_ptr();
-const void* solo_kernel_ptr();
+const void* solo_kernel_ptr(bool far);
 const void* symmetry_kernel_ptr(bool arena);
 const void* bottom_up_kernel_ptr();
 const void* tally_kernel_ptr();

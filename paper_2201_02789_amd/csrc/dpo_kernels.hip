@@ -1913,19 +1913,29 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
 // distances and frontier in LDS.  On such a graph a level step is four kernels
 // of 5 to 25 us whose relaxations meet on a few hubs; here a level is two
 // dependent loads, and then about 1.3 edges a cycle, bound by the compute unit's
-// instructions (about 45 a wave and 64 edges).  8,191 vertices, 204,000 entries:
-// 422 -> 376 us.  Frontier entries past what LDS holds go to the overflow queues
-// and are run in passes.
+// instructions (about 45 a wave and 64 edges).  Frontier entries past what LDS
+// holds go to the overflow queues and are run in passes.
+//
+// FAR: level order relaxes a dense graph's edges two to three times.  A vertex
+// improved to a distance above the bound waits instead, until no vertex below it
+// is left and the bound moves to 1.5 times the least distance that waits; once
+// half of the entries have been run it is lifted, as what is left is many levels
+// of few edges.  8,191 vertices, 204,000 entries, weights up to 255: 14 levels and
+// 2 new bounds instead of 13 levels, a third of the edges; level steps 422 us,
+// level order 356, with the bound 195 (never lifted 227; moved to 1.25 or 2 times
+// the least distance 277 / 272).  16,383 vertices, 245,000 entries 459 -> 261.
+// Equal weights gain nothing and pay for the two bit sets: 131 -> 145.
 struct SoloLds {
   uint32_t words[SOLO_WORDS];
   unsigned long long rows[NARROW_BLOCK / 64][64];  // per wave: {row start, distance} of a window
   __align__(8) uint8_t heads[NARROW_BLOCK / 64][64 * NARROW_U];
   uint32_t wsum[NARROW_BLOCK / 64], wrows[NARROW_BLOCK / 64];
-  uint32_t cnt, bad;
+  uint32_t cnt, bad, low, ran;
 };
 
 // Writes its output and its verdict and needs nothing of the workspace but the
 // overflow queues.
+template <bool FAR>
 __global__ __launch_bounds__(NARROW_BLOCK) void solo_kernel(Args a, uint32_t src, uint32_t ticket,
                                                             uint32_t* verdict) {
   __shared__ SoloLds sh;
@@ -1933,23 +1943,28 @@ __global__ __launch_bounds__(NARROW_BLOCK) void solo_kernel(Args a, uint32_t src
   const uint32_t tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const uint32_t n = (uint32_t)a.n, nbits = (n + 31) / 32;
-  const uint32_t FC = min((uint32_t)SOLO_FRONT, (SOLO_WORDS - nbits - n) / 5);
+  const uint32_t FC = min((uint32_t)SOLO_FRONT, (SOLO_WORDS - (FAR ? 2 : 1) * nbits - n) / 5);
   uint32_t* s_dist = sh.words;
   uint32_t* s_bits = s_dist + n;       // queued for the next level
-  uint32_t* s_front = s_bits + nbits;  // two of FC: this level's, the next one's
+  uint32_t* s_far = s_bits + (FAR ? nbits : 0u);  // waiting for the bound to reach them
+  uint32_t* s_front = s_far + nbits;  // two of FC: this level's, the next one's
   uint32_t* s_start = s_front + 2 * FC;
   uint32_t* s_off = s_front + 3 * FC;
   uint32_t* s_slot = s_front + 4 * FC;
   for (uint32_t i = tid; i < n; i += NB) s_dist[i] = i == src ? 0u : 0xFFFFFFFFu;
-  for (uint32_t i = tid; i < nbits; i += NB) s_bits[i] = 0;
+  for (uint32_t i = tid; i < (FAR ? 2 : 1) * nbits; i += NB) s_bits[i] = 0;
   if (tid == 0) {
     s_front[0] = src;
     sh.bad = 0;
     sh.cnt = 0;
+    sh.low = 0xFFFFFFFFu;
+    sh.ran = 0;
   }
   __syncthreads();
-  uint32_t cur = 0, nxt = FC, F = 1;
-  for (uint32_t L = 0; F != 0 && L <= n; ++L) {
+  uint32_t cur = 0, nxt = FC, F = 1, ran = 0;
+  uint32_t bound = FAR ? 0u : 0xFFFFFFFFu;
+  // (as many levels for a bound's vertices as there are, and one to raise it)
+  for (uint32_t L = 0; F != 0 && L <= (FAR ? 2 * n + 1 : n); ++L) {
     uint32_t* spill_in = (uint32_t*)((L & 1) ? a.front1 : a.front0) + (size_t)NQF * a.fcap;
     uint32_t* spill_out = (uint32_t*)((L & 1) ? a.front0 : a.front1) + (size_t)NQF * a.fcap;
     // appends what a batch found
@@ -2007,7 +2022,9 @@ __global__ __launch_bounds__(NARROW_BLOCK) void solo_kernel(Args a, uint32_t src
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u) {
         const uint32_t bit = 1u << (v[u] & 31);
-        if (nd[u] < x[u]) x[u] = atomicOr(&s_bits[v[u] >> 5], bit) & bit;
+        const bool better = nd[u] < x[u];
+        if (FAR && better && nd[u] > bound) atomicOr(&s_far[v[u] >> 5], bit);
+        if (better && (!FAR || nd[u] <= bound)) x[u] = atomicOr(&s_bits[v[u] >> 5], bit) & bit;
         else x[u] = 1;
       }
       pin(x);
@@ -2043,6 +2060,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void solo_kernel(Args a, uint32_t src
         rows += deg[j] != 0;
         big |= deg[j] > U;
       }
+      ran += sum;
       if (!__syncthreads_or(big)) {
         // one short row per thread, which it runs itself
         if (__any(deg[0] != 0)) {
@@ -2119,6 +2137,53 @@ __global__ __launch_bounds__(NARROW_BLOCK) void solo_kernel(Args a, uint32_t src
       // (with a spilled frontier the next pass or level reads what this one
       // stored globally)
       __syncthreads();
+    }
+    if (FAR && sh.cnt == 0 && bound != 0xFFFFFFFFu) {
+      // The least distance that waits, and the new bound's vertices.  One that
+      // waits below the old bound was improved again and has been queued since.
+      uint32_t low = 0xFFFFFFFFu;
+      for (uint32_t v = tid; v < n; v += NB) {
+        const uint32_t d = s_dist[v];
+        if ((s_far[v >> 5] >> (v & 31) & 1u) && d > bound) low = min(low, d);
+      }
+      if (__any(low != 0xFFFFFFFFu)) {
+#pragma unroll
+        for (int o = 32; o; o >>= 1) low = min(low, (uint32_t)__shfl_xor((int)low, o, 64));
+        if (lane == 0) atomicMin(&sh.low, low);
+      }
+#pragma unroll
+      for (int o = 32; o; o >>= 1) ran += (uint32_t)__shfl_xor((int)ran, o, 64);
+      if (lane == 0) atomicAdd(&sh.ran, ran);
+      ran = 0;
+      lds_barrier();
+      low = sh.low;
+      const uint32_t old = bound;
+      bound = low + low / 2 < low || sh.ran >= (uint32_t)a.m / 2 ? 0xFFFFFFFFu : low + low / 2;
+      if (low != 0xFFFFFFFFu) {
+        for (uint32_t v0 = wave * 64; v0 < n; v0 += NB) {
+          const uint32_t v = v0 + (uint32_t)lane;
+          const bool far = v < n && (s_far[v >> 5] >> (v & 31) & 1u);
+          const uint32_t d = far ? s_dist[v] : 0xFFFFFFFFu;
+          const unsigned long long off = __ballot(far && d <= bound);
+          if (off == 0) continue;
+          const bool take = far && d <= bound && d > old;
+          const unsigned long long m = __ballot(take);
+          const uint32_t half = (uint32_t)(off >> (lane & 32)), mine = (uint32_t)(m >> (lane & 32));
+          if ((lane & 31) == 0 && half) {  // the wave's own words
+            s_far[v >> 5] &= ~half;
+            s_bits[v >> 5] |= mine;
+          }
+          uint32_t base = 0;
+          if (lane == 0 && m) base = atomicAdd(&sh.cnt, (uint32_t)__popcll(m));
+          const uint32_t pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + lane_rank(m);
+          if (take) {
+            if (pos < FC) s_front[nxt + pos] = v;
+            else if (pos < n) spill_out[pos] = v;
+          }
+        }
+      }
+      __syncthreads();
+      if (tid == 0) sh.low = 0xFFFFFFFFu;
     }
     F = sh.cnt;
     const uint32_t t = cur;
@@ -3245,7 +3310,9 @@ const void* narrow_kernel_ptr(int32_t slots) {
 
 const void* near_kernel_ptr() { return (const void*)near_kernel; }
 
-const void* solo_kernel_ptr() { return (const void*)solo_kernel; }
+const void* solo_kernel_ptr(bool far) {
+  return far ? (const void*)solo_kernel<true> : (const void*)solo_kernel<false>;
+}
 
 const void* symmetry_kernel_ptr(bool arena) {
   return arena ? (const void*)symmetry_kernel<true> : (const void*)symmetry_kernel<false>;

@@ -52,6 +52,32 @@ def test_single(name, make, src):
                 assert np.array_equal(dpo.as_uint32(out), want), (name, opts.label())
 
 
+WEIGHTS = {"equal": lambda r, m: np.full(m, 7), "zeros": lambda r, m: r.integers(0, 2, m) * 9,
+           "octets": lambda r, m: r.integers(1, 256, m), "skewed": lambda r, m: 1 << r.integers(0, 28, m),
+           # three edges stay below 2^32 - 1, 1.5 times two do not
+           "heavy": lambda r, m: r.integers(1300000000, 1400000000, m)}
+
+
+@pytest.mark.parametrize("weights", WEIGHTS)
+@pytest.mark.parametrize("leaves,hubs", [(15018, 3), (15019, 3), (8191, 6), (16378, 6), (16377, 7), (5000, 9)])
+def test_bound_moves(leaves, hubs, weights):
+    """Every leaf at every hub: around the entries from which a bound is kept,
+    bounds that let one vertex or all of them through, more than LDS holds."""
+    e = np.stack(np.meshgrid(np.arange(hubs), hubs + np.arange(leaves)), -1).reshape(-1, 2)
+    g = gg.from_edges(hubs + leaves, e)
+    w = WEIGHTS[weights](np.random.default_rng(leaves), g.m).astype(np.uint32)
+    g = gg.Graph(g.row_ptr, g.col_idx, w)  # not the same both ways
+    dg = dpo.DeviceGraph.from_host(g)
+    o = dpo.Options()
+    ws = dpo.alloc_workspace(dg, o)
+    for src in (0, hubs + 1):
+        print(leaves, hubs, weights, src, flush=True)
+        ws.fill_(0xA5)
+        out = torch.full((g.n,), -7, dtype=torch.int32, device="cuda")
+        dpo.dpo_sssp(dg, src, o, out, ws)
+        assert np.array_equal(dpo.as_uint32(out), oracle.dijkstra(g, src)), src
+
+
 def test_batch():
     gs = [gg.rmat(9, 8, 3, perm_seed=4), gg.rmat(13, 16, 5, perm_seed=6), gg.road_like(60, 70, 2),
           gg.star_graph(9000), gg.path_graph(400), gg.from_edges(75, [(1, 2), (2, 3)]),
