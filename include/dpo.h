@@ -133,8 +133,8 @@ typedef struct {
                                BFS without counters also runs wide levels
                                bottom-up (an unvisited vertex looks for a
                                visited neighbour) if it finds the graph
-                               symmetric; in a batch or a serving engine each
-                               query's.  Speed only.                            */
+                               symmetric; in a large batch or a busy serving
+                               engine each query's.  Speed only.                */
 } dpo_options;
 
 typedef enum {
@@ -143,8 +143,8 @@ typedef enum {
                          (the arena for an engine) has at least 8 directed
                          entries per vertex, and then for SSSP batches and for
                          nested, aggregated BFS batches without counters whose
-                         queries have at least as many vertices as the arena;
-                         off for other BFS batches and sparser graphs, where
+                         queries have at least as many vertices as the arena
+                         and about 20 M entries to run; off for other BFS batches and sparser graphs, where
                          many narrow levels would each pay the extra kernel
                          launch                                                */
   DPO_HINT_ON = 1,

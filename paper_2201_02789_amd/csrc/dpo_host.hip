@@ -328,6 +328,14 @@ struct SetRun {
   int32_t* qlist = nullptr;  // device: indices of the queries being admitted
 };
 
+// Queries of `slots` vertices in all, over the graphs of g, go bottom-up by
+// themselves: the check reads all of g (about 8 times as fast per entry as a
+// traversal), and a level step of such queries is three kernels longer
+// (BU_QUERIES_EDGES).
+bool queries_pay(const dpo_csr& g, int64_t slots) {
+  return slots >= g.n && (double)slots / g.n * g.m >= (double)BU_QUERIES_EDGES;
+}
+
 bool dense_graph(const dpo_csr& g) { return g.m >= (int64_t)HINT_AUTO_MIN_DEGREE * g.n; }
 
 // tm: phase-timing rows; non-null selects the timed instantiations of the
@@ -345,15 +353,15 @@ dpo_status prepare_set(Runtime& r, int problem, const dpo_csr* g, const dpo_opti
   sr->lay = lay;
   // Found bytes and the harvest (BFS: with per-XCD copies): single traversals,
   // the serving engine, SSSP batches (64 queries over 16 graphs 856 -> 805 us)
-  // and BFS batches whose queries go bottom-up, on graphs whose average degree is at least HINT_AUTO_MIN_DEGREE, unless the options say
-  // otherwise.  The harvest adds a kernel launch to every level step; a graph of
-  // low average degree runs many narrow levels and rarely a wide one.
+  // and BFS batches whose queries go bottom-up, on graphs whose average degree is
+  // at least HINT_AUTO_MIN_DEGREE, unless the options say otherwise.  The harvest
+  // adds a kernel launch to every level step; a graph of low average degree runs
+  // many narrow levels and rarely a wide one.
   const bool dense = dense_graph(*g);
   const bool bfs = problem == PROB_BFS;
-  // Queries that go bottom-up by themselves: a serving engine, and a batch that
-  // is at least as large as its arena (the symmetry check reads all of it, and
-  // is about 8 times as fast per entry as a traversal).  They use found bytes.
-  const bool by_query = bfs && (batch_call ? slots >= g->n : nq > 1) && gran != AGG_FLAT &&
+  // Queries that go bottom-up by themselves: a batch of enough work, and a serving
+  // engine once enough has been admitted.  They use found bytes.
+  const bool by_query = bfs && (batch_call ? queries_pay(*g, slots) : nq > 1) && gran != AGG_FLAT &&
                         gran != AGG_NONE && !count_stats && !tm;
   const bool hint = o.claim_hint == DPO_HINT_ON ||
                     (o.claim_hint == DPO_HINT_AUTO && (!batch_call || by_query || !bfs) && dense);
@@ -928,6 +936,7 @@ struct dpo_engine {
   int32_t running = 0;
   bool inflight = false;
   hipGraphExec_t exec = nullptr;
+  hipGraphExec_t plain = nullptr;  // BU_QUERIES: the replay before the check
   dpo::Query* hq = nullptr;   // pinned mirror of the device query table
   int32_t* hlist = nullptr;   // pinned
   uint32_t* hflags = nullptr; // pinned
@@ -1051,7 +1060,7 @@ dpo_status engine_enqueue(dpo_engine* e, int32_t& retired) {
     }
     if ((s = admit(sr, e->hq, e->max_queries, e->hlist, count)) != DPO_OK) return s;
     for (int32_t k = 0; k < count; ++k) e->served += e->hq[e->hlist[k]].n;
-    if (sr.a.bottom_up && !e->checked && e->served >= sr.n) {
+    if (sr.a.bottom_up && !e->checked && queries_pay(e->csr, e->served)) {
       // enough work for the check to pay (see prepare_set); the answer holds
       // until the engine is idle
       if ((s = check_symmetry(r, sr, e->vbase.data(), (int32_t)e->vbase.size() - 1)) != DPO_OK)
@@ -1060,7 +1069,10 @@ dpo_status engine_enqueue(dpo_engine* e, int32_t& retired) {
     }
   }
   if (e->running > 0) {
-    if (hipGraphLaunch(e->exec, sr.stream) != hipSuccess) return DPO_ERR_HIP;
+    // (the tallies of a query are zero from its admission until the first replay
+    // that makes them)
+    if (hipGraphLaunch(e->plain && !e->checked ? e->plain : e->exec, sr.stream) != hipSuccess)
+      return DPO_ERR_HIP;
     if (hipMemcpyAsync(e->hq, sr.a.q, (size_t)e->max_queries * sizeof(Query),
                        hipMemcpyDeviceToHost, sr.stream) != hipSuccess)
       return DPO_ERR_HIP;
@@ -1144,6 +1156,12 @@ dpo_status dpo_engine_create(const dpo_arena* arena, int32_t kind, const dpo_opt
     s = get_exec(r, e->sr.parent, e->sr.child, e->sr.third, e->sr.fourth, e->sr.pgrid,
                  e->sr.cgrid, e->sr.tgrid, e->sr.fgrid, e->sr.steps, e->sr.a, e->hflags,
                  &e->exec, false);
+    if (s == DPO_OK && e->sr.a.bottom_up) {
+      Args a = e->sr.a;
+      a.bottom_up = BU_OFF;
+      s = get_exec(r, e->sr.parent, e->sr.child, e->sr.third, e->sr.fourth, e->sr.pgrid,
+                   e->sr.cgrid, e->sr.tgrid, e->sr.fgrid, e->sr.steps, a, e->hflags, &e->plain, false);
+    }
   }
   if (s == DPO_OK) s = start_set(r, e->sr);
   if (s == DPO_OK && e->sr.a.hint) {
@@ -1160,6 +1178,7 @@ dpo_status dpo_engine_create(const dpo_arena* arena, int32_t kind, const dpo_opt
   if (s == DPO_OK && hipStreamSynchronize(e->sr.stream) != hipSuccess) s = DPO_ERR_HIP;
   if (s != DPO_OK) {
     if (e->exec) (void)hipGraphExecDestroy(e->exec);
+    if (e->plain) (void)hipGraphExecDestroy(e->plain);
     if (e->retired) (void)hipEventDestroy(e->retired);
     if (p) (void)hipHostFree(p);
     delete e;
@@ -1208,6 +1227,7 @@ void dpo_engine_destroy(dpo_engine* e) {
   if (!e) return;
   if (e->inflight) (void)hipStreamSynchronize(e->sr.stream);
   if (e->exec) (void)hipGraphExecDestroy(e->exec);
+  if (e->plain) (void)hipGraphExecDestroy(e->plain);
   if (e->retired) (void)hipEventDestroy(e->retired);
   if (e->hflags) (void)hipHostFree(e->hflags);
   delete e;

@@ -94,6 +94,11 @@ enum { AFTER_NONE = 0, AFTER_STEP, AFTER_BOTTOM_UP };
 // 386 / 382 / 382 / 584, a batch of 512 1,860 / 1,824 / 1,903 / 2,085; R-MAT of
 // scale 22 618 / 472 / 472.
 constexpr uint32_t BU_ALPHA = 16;
+// Queries go bottom-up if they have this many entries together.  Measured (us, top-down /
+// bottom-up): batches of 2.4 M entries 228 / 280, 12 M 420 / 465, 19 M 390 / 390 and 449 /
+// 456, 30 M 676 / 602, 50 M 700 / 618; served queries of 13 M 333 / 412, 15 M 365 / 447,
+// 46 M 525 / 484, 57 M 656 / 618, 180 M 1,441 / 847.
+constexpr int64_t BU_QUERIES_EDGES = 20 << 20;
 // Several queries: frontier entries from which a level's edges are tallied, and
 // edges from which a query may go bottom-up (fewer are run top-down in less
 // time than the tally and the bottom-up kernel take).

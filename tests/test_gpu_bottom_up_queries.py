@@ -20,7 +20,7 @@ from paper_2201_02789_amd import dpo  # noqa: E402
 def _graphs(broken):
     """Skewed, uniform, tiny, long and partly isolated graphs; `broken`: one
     directed entry of the third is missing."""
-    gs = [gg.rmat(15, 16, 1, perm_seed=2), gg.rmat(9, 8, 3, perm_seed=4), gg.rmat(14, 30, 5, perm_seed=6),
+    gs = [gg.rmat(16, 16, 1, perm_seed=2), gg.rmat(9, 8, 3, perm_seed=4), gg.rmat(14, 30, 5, perm_seed=6),
           gg.erdos_renyi(20011, 300000, 7), gg.path_graph(260), gg.complete_graph(300),
           gg.from_edges(75, [(1, 2), (2, 3)])]
     if broken:
@@ -37,7 +37,7 @@ def arena(request):
     ar, vbase = gg.pack_arena(gs)
     rng = np.random.default_rng(3)
     qs = []
-    for _ in range(3):
+    for _ in range(9):
         qs += [(k, int(rng.choice(np.flatnonzero(g.degrees())))) for k, g in enumerate(gs)]
     qs += [qs[0], qs[2]]
     return gs, dpo.DeviceArena(ar, vbase), qs, [oracle.bfs(gs[k], s)[0] for k, s in qs]
@@ -98,7 +98,7 @@ def test_an_entry_that_leaves_its_graph_is_reported():
         col = np.insert(col, rp[a + 1], b)
         rp[a + 1:] += 1
     da = dpo.DeviceArena(gg.Graph(rp.astype(np.int32), col.astype(np.int32)), vbase)
-    qs = [(0, u), (1, 5), (0, 7)]
+    qs = [(0, u), (1, 5), (0, 7)] * 20
     opts = dpo.Options()
     tot, _ = dpo.dpo_batch_slots(da, qs)
     out = torch.empty(tot, dtype=torch.int32, device="cuda")
