@@ -167,7 +167,7 @@ struct Runtime {
   std::vector<CachedGraph> graphs;
   uint64_t tick = 0;
   uint32_t* host_flags = nullptr;  // pinned: base, done, error, levels_run; [8]: verdict
-  uint32_t ticket = 0;             // of the last narrow launch (24 bits)
+  uint32_t ticket = 0;             // of the last narrow launch that posted a verdict (24 bits)
   std::mt19937 keys{std::random_device{}()};  // of the symmetry checks
   unsigned long long* host_stats = nullptr;  // pinned: MAX_GRID * NSTAT
   Query* host_q = nullptr;                   // pinned: MAX_QUERIES query records
@@ -611,6 +611,22 @@ bool any_kernel(const dpo_options& o, bool stats, bool timed) {
   return o.mode == DPO_MODE_NESTED && o.agg != DPO_AGG_NONE && !stats && !timed;
 }
 
+// Ticket of the next narrow launch that posts to `verdict`, which holds no
+// other's from here on.  Never 0: the solo and near-far kernels post to the same
+// word under ticket 0, and 0 is what the word is cleared to.
+uint32_t next_ticket(Runtime& r, uint32_t* verdict) {
+  r.ticket = r.ticket % 0xFFFFFFu + 1;
+  __atomic_store_n(verdict, 0u, __ATOMIC_RELAXED);
+  return r.ticket;
+}
+
+// Result of a solo or near-far launch that has ended, from its verdict.
+dpo_status ended(uint32_t verdict) {
+  const uint32_t code = verdict & 15u;
+  if (code == V_DONE) return DPO_OK;
+  return code == V_ERROR ? (dpo_status)(-(int32_t)((verdict >> 4) & 15u)) : DPO_ERR_HIP;
+}
+
 // SSSP on a small graph.
 dpo_status launch_solo(SetRun& sr, int32_t source, uint32_t* verdict) {
   uint32_t src = (uint32_t)source, ticket = 0;
@@ -663,11 +679,11 @@ dpo_status copy_verdict(SetRun& sr, uint32_t* out) {
 dpo_status run_narrow_and_wide(Runtime& r, SetRun& sr, int64_t max_levels, uint32_t* verdict) {
   uint32_t after = AFTER_NONE;
   for (int64_t rep = 0; rep < max_levels + 2; ++rep) {
-    r.ticket = (r.ticket + 1) & 0xFFFFFFu;
-    dpo_status s = launch_narrow(sr, after, r.ticket, verdict);
+    const uint32_t ticket = verdict ? next_ticket(r, verdict) : 0u;
+    dpo_status s = launch_narrow(sr, after, ticket, verdict);
     uint32_t v = 0;
     if (s == DPO_OK)
-      s = verdict ? wait_verdict(verdict, r.ticket, sr.stream, &v) : copy_verdict(sr, &v);
+      s = verdict ? wait_verdict(verdict, ticket, sr.stream, &v) : copy_verdict(sr, &v);
     if (s != DPO_OK) return s;
     const uint32_t code = v & 15u;
     if (code == V_DONE || code == V_ERROR) {
@@ -734,22 +750,23 @@ dpo_status traverse(int problem, const dpo_csr* g, int32_t source, const dpo_opt
   const bool narrow = any && problem == PROB_BFS;
   if (any && problem == PROB_SSSP && g->n <= SOLO_VERTICES && g->m <= SOLO_EDGES) {
     uint32_t* verdict = r.host_flags + 8;
+    *verdict = 0;
     if ((s = launch_solo(sr, source, verdict)) != DPO_OK) return s;
     if (hipStreamSynchronize(sr.stream) != hipSuccess) return DPO_ERR_HIP;
-    return (dpo_status)(-(int32_t)((*verdict >> 4) & 15u));
+    return ended(*verdict);
   }
   sr.a.bottom_up = narrow && sr.a.hint ? BU_SINGLE : BU_OFF;
   s = start_single(r, sr, Query{0, g->n, 0, 0, o->threshold, o->coarsen, 0, source});
   if (s != DPO_OK) return s;
   if (any && problem == PROB_SSSP && g->n <= NEAR_VERTICES && !dense_graph(*g)) {
     uint32_t* verdict = r.host_flags + 8;
+    *verdict = 0;
     uint32_t src = (uint32_t)source;
     void* p[] = {&sr.a, &src, &verdict};
     if (hipLaunchKernel(near_kernel_ptr(), dim3(1), dim3(NARROW_BLOCK), p, 0, sr.stream) != hipSuccess ||
         hipStreamSynchronize(sr.stream) != hipSuccess)
       return DPO_ERR_HIP;
-    const uint32_t code = *verdict & 15u;
-    if (code != V_TOP_DOWN) return code == V_DONE ? DPO_OK : (dpo_status)(-(int32_t)((*verdict >> 4) & 15u));
+    if ((*verdict & 15u) != V_TOP_DOWN) return ended(*verdict);
   }
   s = narrow ? run_narrow_and_wide(r, sr, g->n, r.host_flags + 8) : run_to_completion(r, sr, g->n);
   return s != DPO_OK ? s : read_stats(r, sr, st);

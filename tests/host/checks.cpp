@@ -1,0 +1,119 @@
+// The host driver with its kernels replaced by what a test makes them do
+// (hip/hip_runtime.h beside this file).  One check per command-line argument.
+#include "dpo_host.hip"
+
+#include <cstdio>
+
+namespace dpo {
+const void* parent_kernel_ptr(int, int, bool) { return fake::kernel("parent"); }
+const void* child_kernel_ptr(int, bool, bool) { return fake::kernel("child"); }
+const void* serial_kernel_ptr(int p, int g, bool) {
+  return p == PROB_BFS || g == AGG_FLAT ? nullptr : fake::kernel("serial");
+}
+const void* harvest_kernel_ptr(int, bool) { return fake::kernel("harvest"); }
+const void* init_kernel_ptr(int) { return fake::kernel("init"); }
+const void* narrow_kernel_ptr(int32_t) { return fake::kernel("narrow"); }
+const void* near_kernel_ptr() { return fake::kernel("near"); }
+const void* solo_kernel_ptr(bool) { return fake::kernel("solo"); }
+const void* symmetry_kernel_ptr(bool) { return fake::kernel("symmetry"); }
+const void* bottom_up_kernel_ptr() { return fake::kernel("bottom_up"); }
+const void* tally_kernel_ptr() { return fake::kernel("tally"); }
+const void* bottom_up_words_kernel_ptr() { return fake::kernel("words"); }
+const void* bottom_up_queries_kernel_ptr() { return fake::kernel("bottom_up_queries"); }
+const void* settle_symmetry_kernel_ptr() { return fake::kernel("settle"); }
+const void* start_kernel_ptr(int) { return fake::kernel("start"); }
+const void* admit_kernel_ptr(int) { return fake::kernel("admit"); }
+const void* admit_sources_kernel_ptr() { return fake::kernel("admit_sources"); }
+const void* retire_kernel_ptr() { return fake::kernel("retire"); }
+const void* clear_found_kernel_ptr() { return fake::kernel("clear_found"); }
+const void* advance_kernel_ptr() { return fake::kernel("advance"); }
+}  // namespace dpo
+
+using namespace dpo;
+
+static int failures = 0;
+#define CHECK(x) \
+  do { \
+    if (!(x)) { \
+      printf("%s:%d: %s\n", __FILE__, __LINE__, #x); \
+      ++failures; \
+    } \
+  } while (0)
+
+static fake::Runtime& F = fake::rt();
+
+// A narrow kernel that posts the given verdicts one after the other.
+static void post_in_turn(std::vector<uint32_t> codes) {
+  auto left = std::make_shared<std::deque<uint32_t>>(codes.begin(), codes.end());
+  F.kernels["narrow"] = [left](void** p) -> std::function<void()> {
+    const uint32_t ticket = *(uint32_t*)p[2];
+    uint32_t* verdict = *(uint32_t**)p[3];
+    State* st = ((Args*)p[0])->st;
+    return [=] {
+      const uint32_t code = left->front();
+      left->pop_front();
+      st->plan = code;
+      st->done = code == V_DONE;
+      if (verdict) *verdict = ticket << 8 | code;
+    };
+  };
+}
+
+struct Single {
+  std::vector<int32_t> rp, col;
+  std::vector<uint32_t> w, out;
+  std::vector<char> ws;
+  dpo_options o;
+  dpo_csr g;
+  Single(int32_t n, int32_t m) : rp(n + 1), col(m), w(m, 1), out(n) {
+    dpo_default_options(&o);
+    g = dpo_csr{n, m, rp.data(), col.data(), w.data()};
+    ws.resize(dpo_workspace_bytes(&g, &o));
+  }
+  dpo_status bfs() {
+    return dpo_bfs(&g, 0, &o, (int32_t*)out.data(), ws.data(), ws.size(), nullptr, nullptr);
+  }
+  dpo_status sssp() { return dpo_sssp(&g, 0, &o, out.data(), ws.data(), ws.size(), nullptr, nullptr); }
+};
+
+// The verdict of a solo (near-far) SSSP stays in the word the narrow kernel's
+// verdicts are polled in; no later traversal may take it for its own, whatever
+// the launch ticket has come to.
+static void stale_verdict(const char* kernel, int32_t n, int32_t m) {
+  Single s(n, m);
+  F.kernels[kernel] = [=](void** p) -> std::function<void()> {
+    uint32_t* verdict = *(uint32_t**)p[strcmp(kernel, "near") ? 3 : 2];
+    return [=] { *verdict = V_DONE; };
+  };
+  CHECK(s.sssp() == DPO_OK);
+  CHECK(F.launched[kernel] == 1);
+  rt().ticket = 0xFFFFFF;
+  post_in_turn({V_TOP_DOWN, V_DONE});
+  CHECK(s.bfs() == DPO_OK);
+  CHECK(F.launched["narrow"] == 2);
+  CHECK(F.launched["parent"] == 1);
+}
+
+// Launches that post nothing leave a verdict behind whose ticket comes round.
+static void stale_verdict_unposted() {
+  Single s(100, 10);
+  post_in_turn({V_DONE});
+  CHECK(s.bfs() == DPO_OK);  // posts ticket t
+  const uint32_t t = rt().ticket;
+  post_in_turn({V_DONE});
+  CHECK(dpo_bfs_noalloc(&s.g, 0, &s.o, (int32_t*)s.out.data(), nullptr) == DPO_OK);
+  rt().ticket = t - 1;  // as 2^24 - 2 more of them would
+  post_in_turn({V_TOP_DOWN, V_DONE});
+  CHECK(s.bfs() == DPO_OK);
+  CHECK(F.launched["parent"] == 1);
+}
+
+int main(int argc, char** argv) {
+  const std::string name = argc > 1 ? argv[1] : "";
+  if (name == "stale_solo") stale_verdict("solo", 100, 200);
+  else if (name == "stale_near") stale_verdict("near", 20000, 40000);
+  else if (name == "stale_unposted") stale_verdict_unposted();
+  else { printf("no check %s\n", name.c_str()); return 2; }
+  if (!failures) printf("ok\n");
+  return failures != 0;
+}
