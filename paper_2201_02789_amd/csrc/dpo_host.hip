@@ -19,6 +19,7 @@
 // graph serves every call with the same arguments; graphs are cached by their
 // exact kernel arguments.
 #include <hip/hip_runtime.h>
+#include <sys/random.h>
 
 #include <algorithm>
 #include <chrono>
@@ -27,11 +28,11 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
-#include <random>
 #include <vector>
 
 #include "dpo.h"
 #include "dpo_internal.h"
+#include "dpo_pair.h"
 
 namespace dpo {
 namespace {
@@ -168,7 +169,7 @@ struct Runtime {
   uint64_t tick = 0;
   uint32_t* host_flags = nullptr;  // pinned: base, done, error, levels_run; [8]: verdict
   uint32_t ticket = 0;             // of the last narrow launch that posted a verdict (24 bits)
-  std::mt19937 keys{std::random_device{}()};  // of the symmetry checks
+  uint64_t drawn = 0;              // keys drawn without the system's help (draw_key)
   unsigned long long* host_stats = nullptr;  // pinned: MAX_GRID * NSTAT
   Query* host_q = nullptr;                   // pinned: MAX_QUERIES query records
   int32_t* host_list = nullptr;              // pinned: MAX_QUERIES query indices + prefix
@@ -507,12 +508,26 @@ dpo_status start_set(Runtime& r, SetRun& sr) {
   return DPO_OK;
 }
 
+// A key that nothing about the graph can have to do with: the system's random
+// bytes, or, should it have none to give, the clock and a counter.
+PairKey draw_key(Runtime& r) {
+  PairKey key;
+  if (getrandom(&key, sizeof(key), 0) == (ssize_t)sizeof(key)) return key;
+  uint64_t x = (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() + (uint64_t)(uintptr_t)&r;
+  for (uint32_t& k : key.k) {
+    x = (x + ++r.drawn) * 0x9E3779B97F4A7C15ull;
+    x ^= x >> 29;
+    k = (uint32_t)(x >> 32);
+  }
+  return key;
+}
+
 // Symmetry check of the graph; vbase, ngraphs: of the graphs of an arena (device).
 dpo_status launch_symmetry(Runtime& r, SetRun& sr, const uint32_t* vbase = nullptr,
                            uint32_t ngraphs = 0) {
   uint32_t n = (uint32_t)sr.n;
-  uint32_t key[4] = {(uint32_t)r.keys(), (uint32_t)r.keys(), (uint32_t)r.keys(), (uint32_t)r.keys()};
-  void* p[] = {&sr.a, &n, key, &vbase, &ngraphs};
+  PairKey key = draw_key(r);
+  void* p[] = {&sr.a, &n, &key, &vbase, &ngraphs};
   const int64_t grid = std::min<int64_t>(cdiv(sr.a.m, (int64_t)NW * SYM_EDGES), 8 * (int64_t)r.cu_count);
   return hip_ok(hipLaunchKernel(symmetry_kernel_ptr(vbase != nullptr), dim3((unsigned)std::max<int64_t>(grid, 1)),
                                 dim3(PB), p, 0, sr.stream));

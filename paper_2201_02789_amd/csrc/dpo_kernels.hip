@@ -71,6 +71,7 @@
 #include <stdint.h>
 
 #include "dpo_internal.h"
+#include "dpo_pair.h"
 
 namespace dpo {
 
@@ -2484,36 +2485,19 @@ __global__ __launch_bounds__(NARROW_BLOCK) void near_kernel(Args a, uint32_t src
 // level looks for a parent of v along v's own row, which finds the edges into v
 // only then.  Nothing promises it, so the first level that would go bottom-up
 // is preceded by this pass over the adjacency: the sum over all entries of
-// h(u, v) where u < v and -h(v, u) where u > v, h a keyed mix, is zero modulo
-// 2^64 if the graph is symmetric, and otherwise as good as never (2^-62 for a
-// mix without structure; 2^-62 * k where k divides every surplus).  The key is
-// drawn anew for each call.  An id out of range counts as asymmetric.
+// h(u, v) where u < v and -h(v, u) where u > v, h a keyed mix (add_pair), is zero
+// modulo 2^64 if the graph is symmetric, and otherwise for few keys: for none if
+// one entry lacks its reverse, for some 2^-46 of them or fewer for the worst small
+// sets that were looked for.  The key is drawn anew for each check.  An id out of
+// range counts as asymmetric.
 //
-// The mix is two 32 x 32 bit products, the second of the first's keyed halves:
-// it is not linear in either id and takes two quarter-rate instructions (two
-// 64-bit products take six).  Bound by its instructions and the adjacency
-// stream together: scale 22, 513 MB in 145 us, 3.5 TB/s.
-struct PairKey {
-  uint32_t k[4];
-};
-
-// +-h of the entry (u, v), added to sum; nothing for a loop
-__device__ __forceinline__ long long add_pair(long long sum, uint32_t u, uint32_t v,
-                                              const PairKey& key) {
-  const uint64_t x = (uint64_t)(min(u, v) + key.k[0]) * (max(u, v) ^ key.k[1]);
-  int32_t a = (int32_t)(((uint32_t)x ^ key.k[2]) >> 1);
-  a = u > v ? -a : a;
-  a = u == v ? 0 : a;
-  return sum + (long long)a * (int32_t)((uint32_t)(x >> 32) ^ key.k[3]);
-}
-
 // A wave runs an even share of the entries in slices of 64 * U, the next slice's
 // loads issued before a slice is summed; the rows come in windows of 64.
 // ARENA: `vbase` holds the first vertex of each of `ngraphs` graphs (and n after
 // them), and an entry that leaves its row's graph counts as asymmetric too: a
 // bottom-up level might pass it by, where a top-down one reports it.
 template <bool ARENA>
-__global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, PairKey key,
+__global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, const PairKey key,
                                                       const uint32_t* vbase, uint32_t ngraphs) {
   constexpr uint32_t U = NARROW_U;
   __shared__ uint32_t s_row[NW][64];
@@ -2527,7 +2511,7 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, PairKe
   const uint32_t nw = gridDim.x * NW, gw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * NW + wave));
   uint32_t x0 = (uint32_t)((uint64_t)gw * m / nw);
   const uint32_t x1 = (uint32_t)((uint64_t)(gw + 1) * m / nw);
-  long long sum = 0;
+  unsigned long long sum = 0;
   if (x0 < x1) {
     uint32_t r = wave_upper_search(n, x0, lane, [&](uint32_t p) { return (uint32_t)a.rp[p]; });
     r = (uint32_t)__builtin_amdgcn_readfirstlane((int)r);
@@ -2601,7 +2585,7 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, PairKe
               const bool in = whole || x0 + u * 64u + (uint32_t)lane - lo < hi - lo;
               if (!in) w = v[u];
               if (ARENA && !one) leaves |= in && v[u] - s_lo[wave][k] >= s_n[wave][k];
-              sum = add_pair(sum, w, v[u], key);
+              sum = add_pair(sum, w, v[u], key.k);
             }
             wave_lds_sync();
           } else {  // within one row
@@ -2610,7 +2594,7 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, PairKe
             for (uint32_t u = 0; u < U; ++u) {
               const bool in = whole || x0 + u * 64u + (uint32_t)lane - lo < hi - lo;
               if (ARENA && !one) leaves |= in && v[u] - s_lo[wave][first] >= s_n[wave][first];
-              sum = add_pair(sum, in ? row : v[u], v[u], key);
+              sum = add_pair(sum, in ? row : v[u], v[u], key.k);
             }
           }
           if (ARENA && one) {  // the usual case, without the lookups
@@ -2639,7 +2623,7 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, PairKe
   }
 #pragma unroll
   for (int d = 32; d; d >>= 1) sum += __shfl_down(sum, d, 64);
-  if (lane == 0) s_sum[wave] = (unsigned long long)sum;
+  if (lane == 0) s_sum[wave] = sum;
   __syncthreads();
   if (tid == 0) {
     unsigned long long all = 0;
