@@ -964,6 +964,7 @@ struct dpo_engine {
   std::vector<int32_t> free_q;
   std::deque<dpo::Pending> pending;
   std::deque<uint64_t> completed;
+  std::vector<uint64_t> landing;  // tickets whose results are being copied
   uint64_t next_ticket = 1;
   int32_t running = 0;
   bool inflight = false;
@@ -973,7 +974,7 @@ struct dpo_engine {
   int32_t* hlist = nullptr;   // pinned
   uint32_t* hflags = nullptr; // pinned
   uint4* hretire = nullptr;   // pinned: queries being retired, then their workgroup prefix
-  std::vector<int32_t> hretire_pre;
+  std::vector<int32_t> hretire_pre, hretire_q;
   hipEvent_t retired = nullptr;
   int64_t max_n = 0;
   int64_t served = 0;  // vertices of the queries admitted since the engine was last idle
@@ -1030,34 +1031,42 @@ dpo_status launch_retire(dpo_engine* e, int32_t count, int32_t groups) {
   return hip_ok(hipEventRecord(e->retired, sr.stream));
 }
 
-// Retires, admits and launches; retired: queries whose results launch_retire
-// copies.
-dpo_status engine_enqueue(dpo_engine* e, int32_t& retired) {
+// Retires, admits and launches.
+dpo_status engine_enqueue(dpo_engine* e) {
   Runtime& r = rt();
   SetRun& sr = e->sr;
   dpo_status s = DPO_OK;
   if (e->inflight) {
     if (hipStreamSynchronize(sr.stream) != hipSuccess) return DPO_ERR_HIP;
-    e->inflight = false;
-    if (e->hflags[2] != 0) return (dpo_status)(-(int32_t)e->hflags[2]);
+    if (e->hflags[2] != 0) {
+      e->inflight = false;
+      return (dpo_status)(-(int32_t)e->hflags[2]);
+    }
     // queries without frontier entries at the last level run have finished
     const int32_t last_level = (int32_t)e->hflags[0] - 1;
     const bool all_done = e->hflags[1] != 0;
     int64_t groups = 0;
+    int32_t retired = 0;
     for (int32_t q = 0; q < e->max_queries; ++q) {
-      Running& ru = e->run[q];
+      const Running& ru = e->run[q];
       if (!ru.used || !(all_done || e->hq[q].last < last_level)) continue;
       const uint64_t out = (uint64_t)ru.out;
       e->hretire[retired] = uint4{(uint32_t)out, (uint32_t)(out >> 32), (uint32_t)ru.slot0, (uint32_t)ru.n};
+      e->hretire_q[retired] = q;
       e->hretire_pre[retired++] = (int32_t)groups;
       groups += cdiv(ru.n, ADMIT_CHUNK);
+    }
+    // (should it fail, they stay as they are and the next step tries again)
+    if (retired && (s = launch_retire(e, retired, (int32_t)groups)) != DPO_OK) return s;
+    e->inflight = false;
+    for (int32_t k = 0; k < retired; ++k) {
+      Running& ru = e->run[e->hretire_q[k]];
       slots_free(e, ru.slot0, ru.footprint);
-      e->completed.push_back(ru.ticket);
+      e->landing.push_back(ru.ticket);
       ru = Running{};
-      e->free_q.push_back(q);
+      e->free_q.push_back(e->hretire_q[k]);
       --e->running;
     }
-    if (retired && (s = launch_retire(e, retired, (int32_t)groups)) != DPO_OK) return s;
   }
   // admit in arrival order while a table entry and the footprint fit
   int32_t count = 0;
@@ -1114,11 +1123,14 @@ dpo_status engine_enqueue(dpo_engine* e, int32_t& retired) {
 }
 
 dpo_status engine_step(dpo_engine* e) {
-  int32_t retired = 0;
-  const dpo_status s = engine_enqueue(e, retired);
+  const dpo_status s = engine_enqueue(e);
   // the retired queries' results are with their callers before dpo_engine_poll
   // can report them; admission and the next replay were enqueued behind them
-  if (retired && hipEventSynchronize(e->retired) != hipSuccess) return DPO_ERR_HIP;
+  if (!e->landing.empty()) {
+    if (hipEventSynchronize(e->retired) != hipSuccess) return DPO_ERR_HIP;
+    e->completed.insert(e->completed.end(), e->landing.begin(), e->landing.end());
+    e->landing.clear();
+  }
   return s;
 }
 
@@ -1169,6 +1181,9 @@ dpo_status dpo_engine_create(const dpo_arena* arena, int32_t kind, const dpo_opt
   e->out_arena = (char*)out_arena;
   e->free_slots[0] = max_slots;
   e->run.assign(max_queries, Running{});
+  e->hretire_pre.resize(max_queries);
+  e->hretire_q.resize(max_queries);
+  e->landing.reserve(max_queries);
   for (int32_t q = max_queries - 1; q >= 0; --q) e->free_q.push_back(q);
   s = prepare_set(r, problem, &e->csr, bucket_opts[0], max_slots, max_queries, out_arena, ws,
                   ws_bytes, stream, false, &e->sr);
@@ -1181,7 +1196,6 @@ dpo_status dpo_engine_create(const dpo_arena* arena, int32_t kind, const dpo_opt
   if (s == DPO_OK) {
     e->hflags = (uint32_t*)p;
     e->hretire = (uint4*)((char*)p + 64);
-    e->hretire_pre.resize(max_queries);
     e->hq = (Query*)((char*)e->hretire + (size_t)max_queries * 20);
     e->hlist = (int32_t*)(e->hq + max_queries);
     std::memset(e->hq, 0, (size_t)max_queries * sizeof(Query));

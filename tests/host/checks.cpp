@@ -108,11 +108,83 @@ static void stale_verdict_unposted() {
   CHECK(F.launched["parent"] == 1);
 }
 
+// An engine over graphs of the given sizes whose replays end every query.
+struct Served {
+  std::vector<int32_t> vbase, rp, col;
+  std::vector<uint32_t> w;
+  std::vector<char> ws, out_arena;
+  std::vector<std::vector<uint32_t>> outs;
+  dpo_options o;
+  dpo_arena ar;
+  dpo_engine* e = nullptr;
+  Served(std::vector<int32_t> sizes, int32_t m, int kind, int64_t slots = 1 << 16) : vbase{0}, col(m), w(m, 1) {
+    for (int32_t n : sizes) vbase.push_back(vbase.back() + n);
+    rp.resize(vbase.back() + 1);
+    dpo_default_options(&o);
+    o.steps_per_replay = 2;
+    ar = dpo_arena{(int32_t)sizes.size(), vbase.data(), {vbase.back(), m, rp.data(), col.data(), w.data()}};
+    ws.resize(dpo_engine_workspace_bytes(&o, 64, slots));
+    out_arena.resize(slots * 4);
+    for (int64_t i = 0; i < slots; ++i) ((uint32_t*)out_arena.data())[i] = (uint32_t)i + 1000;
+    F.kernels["advance"] = [](void** p) -> std::function<void()> {
+      uint32_t* flags = *(uint32_t**)p[2];
+      return [=] {
+        flags[0] += 2;
+        flags[1] = 1;
+      };
+    };
+    F.kernels["retire"] = [](void** p) -> std::function<void()> {
+      const uint32_t* from = *(const uint32_t**)p[0];
+      const uint4* list = *(const uint4**)p[1];
+      const int32_t count = *(int32_t*)p[3];
+      return [=] {
+        for (int32_t k = 0; k < count; ++k)
+          memcpy((void*)((uint64_t)list[k].y << 32 | list[k].x), from + list[k].z, (size_t)list[k].w * 4);
+      };
+    };
+    CHECK(dpo_engine_create(&ar, kind, &o, 1, nullptr, 64, slots, ws.data(), ws.size(), out_arena.data(), nullptr,
+                            &e) == DPO_OK);
+  }
+  uint64_t submit(int32_t graph) {
+    outs.emplace_back(vbase[graph + 1] - vbase[graph], 7u);
+    uint64_t t = 0;
+    CHECK(dpo_engine_submit(e, graph, 0, outs.back().data(), &t) == DPO_OK);
+    return t;
+  }
+  std::vector<uint64_t> poll() {
+    uint64_t t[64];
+    const int32_t k = dpo_engine_poll(e, t, 64);
+    return std::vector<uint64_t>(t, t + k);
+  }
+  ~Served() { dpo_engine_destroy(e); }
+};
+
+// A step whose copy of finished results fails reports no ticket; the results are
+// copied by the next step that can.
+static void failed_copy() {
+  Served s({40, 100}, 300, 1);
+  s.outs.reserve(8);
+  s.submit(0);
+  s.submit(1);
+  int32_t running = 0, pending = 0;
+  CHECK(dpo_engine_step(s.e, &running, &pending) == DPO_OK && running == 2);
+  F.fail_launch = "retire";
+  CHECK(dpo_engine_step(s.e, &running, &pending) == DPO_ERR_HIP);
+  CHECK(s.poll().empty());
+  CHECK(running == 2);
+  F.fail_launch = "";
+  CHECK(dpo_engine_step(s.e, &running, &pending) == DPO_OK && running == 0);
+  CHECK(s.poll().size() == 2);
+  for (auto& out : s.outs)
+    for (size_t i = 0; i < out.size(); ++i) CHECK(out[i] == out[0] + i && out[i] >= 1000);
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "stale_solo") stale_verdict("solo", 100, 200);
   else if (name == "stale_near") stale_verdict("near", 20000, 40000);
   else if (name == "stale_unposted") stale_verdict_unposted();
+  else if (name == "failed_copy") failed_copy();
   else { printf("no check %s\n", name.c_str()); return 2; }
   if (!failures) printf("ok\n");
   return failures != 0;

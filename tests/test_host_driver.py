@@ -30,3 +30,7 @@ def test_a_verdict_left_behind_is_nobody_elses(checks, name):
     """A BFS whose launch ticket equals that of a verdict left in the polled
     word waits for its own."""
     _run(checks, name)
+
+
+def test_a_failed_copy_of_results_reports_no_ticket(checks):
+    _run(checks, "failed_copy")
