@@ -935,12 +935,14 @@ struct Pending {
   uint64_t ticket;
   int32_t graph, source;
   void* out;
+  bool copied;  // its result goes to `out` by a copy command
 };
 
 struct Running {
   bool used = false;
   uint64_t ticket = 0;
   void* out = nullptr;
+  bool copied = false;
   int32_t n = 0;
   int64_t slot0 = 0;
   int64_t footprint = 0;
@@ -976,7 +978,7 @@ struct dpo_engine {
   uint4* hretire = nullptr;   // pinned: queries being retired, then their workgroup prefix
   std::vector<int32_t> hretire_pre, hretire_q;
   hipEvent_t retired = nullptr;
-  int64_t max_n = 0;
+  int device = 0;
   int64_t served = 0;  // vertices of the queries admitted since the engine was last idle
   bool checked = false;  // the arena's symmetry, since then
 };
@@ -1014,9 +1016,22 @@ void slots_free(dpo_engine* e, int64_t start, int64_t len) {
   }
 }
 
-// Copies the results of the queries in e->hretire to their callers; the event
-// marks the end of it.  The list goes where the level steps put their records
-// (a query has at least 32 slots, of 16 bytes each there).
+// May retire_kernel store to `out`?  Words of the engine's device's memory;
+// results for anything else (another device's memory, the host's) go by a copy
+// command each, which takes any address.
+bool storable(const dpo_engine* e, const void* out) {
+  if ((uintptr_t)out % 4 != 0) return false;
+  hipPointerAttribute_t at{};
+  if (hipPointerGetAttributes(&at, out) != hipSuccess) {
+    (void)hipGetLastError();  // not an error of the caller's
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == e->device;
+}
+
+// Copies the results of the queries in e->hretire to their callers.  The list
+// goes where the level steps put their records (a query has at least 32 slots,
+// of 16 bytes each there).
 dpo_status launch_retire(dpo_engine* e, int32_t count, int32_t groups) {
   SetRun& sr = e->sr;
   uint4* list = (uint4*)sr.a.rec;
@@ -1026,9 +1041,7 @@ dpo_status launch_retire(dpo_engine* e, int32_t count, int32_t groups) {
     return DPO_ERR_HIP;
   const char* slots = e->out_arena;
   void* p[] = {&slots, &list, &pre, &count};
-  if (hipLaunchKernel(retire_kernel_ptr(), dim3((unsigned)groups), dim3(PB), p, 0, sr.stream) != hipSuccess)
-    return DPO_ERR_HIP;
-  return hip_ok(hipEventRecord(e->retired, sr.stream));
+  return hip_ok(hipLaunchKernel(retire_kernel_ptr(), dim3((unsigned)groups), dim3(PB), p, 0, sr.stream));
 }
 
 // Retires, admits and launches.
@@ -1046,18 +1059,25 @@ dpo_status engine_enqueue(dpo_engine* e) {
     const int32_t last_level = (int32_t)e->hflags[0] - 1;
     const bool all_done = e->hflags[1] != 0;
     int64_t groups = 0;
-    int32_t retired = 0;
+    int32_t retired = 0, listed = 0;
     for (int32_t q = 0; q < e->max_queries; ++q) {
       const Running& ru = e->run[q];
       if (!ru.used || !(all_done || e->hq[q].last < last_level)) continue;
+      e->hretire_q[retired++] = q;
+      // (should a copy fail, all stay as they are and the next step tries again)
+      if (ru.copied) {
+        if (hipMemcpyAsync(ru.out, e->out_arena + ru.slot0 * 4, (size_t)ru.n * 4, hipMemcpyDeviceToDevice,
+                           sr.stream) != hipSuccess)
+          return DPO_ERR_HIP;
+        continue;
+      }
       const uint64_t out = (uint64_t)ru.out;
-      e->hretire[retired] = uint4{(uint32_t)out, (uint32_t)(out >> 32), (uint32_t)ru.slot0, (uint32_t)ru.n};
-      e->hretire_q[retired] = q;
-      e->hretire_pre[retired++] = (int32_t)groups;
+      e->hretire[listed] = uint4{(uint32_t)out, (uint32_t)(out >> 32), (uint32_t)ru.slot0, (uint32_t)ru.n};
+      e->hretire_pre[listed++] = (int32_t)groups;
       groups += cdiv(ru.n, ADMIT_CHUNK);
     }
-    // (should it fail, they stay as they are and the next step tries again)
-    if (retired && (s = launch_retire(e, retired, (int32_t)groups)) != DPO_OK) return s;
+    if (listed && (s = launch_retire(e, listed, (int32_t)groups)) != DPO_OK) return s;
+    if (retired && hipEventRecord(e->retired, sr.stream) != hipSuccess) return DPO_ERR_HIP;
     e->inflight = false;
     for (int32_t k = 0; k < retired; ++k) {
       Running& ru = e->run[e->hretire_q[k]];
@@ -1085,6 +1105,7 @@ dpo_status engine_enqueue(dpo_engine* e) {
     ru.used = true;
     ru.ticket = p.ticket;
     ru.out = p.out;
+    ru.copied = p.copied;
     ru.n = n;
     ru.slot0 = slot0;
     ru.footprint = round32(n);
@@ -1171,6 +1192,7 @@ dpo_status dpo_engine_create(const dpo_arena* arena, int32_t kind, const dpo_opt
   if ((s = ensure_runtime(r)) != DPO_OK) return s;
   dpo_engine* e = new dpo_engine();
   e->problem = problem;
+  (void)hipGetDevice(&e->device);
   e->csr = arena->csr;
   e->vbase.assign(arena->graph_vbase, arena->graph_vbase + arena->ngraphs + 1);
   e->bopts.assign(bucket_opts, bucket_opts + nbuckets);
@@ -1241,7 +1263,7 @@ dpo_status dpo_engine_submit(dpo_engine* e, int32_t graph, int32_t source, void*
   if (source < 0 || source >= n) return DPO_ERR_SOURCE;
   if (dpo::round32(n) > e->max_slots) return DPO_ERR_CAPACITY;
   const uint64_t t = e->next_ticket++;
-  e->pending.push_back(dpo::Pending{t, graph, source, out});
+  e->pending.push_back(dpo::Pending{t, graph, source, out, !dpo::storable(e, out)});
   if (ticket) *ticket = t;
   return DPO_OK;
 }

@@ -179,12 +179,43 @@ static void failed_copy() {
     for (size_t i = 0; i < out.size(); ++i) CHECK(out[i] == out[0] + i && out[i] >= 1000);
 }
 
+// Results whose array a kernel on the engine's device may not store to (another
+// device's, the host's, not at a word's boundary) are copied, beside those that
+// the kernel stores.
+static void foreign_outputs() {
+  Served s({40, 100, 33, 70, 64}, 300, 0);
+  std::vector<uint32_t> far(40, 7u), host(100, 7u), own(64, 7u), managed(70, 7u);
+  std::vector<char> odd(33 * 4 + 1, 7);
+  F.attributes[far.data()] = {hipMemoryTypeDevice, 1};
+  F.attributes[host.data()] = {hipMemoryTypeHost, 0};
+  F.attributes[managed.data()] = {hipMemoryTypeManaged, 0};
+  void* outs[5] = {far.data(), host.data(), odd.data() + 1, managed.data(), own.data()};
+  for (int k = 0; k < 5; ++k) {
+    uint64_t t;
+    CHECK(dpo_engine_submit(s.e, k, 0, outs[k], &t) == DPO_OK);
+  }
+  for (int i = 0; i < 2; ++i) CHECK(dpo_engine_step(s.e, nullptr, nullptr) == DPO_OK);
+  CHECK(s.poll().size() == 5);
+  CHECK(F.copies["device"] == 4);
+  CHECK(F.launched["retire"] == 1);
+  for (int k = 0; k < 5; ++k) {
+    uint32_t first, v;
+    memcpy(&first, outs[k], 4);
+    CHECK(first >= 1000);
+    for (int32_t i = 0; i < s.vbase[k + 1] - s.vbase[k]; ++i) {
+      memcpy(&v, (char*)outs[k] + 4 * i, 4);
+      CHECK(v == first + (uint32_t)i);
+    }
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "stale_solo") stale_verdict("solo", 100, 200);
   else if (name == "stale_near") stale_verdict("near", 20000, 40000);
   else if (name == "stale_unposted") stale_verdict_unposted();
   else if (name == "failed_copy") failed_copy();
+  else if (name == "foreign_outputs") foreign_outputs();
   else { printf("no check %s\n", name.c_str()); return 2; }
   if (!failures) printf("ok\n");
   return failures != 0;

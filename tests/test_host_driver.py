@@ -34,3 +34,7 @@ def test_a_verdict_left_behind_is_nobody_elses(checks, name):
 
 def test_a_failed_copy_of_results_reports_no_ticket(checks):
     _run(checks, "failed_copy")
+
+
+def test_results_for_other_memory_are_copied(checks):
+    _run(checks, "foreign_outputs")
