@@ -155,8 +155,9 @@ struct State {
   uint32_t symmetric;   // 0 not checked, 1 yes, 2 no
   unsigned long long run_edges;  // edges of the levels so far (about)
   unsigned long long sym_sum[8];  // symmetry check: shares of the signed sum
+  unsigned long long plan_edges;  // edges of the level planned last, not in run_edges yet
   uint32_t asymmetric;  // symmetry check: met an id out of range
-  uint32_t pad[33];
+  uint32_t pad[31];
   LevelSet set[3];
 };
 

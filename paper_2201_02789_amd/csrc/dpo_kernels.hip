@@ -1657,7 +1657,8 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
   const bool bottom_up = goes_bottom_up(st);
   const bool adv = after == AFTER_BOTTOM_UP ? bottom_up : after != AFTER_NONE;
   uint32_t symmetric = st->plan == V_CHECK ? (bottom_up ? 1u : 2u) : st->symmetric;
-  unsigned long long run_edges = st->run_edges;
+  // (a planned level's edges count once it has run, however often it is planned)
+  unsigned long long run_edges = st->run_edges + (adv ? st->plan_edges : 0), plan_edges = 0;
   uint32_t L = st->base + adv;
   const uint32_t n = (uint32_t)a.q[0].n;
   if (tid == 0) sh.bad = 0;
@@ -1893,13 +1894,14 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
         }
       }
     }
-    run_edges += E;
+    plan_edges = E;
   }
   if (tid == 0) {
     st->base = L;
     st->plan = code;
     st->symmetric = symmetric;
     st->run_edges = run_edges;
+    st->plan_edges = plan_edges;
     if (L != L0) {
       st->vsel[L & 1] = c;
       st->vstale[L & 1] = 1u;
