@@ -17,6 +17,14 @@ constexpr int NW = PB / 64;      // wave64s per workgroup
 // 248 -> 240.  At 768 2 M/30 takes 390 and 100 K/64 174; at 192 250 K/8 takes 292:
 // blocks of few edges cost more than they spread.
 constexpr int SPREAD_EDGES = 384;
+// A level that probes and claims one bitmap spreads over so many blocks at most:
+// where neighbours have ids close together its claims meet on few lines, the more
+// waves the worse (us, at 32 / 64 / without a limit; level steps of full blocks in
+// brackets: 300 layers of 3,000 vertices, degree 24, 9,980 / 11,390 / 11,990
+// [9,310], 100 layers of 20,000 3,840 / 3,840 / 5,080 [3,810], a 100^3 grid of 26
+// neighbours 3,950 / 3,910 / 4,430 [4,040]; ids at random: the same grid 3,040 /
+// 2,940 / 2,650 [3,170], Erdos-Renyi of 1 M, degree 16, 322 / 312 / 308 [331]).
+constexpr uint32_t ONE_COPY_BLOCKS = 32;
 constexpr int STAGE = 512;       // LDS slots per wave for next-frontier staging
 constexpr int NQD = 8;           // descriptor queues (one per XCD: queue = virtual block % 8)
 constexpr int NQF = 64;          // frontier queues (queue = workgroup % 64), plus one overflow
@@ -80,12 +88,12 @@ constexpr uint32_t NEAR_STEP = 8;
 constexpr uint32_t NONE = 0xFFFFFFFFu;        // no vertex
 constexpr uint32_t NARROW_LEVELS = 4096;      // most levels per launch (a few ms)
 // How a narrow launch ended: the traversal done or failed, more narrow levels,
-// or a wide level, which goes top-down (a level step), bottom-up, or bottom-up
-// if the graph turns out symmetric.
-enum { V_DONE = 1, V_ERROR, V_MORE, V_TOP_DOWN, V_BOTTOM_UP, V_CHECK };
-// What a narrow launch follows: no level, a level step, a bottom-up level if
-// one was due.
-enum { AFTER_NONE = 0, AFTER_STEP, AFTER_BOTTOM_UP };
+// or a wide level, which goes top-down (a level step; V_STILL: and the launch ran
+// no level before it), bottom-up, or bottom-up if the graph turns out symmetric.
+enum { V_DONE = 1, V_ERROR, V_MORE, V_TOP_DOWN, V_BOTTOM_UP, V_CHECK, V_STILL };
+// What a narrow launch follows: a bottom-up level if one was due, or so many
+// level steps.
+constexpr uint32_t AFTER_BOTTOM_UP = ~0u;
 
 // bottom-up levels (BFS)
 // A level goes bottom-up if its frontier has at least 1 / BU_ALPHA of the edges
@@ -94,6 +102,14 @@ enum { AFTER_NONE = 0, AFTER_STEP, AFTER_BOTTOM_UP };
 // 386 / 382 / 382 / 584, a batch of 512 1,860 / 1,824 / 1,903 / 2,085; R-MAT of
 // scale 22 618 / 472 / 472.
 constexpr uint32_t BU_ALPHA = 16;
+// Once a bottom-up level has found less than 1 / BU_VAIN of the edges left, it has
+// run most rows to their ends in vain, and the graph is one of many wide levels:
+// those that would be split levels top-down then need that share to go bottom-up
+// (us, never / 4 / 8: 30 layers of 100,000 vertices 1,200 / 1,090 / 1,060, a band
+// of 1 M vertices 855 / 820 / 805, a 100^3 grid of 26 neighbours 2,025 / 2,090 /
+// 2,040).  One-copy levels are slow enough for bottom-up ones to win all the same
+// (the band 1,080 without this, 1,460 with it).
+constexpr uint32_t BU_VAIN = 8;
 // Queries go bottom-up if they have this many entries together.  Measured (us, top-down /
 // bottom-up): batches of 2.4 M entries 228 / 280, 12 M 420 / 465, 19 M 390 / 390 and 449 /
 // 456, 30 M 676 / 602, 50 M 700 / 618; served queries of 13 M 333 / 412, 15 M 365 / 447,
@@ -157,7 +173,8 @@ struct State {
   unsigned long long sym_sum[8];  // symmetry check: shares of the signed sum
   unsigned long long plan_edges;  // edges of the level planned last, not in run_edges yet
   uint32_t asymmetric;  // symmetry check: met an id out of range
-  uint32_t pad[31];
+  uint32_t in_vain;     // a bottom-up level found less than 1 / BU_VAIN of the edges left
+  uint32_t pad[30];
   LevelSet set[3];
 };
 

@@ -719,7 +719,8 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
   Counters cn{0, 0, 0, 0, 0, 0, 0};
   // Frontier entries per virtual block, and per wave of it: PB and 64, or fewer
   // where that would leave workgroups of the grid without a block while waves
-  // have more than SPREAD_EDGES edges on average.  The groups, lists and records
+  // have more than SPREAD_EDGES edges on average (a level that claims in the
+  // bitmap it probes: over ONE_COPY_BLOCKS at most).  The groups, lists and records
   // of a level are sized for slots / PB blocks of PB entries, so never more
   // blocks than that.  A run that counts or times grids keeps blocks of PB
   // parents, and so does SSSP, whose thresholded parents are shared out evenly
@@ -727,7 +728,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
   // more and smaller grids).
   uint32_t epb = PB;
   if (P == PROB_BFS && PH == PH_BOTH && !TM && !a.count_stats) {
-    const uint32_t most = min(gridDim.x, (uint32_t)a.slots / PB);
+    const uint32_t most = min(split ? gridDim.x : ONE_COPY_BLOCKS, (uint32_t)a.slots / PB);
     while ((uint64_t)epb * (uint32_t)a.m > (uint64_t)SPREAD_EDGES * NW * (uint32_t)a.n &&
            epb > (uint32_t)NW && ceil_div(F, epb / 2) <= most)
       epb /= 2;
@@ -1640,7 +1641,7 @@ __device__ __forceinline__ void narrow_visit(const Args& a, uint32_t* s_bits, ui
   }
 }
 
-// after: what ran since the last launch (AFTER_*).
+// after: what ran since the last launch: so many level steps, or AFTER_BOTTOM_UP.
 // LDS: the visited bits are in LDS.
 template <bool LDS>
 __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t after, uint32_t ticket,
@@ -1655,10 +1656,12 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     return;
   }
   const bool bottom_up = goes_bottom_up(st);
-  const bool adv = after == AFTER_BOTTOM_UP ? bottom_up : after != AFTER_NONE;
+  const uint32_t adv = after == AFTER_BOTTOM_UP ? bottom_up : after;
   uint32_t symmetric = st->plan == V_CHECK ? (bottom_up ? 1u : 2u) : st->symmetric;
-  // (a planned level's edges count once it has run, however often it is planned)
-  unsigned long long run_edges = st->run_edges + (adv ? st->plan_edges : 0), plan_edges = 0;
+  // (a planned level's edges count once it has run, however often it is planned,
+  // and for those of the level steps behind it)
+  unsigned long long run_edges = st->run_edges + adv * st->plan_edges, plan_edges = 0;
+  uint32_t in_vain = st->in_vain;
   uint32_t L = st->base + adv;
   const uint32_t n = (uint32_t)a.q[0].n;
   if (tid == 0) sh.bad = 0;
@@ -1856,7 +1859,8 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     const uint32_t fill = (uint32_t)(&st->set[(L + 2) % 3].fcnt[NQF] - sets);
     for (uint32_t i = tid; i < 3 * sizeof(LevelSet) / 4; i += NB) sets[i] = i == fill ? F : 0u;
   }
-  uint32_t code = wide ? V_TOP_DOWN : V_MORE;
+  const uint32_t top_down = L == L0 ? V_STILL : V_TOP_DOWN;
+  uint32_t code = wide ? top_down : V_MORE;
   if (a.bottom_up && wide) {
     // the level's edges, from the degrees of up to NB of its vertices
     const int32_t* fin = (L & 1) ? a.front1 : a.front0;
@@ -1875,7 +1879,9 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     for (uint32_t w = 0; w < NB / 64; ++w) E += sh.wsum[w];
     if (F > NB) E = E * F / NB;
     const unsigned long long left = (unsigned long long)a.m > run_edges ? a.m - run_edges : 0;
-    if (symmetric != 2 && E * BU_ALPHA >= left) {
+    in_vain |= adv && after == AFTER_BOTTOM_UP && E * BU_VAIN < left;
+    const uint32_t alpha = in_vain && F >= (uint32_t)a.split_min ? BU_VAIN : BU_ALPHA;
+    if (symmetric != 2 && E * alpha >= left) {
       code = V_BOTTOM_UP;
       if (!symmetric) {
         // The symmetry check reads the whole graph; on the directed graphs one
@@ -1890,7 +1896,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
         code = V_CHECK;
         if (__syncthreads_or(missing)) {
           symmetric = 2;
-          code = V_TOP_DOWN;
+          code = top_down;
         }
       }
     }
@@ -1902,6 +1908,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     st->symmetric = symmetric;
     st->run_edges = run_edges;
     st->plan_edges = plan_edges;
+    st->in_vain = in_vain;
     if (L != L0) {
       st->vsel[L & 1] = c;
       st->vstale[L & 1] = 1u;

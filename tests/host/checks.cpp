@@ -108,6 +108,30 @@ static void stale_verdict_unposted() {
   CHECK(F.launched["parent"] == 1);
 }
 
+// A run of wide levels takes half as many level steps at a time as it has had;
+// a narrow or bottom-up level in between ends the run.
+static void wide_run(bool noalloc) {
+  Single s(5000, 10);
+  auto after = std::make_shared<std::vector<uint32_t>>();
+  const std::vector<uint32_t> codes = {V_STILL, V_STILL, V_STILL, V_STILL, V_STILL, V_STILL, V_TOP_DOWN,
+                                       V_STILL, V_BOTTOM_UP, 0, V_STILL, V_STILL, V_DONE};
+  post_in_turn(codes);
+  auto post = F.kernels["narrow"];
+  F.kernels["narrow"] = [=](void** p) {
+    after->push_back(*(uint32_t*)p[1]);
+    return post(p);
+  };
+  auto steps = std::make_shared<std::vector<uint32_t>>();
+  F.kernels["parent"] = [=](void** p) -> std::function<void()> {
+    steps->push_back(*(uint32_t*)p[1]);
+    return nullptr;
+  };
+  CHECK((noalloc ? dpo_bfs_noalloc(&s.g, 0, &s.o, (int32_t*)s.out.data(), nullptr) : s.bfs()) == DPO_OK);
+  const uint32_t B = AFTER_BOTTOM_UP;
+  CHECK((*after == std::vector<uint32_t>{0, 1, 1, 1, 1, 2, 3, 1, 1, B, B, 1, 1}));
+  CHECK((*steps == std::vector<uint32_t>{0, 0, 0, 0, 0, 1, 0, 1, 2, 0, 0, 0, 0}));
+}
+
 // An engine over graphs of the given sizes whose replays end every query.
 struct Served {
   std::vector<int32_t> vbase, rp, col;
@@ -214,6 +238,8 @@ int main(int argc, char** argv) {
   if (name == "stale_solo") stale_verdict("solo", 100, 200);
   else if (name == "stale_near") stale_verdict("near", 20000, 40000);
   else if (name == "stale_unposted") stale_verdict_unposted();
+  else if (name == "wide_run") wide_run(false);
+  else if (name == "wide_run_noalloc") wide_run(true);
   else if (name == "failed_copy") failed_copy();
   else if (name == "foreign_outputs") foreign_outputs();
   else { printf("no check %s\n", name.c_str()); return 2; }

@@ -38,3 +38,8 @@ def test_a_failed_copy_of_results_reports_no_ticket(checks):
 
 def test_results_for_other_memory_are_copied(checks):
     _run(checks, "foreign_outputs")
+
+
+@pytest.mark.parametrize("name", ["wide_run", "wide_run_noalloc"])
+def test_a_run_of_wide_levels_is_launched_in_growing_parts(checks, name):
+    _run(checks, name)
