@@ -2496,7 +2496,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void near_kernel(Args a, uint32_t src
 // is preceded by this pass over the adjacency: the sum over all entries of
 // h(u, v) where u < v and -h(v, u) where u > v, h a keyed mix (add_pair), is zero
 // modulo 2^64 if the graph is symmetric, and otherwise for few keys: for none if
-// one entry lacks its reverse, for some 2^-46 of them or fewer for the worst small
+// one entry lacks its reverse, for some 2^-47 of them or fewer for the worst small
 // sets that were looked for.  The key is drawn anew for each check.  An id out of
 // range counts as asymmetric.
 //
@@ -2509,7 +2509,7 @@ template <bool ARENA>
 __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, const PairKey key,
                                                       const uint32_t* vbase, uint32_t ngraphs) {
   constexpr uint32_t U = NARROW_U;
-  __shared__ uint32_t s_row[NW][64];
+  __shared__ uint32_t s_row[NW][64];  // its vertex, with the key's first word added
   __shared__ uint32_t s_lo[ARENA ? NW : 1][64], s_n[ARENA ? NW : 1][64];  // its graph's vertices
   __shared__ __align__(8) uint8_t s_heads[NW][64 * U];
   __shared__ unsigned long long s_sum[NW];
@@ -2553,7 +2553,7 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, const 
           wend = (uint32_t)__builtin_amdgcn_readlane((int)e, 63);
           some = e > b && e > lo;
           const unsigned long long rows = __ballot(some);
-          if (some) s_row[wave][lane_rank(rows)] = r + lane;
+          if (some) s_row[wave][lane_rank(rows)] = r + lane + key.k[0];
           if (ARENA && some) {
             if (r + lane >= g1) {
               uint32_t g = 0, end = ngraphs;
@@ -2592,9 +2592,9 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, const 
               const uint32_t k = row_of(s_heads[wave], u, lane, p);
               uint32_t w = s_row[wave][k];
               const bool in = whole || x0 + u * 64u + (uint32_t)lane - lo < hi - lo;
-              if (!in) w = v[u];
+              if (!in) w = v[u] + key.k[0];
               if (ARENA && !one) leaves |= in && v[u] - s_lo[wave][k] >= s_n[wave][k];
-              sum = add_pair(sum, w, v[u], key.k);
+              sum = add_pair(sum, w, v[u] + key.k[0], key.k);
             }
             wave_lds_sync();
           } else {  // within one row
@@ -2603,7 +2603,7 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, const 
             for (uint32_t u = 0; u < U; ++u) {
               const bool in = whole || x0 + u * 64u + (uint32_t)lane - lo < hi - lo;
               if (ARENA && !one) leaves |= in && v[u] - s_lo[wave][first] >= s_n[wave][first];
-              sum = add_pair(sum, in ? row : v[u], v[u], key.k);
+              sum = add_pair(sum, in ? row : v[u] + key.k[0], v[u] + key.k[0], key.k);
             }
           }
           if (ARENA && one) {  // the usual case, without the lookups
