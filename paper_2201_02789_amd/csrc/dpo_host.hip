@@ -643,9 +643,9 @@ dpo_status ended(uint32_t verdict) {
 }
 
 // SSSP on a small graph.
-dpo_status launch_solo(SetRun& sr, int32_t source, uint32_t* verdict) {
-  uint32_t src = (uint32_t)source, ticket = 0;
-  void* p[] = {&sr.a, &src, &ticket, &verdict};
+dpo_status launch_solo(SetRun& sr, int32_t source, int32_t threshold, uint32_t* verdict) {
+  uint32_t src = (uint32_t)source, T = (uint32_t)threshold;
+  void* p[] = {&sr.a, &src, &T, &verdict};
   return hip_ok(hipLaunchKernel(solo_kernel_ptr(sr.a.m >= SOLO_FAR_EDGES), dim3(1), dim3(NARROW_BLOCK),
                                 p, 0, sr.stream));
 }
@@ -773,7 +773,7 @@ dpo_status traverse(int problem, const dpo_csr* g, int32_t source, const dpo_opt
   if (any && problem == PROB_SSSP && g->n <= SOLO_VERTICES && g->m <= SOLO_EDGES) {
     uint32_t* verdict = r.host_flags + 8;
     *verdict = 0;
-    if ((s = launch_solo(sr, source, verdict)) != DPO_OK) return s;
+    if ((s = launch_solo(sr, source, o->threshold, verdict)) != DPO_OK) return s;
     if (hipStreamSynchronize(sr.stream) != hipSuccess) return DPO_ERR_HIP;
     return ended(*verdict);
   }

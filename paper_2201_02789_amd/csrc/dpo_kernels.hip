@@ -1595,6 +1595,27 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// Degrees of the rows [start[j], end[j]) in the ends' place, as a level step takes
+// them: a row that ends before it starts has no entries, and one that would launch
+// (T) outside the adjacency is not read, but an error.  per: rows in use.
+template <uint32_t PER>
+__device__ __forceinline__ void row_degrees(const Args& a, const uint32_t (&start)[PER], uint32_t (&end)[PER],
+                                            uint32_t per, uint32_t T, uint32_t& bad) {
+  uint32_t top = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < PER; ++j) {
+    if (j >= per) break;
+    top = max(top, max(start[j], end[j]));
+    end[j] = (uint32_t)max((int32_t)(end[j] - start[j]), 0);
+  }
+  if (top <= (uint32_t)a.m) return;
+  for (uint32_t j = 0; j < PER; ++j) {
+    if (end[j] == 0 || end[j] < T || max(start[j], start[j] + end[j]) <= (uint32_t)a.m) continue;
+    end[j] = 0;
+    bad = ERR_CAPACITY;
+  }
+}
+
 // Rows of 64 * NARROW_U consecutive edges, by a wave: heads[x - 1] is set if a
 // row begins at edge x > 0 of them, so that the marks below an edge's own place
 // count the rows begun up to it.
@@ -1663,7 +1684,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
   unsigned long long run_edges = st->run_edges + adv * st->plan_edges, plan_edges = 0;
   uint32_t in_vain = st->in_vain;
   uint32_t L = st->base + adv;
-  const uint32_t n = (uint32_t)a.q[0].n;
+  const uint32_t n = (uint32_t)a.q[0].n, T = (uint32_t)a.q[0].T;
   if (tid == 0) sh.bad = 0;
   const LevelSet* prv = &st->set[(L + 2) % 3];
   if (wave == 0) {
@@ -1698,7 +1719,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
   __syncthreads();
   while (F != 0 && !wide) {
     // rows of this thread's entries [tid * per, tid * per + per)
-    const uint32_t per = ceil_div(F, NB);
+    const uint32_t per = (uint32_t)__builtin_amdgcn_readfirstlane((int)ceil_div(F, NB));
     uint32_t start[PER], deg[PER], sum = 0, rows = 0;
     bool big = F > NB;
 #pragma unroll
@@ -1712,9 +1733,10 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
       }
     }
     if (tid == 0) sh.cnt = 0;
+    row_degrees<PER>(a, start, deg, per, T, sh.bad);
 #pragma unroll
     for (uint32_t j = 0; j < PER; ++j) {
-      deg[j] -= start[j];
+      if (j >= per) break;
       sum += deg[j];
       rows += deg[j] != 0;
       big |= deg[j] > U;
@@ -1730,7 +1752,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u) {
         if (v[u] >= n && valid[u]) {
-          sh.bad = 1;
+          sh.bad = ERR_ARG;
           v[u] = NONE;
         }
       }
@@ -1837,7 +1859,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
   }
   __syncthreads();
   if (F == 0 || sh.bad) {
-    const uint32_t err = sh.bad ? (uint32_t)ERR_ARG : 0u;
+    const uint32_t err = sh.bad;
     if (tid == 0) {
       st->done = 1;
       st->error = err;
@@ -1869,7 +1891,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
       const uint32_t i = F <= NB ? tid : (uint32_t)((uint64_t)tid * F / NB);
       v = L == L0 ? (uint32_t)frontier_at(a, fin, sh.fpre, i)
           : i < FC ? s_front[cur + i] : (uint32_t)fin[(size_t)NQF * a.fcap + i];
-      deg = (uint32_t)(a.rp[v + 1] - a.rp[v]);
+      deg = (uint32_t)max(a.rp[v + 1] - a.rp[v], 0);
     }
     const uint32_t incl = wave_incl_scan(deg, lane);
     if (lane == 63) sh.wsum[wave] = incl;
@@ -1888,9 +1910,10 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
         // meets, a few entries' missing reverses spare it.
         bool missing = false;
         if (tid < SYM_SAMPLES && deg) {
-          const uint32_t w = (uint32_t)a.col[(uint32_t)a.rp[v] + tid * 0x9E3779B1u % deg];
+          const uint32_t x = (uint32_t)a.rp[v] + tid * 0x9E3779B1u % deg;
+          const uint32_t w = x < (uint32_t)a.m ? (uint32_t)a.col[x] : n;
           const uint32_t b = w < n ? (uint32_t)a.rp[w] : 0u, e = w < n ? (uint32_t)a.rp[w + 1] : 0u;
-          missing = e - b <= SYM_SAMPLE_DEGREE;
+          missing = e - b <= SYM_SAMPLE_DEGREE && e <= (uint32_t)a.m;
           for (uint32_t x = b; x < e && missing; ++x) missing = (uint32_t)a.col[x] != v;
         }
         code = V_CHECK;
@@ -1946,7 +1969,7 @@ struct SoloLds {
 // Writes its output and its verdict and needs nothing of the workspace but the
 // overflow queues.
 template <bool FAR>
-__global__ __launch_bounds__(NARROW_BLOCK) void solo_kernel(Args a, uint32_t src, uint32_t ticket,
+__global__ __launch_bounds__(NARROW_BLOCK) void solo_kernel(Args a, uint32_t src, uint32_t T,
                                                             uint32_t* verdict) {
   __shared__ SoloLds sh;
   constexpr uint32_t NB = NARROW_BLOCK, PER = SOLO_FRONT / NB, U = NARROW_U;
@@ -2022,7 +2045,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void solo_kernel(Args a, uint32_t src
         bad |= v[u] >= n;
         x[u] = s_dist[min(v[u], n - 1)];
       }
-      if (bad) sh.bad = 1;
+      if (bad) sh.bad = ERR_ARG;
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u) {
         if (nd[u] < x[u] && v[u] < n) x[u] = atomicMin(&s_dist[v[u]], nd[u]);
@@ -2049,7 +2072,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void solo_kernel(Args a, uint32_t src
         __syncthreads();
       }
       // rows of this thread's entries [tid * per, tid * per + per)
-      const uint32_t per = ceil_div(count, NB);
+      const uint32_t per = (uint32_t)__builtin_amdgcn_readfirstlane((int)ceil_div(count, NB));
       uint32_t start[PER], deg[PER], sum = 0, rows = 0;
       bool big = count > NB;
 #pragma unroll
@@ -2063,9 +2086,10 @@ __global__ __launch_bounds__(NARROW_BLOCK) void solo_kernel(Args a, uint32_t src
           atomicAnd(&s_bits[v >> 5], ~(1u << (v & 31)));  // may be queued again
         }
       }
+      row_degrees<PER>(a, start, deg, per, T, sh.bad);
 #pragma unroll
       for (uint32_t j = 0; j < PER; ++j) {
-        deg[j] -= start[j];
+        if (j >= per) break;
         sum += deg[j];
         rows += deg[j] != 0;
         big |= deg[j] > U;
@@ -2205,8 +2229,8 @@ __global__ __launch_bounds__(NARROW_BLOCK) void solo_kernel(Args a, uint32_t src
   }
   for (uint32_t i = tid; i < n; i += NB) a.dist[i] = s_dist[i];
   if (tid == 0) {
-    const uint32_t err = sh.bad ? (uint32_t)ERR_ARG : F ? (uint32_t)ERR_TIMEOUT : 0u;
-    post_verdict(verdict, ticket, err ? V_ERROR : V_DONE, err);
+    const uint32_t err = sh.bad ? sh.bad : F ? (uint32_t)ERR_TIMEOUT : 0u;
+    post_verdict(verdict, 0, err ? V_ERROR : V_DONE, err);
   }
 }
 
@@ -2236,7 +2260,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void near_kernel(Args a, uint32_t src
   constexpr uint32_t NB = NARROW_BLOCK, FC = NEAR_FRONT, PER = FC / NB, U = NARROW_U;
   const uint32_t tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  const uint32_t n = (uint32_t)a.n, m = (uint32_t)a.m, nbits = (n + 31) / 32;
+  const uint32_t n = (uint32_t)a.n, m = (uint32_t)a.m, nbits = (n + 31) / 32, T = (uint32_t)a.q[0].T;
   uint32_t* s_near = sh.words;  // in the next frontier
   uint32_t* s_wait = s_near + nbits;  // in the far list
   uint32_t* s_front = s_wait + nbits;
@@ -2319,14 +2343,14 @@ __global__ __launch_bounds__(NARROW_BLOCK) void near_kernel(Args a, uint32_t src
       // no probe first: it would be one more round trip, for as many accesses
       x[u] = nd[u] != 0xFFFFFFFFu ? atomicMin(&dist[v[u]], nd[u]) : 0u;
     }
-    if (bad) sh.bad = 1;
+    if (bad) sh.bad = ERR_ARG;
     pin(x);
 #pragma unroll
     for (uint32_t u = 0; u < U; ++u) f[u] = nd[u] < x[u];
     append(f, v, nd);
   };
   for (unsigned long long round = 0; F != 0 && !wide && !sh.bad; ++round) {
-    const uint32_t per = ceil_div(F, NB);
+    const uint32_t per = (uint32_t)__builtin_amdgcn_readfirstlane((int)ceil_div(F, NB));
     uint32_t start[PER], deg[PER], du[PER], sum = 0, rows = 0;
     bool big = F > NB;
 #pragma unroll
@@ -2346,11 +2370,12 @@ __global__ __launch_bounds__(NARROW_BLOCK) void near_kernel(Args a, uint32_t src
     pin(deg);
     pin(du);
     if (tid == 0) sh.cnt = 0;
+    row_degrees<PER>(a, start, deg, per, T, sh.bad);
 #pragma unroll
     for (uint32_t j = 0; j < PER; ++j) {
+      if (j >= per) break;
       const uint32_t i = tid * per + j;
-      if (j < per && i < F) a.dist2[s_front[cur + i]] = du[j];  // as a level step folds
-      deg[j] -= start[j];
+      if (i < F) a.dist2[s_front[cur + i]] = du[j];  // as a level step folds
       sum += deg[j];
       rows += deg[j] != 0;
       big |= deg[j] > U;
@@ -2465,11 +2490,11 @@ __global__ __launch_bounds__(NARROW_BLOCK) void near_kernel(Args a, uint32_t src
     const uint32_t t = cur;
     cur = nxt;
     nxt = t;
-    if (round > (unsigned long long)n * 64) sh.bad = 2;
+    if (round > (unsigned long long)n * 64) sh.bad = ERR_TIMEOUT;
     __syncthreads();
   }
   __syncthreads();
-  uint32_t code = V_DONE, err = sh.bad == 1 ? ERR_ARG : sh.bad ? ERR_TIMEOUT : 0;
+  uint32_t code = V_DONE, err = sh.bad;
   if (err) code = V_ERROR;
   if (wide && !err) {
     code = V_TOP_DOWN;
@@ -2498,7 +2523,9 @@ __global__ __launch_bounds__(NARROW_BLOCK) void near_kernel(Args a, uint32_t src
 // modulo 2^64 if the graph is symmetric, and otherwise for few keys: for none if
 // one entry lacks its reverse, for some 2^-47 of them or fewer for the worst small
 // sets that were looked for.  The key is drawn anew for each check.  An id out of
-// range counts as asymmetric.
+// range counts as asymmetric, and so does a row that ends before it starts or rows
+// that are not those of a.m entries: what a level step reports of them, a bottom-up
+// level would not.
 //
 // A wave runs an even share of the entries in slices of 64 * U, the next slice's
 // loads issued before a slice is summed; the rows come in windows of 64.
@@ -2552,6 +2579,7 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, const 
         if (fresh) {
           wend = (uint32_t)__builtin_amdgcn_readlane((int)e, 63);
           some = e > b && e > lo;
+          top = e < b ? ~0u : top;
           const unsigned long long rows = __ballot(some);
           if (some) s_row[wave][lane_rank(rows)] = r + lane + key.k[0];
           if (ARENA && some) {
@@ -2627,7 +2655,7 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, const 
       if (lo < send) break;  // rows that end before the entries do
       x0 = send;
     }
-    const bool bad = __any(top >= n || leaves) || x0 < x1;
+    const bool bad = __any(top >= n || leaves) || x0 < x1 || (uint32_t)a.rp[n] != m;
     if (bad && lane == 0) atomicOr(&st->asymmetric, 1u);
   }
 #pragma unroll
