@@ -330,9 +330,9 @@ struct SetRun {
 };
 
 // Queries of `slots` vertices in all, over the graphs of g, go bottom-up by
-// themselves: the check reads all of g (about 8 times as fast per entry as a
-// traversal), and a level step of such queries is three kernels longer
-// (BU_QUERIES_EDGES).
+// themselves, if g is symmetric: the check reads all of g (about 8 times as fast
+// per entry as a traversal), and a level step of such queries is three kernels
+// longer (BU_QUERIES_EDGES).
 bool queries_pay(const dpo_csr& g, int64_t slots) {
   return slots >= g.n && (double)slots / g.n * g.m >= (double)BU_QUERIES_EDGES;
 }
@@ -361,7 +361,9 @@ dpo_status prepare_set(Runtime& r, int problem, const dpo_csr* g, const dpo_opti
   const bool dense = dense_graph(*g);
   const bool bfs = problem == PROB_BFS;
   // Queries that go bottom-up by themselves: a batch of enough work, and a serving
-  // engine once enough has been admitted.  They use found bytes.
+  // engine while enough is running.  They use found bytes (as do those of a large
+  // batch that turns out directed: 512 queries over directed graphs 4,050 -> 3,700
+  // us, 80 over larger ones 1,080 -> 670).
   const bool by_query = bfs && (batch_call ? queries_pay(*g, slots) : nq > 1) && gran != AGG_FLAT &&
                         gran != AGG_NONE && !count_stats && !tm;
   const bool hint = o.claim_hint == DPO_HINT_ON ||
@@ -533,18 +535,21 @@ dpo_status launch_symmetry(Runtime& r, SetRun& sr, const uint32_t* vbase = nullp
                                 dim3(PB), p, 0, sr.stream));
 }
 
-// The same for an arena, and its result into the state (BU_QUERIES).  An arena
-// of more graphs than the space behind the tallies holds stays unchecked, and
-// its queries top-down.
-dpo_status check_symmetry(Runtime& r, SetRun& sr, const int32_t* graph_vbase, int32_t ngraphs) {
+// The same for an arena, its result into the state
+// (BU_QUERIES) and, as V_BOTTOM_UP or V_TOP_DOWN under `ticket`, into the pinned
+// word `verdict`.  *asked: false for an arena of more graphs than the space behind
+// the tallies holds, which stays unchecked.
+dpo_status check_symmetry(Runtime& r, SetRun& sr, const int32_t* graph_vbase, int32_t ngraphs,
+                          uint32_t ticket, uint32_t* verdict, bool* asked) {
   uint32_t* vbase = sr.a.tally + 4 * sr.a.nq;
-  if ((size_t)(4 * sr.a.nq + ngraphs + 1) * 4 > (size_t)MAX_GRID * NSTAT * 8) return DPO_OK;
+  *asked = (size_t)(4 * sr.a.nq + ngraphs + 1) * 4 <= (size_t)MAX_GRID * NSTAT * 8;
+  if (!*asked) return DPO_OK;
   // (pageable memory: copied before the call returns)
   if (hipMemcpyAsync(vbase, graph_vbase, (size_t)(ngraphs + 1) * 4, hipMemcpyHostToDevice, sr.stream) !=
       hipSuccess)
     return DPO_ERR_HIP;
   dpo_status s = launch_symmetry(r, sr, vbase, (uint32_t)ngraphs);
-  void* p[] = {&sr.a.st};
+  void* p[] = {&sr.a.st, &ticket, &verdict};
   return s != DPO_OK ? s
                      : hip_ok(hipLaunchKernel(settle_symmetry_kernel_ptr(), dim3(1), dim3(64), p, 0, sr.stream));
 }
@@ -856,9 +861,18 @@ dpo_status traverse_batch(int problem, const dpo_arena* ar, const dpo_query* qs,
   int32_t* hl = r.host_list;
   for (int32_t i = 0; i < nq; ++i) hl[i] = i;
   if ((s = start_set(r, sr)) != DPO_OK) return s;
+  // bottom-up only if the arena is symmetric: its check runs before the admission,
+  // during which the host learns the answer and picks the replay
+  uint32_t ticket = 0, verdict = V_TOP_DOWN;
+  bool asked = false;
+  if (sr.a.bottom_up) {
+    ticket = next_ticket(r, r.host_flags + 8);
+    s = check_symmetry(r, sr, ar->graph_vbase, ar->ngraphs, ticket, r.host_flags + 8, &asked);
+    if (s != DPO_OK) return s;
+  }
   if ((s = admit(sr, hq, nq, hl, nq)) != DPO_OK) return s;
-  if (sr.a.bottom_up && (s = check_symmetry(r, sr, ar->graph_vbase, ar->ngraphs)) != DPO_OK)
-    return s;
+  if (asked && (s = wait_verdict(r.host_flags + 8, ticket, sr.stream, &verdict)) != DPO_OK) return s;
+  if ((verdict & 15u) != V_BOTTOM_UP) sr.a.bottom_up = BU_OFF;
   if ((s = run_to_completion(r, sr, slots)) != DPO_OK) return s;
   return read_stats(r, sr, st);
 }
@@ -978,7 +992,7 @@ struct dpo_engine {
   int32_t running = 0;
   bool inflight = false;
   hipGraphExec_t exec = nullptr;
-  hipGraphExec_t plain = nullptr;  // BU_QUERIES: the replay before the check
+  hipGraphExec_t plain = nullptr;  // BU_QUERIES: the replay where they would not pay
   dpo::Query* hq = nullptr;   // pinned mirror of the device query table
   int32_t* hlist = nullptr;   // pinned
   uint32_t* hflags = nullptr; // pinned
@@ -986,8 +1000,11 @@ struct dpo_engine {
   std::vector<int32_t> hretire_pre, hretire_q;
   hipEvent_t retired = nullptr;
   int device = 0;
-  int64_t served = 0;  // vertices of the queries admitted since the engine was last idle
-  bool checked = false;  // the arena's symmetry, since then
+  int64_t running_n = 0;  // vertices of the running queries
+  // since the engine was last idle: was the arena's symmetry asked for (the answer
+  // is in hflags[4] once that step's replay has ended); was the last replay `exec`;
+  // has one been followed by `plain`
+  bool asked = false, tallied = false, stale = false;
 };
 
 namespace dpo {
@@ -1089,6 +1106,7 @@ dpo_status engine_enqueue(dpo_engine* e) {
     for (int32_t k = 0; k < retired; ++k) {
       Running& ru = e->run[e->hretire_q[k]];
       slots_free(e, ru.slot0, ru.footprint);
+      e->running_n -= ru.n;
       e->landing.push_back(ru.ticket);
       ru = Running{};
       e->free_q.push_back(e->hretire_q[k]);
@@ -1117,6 +1135,7 @@ dpo_status engine_enqueue(dpo_engine* e) {
     ru.slot0 = slot0;
     ru.footprint = round32(n);
     e->hlist[count++] = q;
+    e->running_n += n;
     ++e->running;
     e->pending.pop_front();
   }
@@ -1124,24 +1143,39 @@ dpo_status engine_enqueue(dpo_engine* e) {
     if (reset) {
       // nothing was running: restart the level sets (and their counters)
       if ((s = start_set(r, sr)) != DPO_OK) return s;
-      e->served = 0;
-      e->checked = false;
+      e->asked = e->tallied = e->stale = false;
     }
     if ((s = admit(sr, e->hq, e->max_queries, e->hlist, count)) != DPO_OK) return s;
-    for (int32_t k = 0; k < count; ++k) e->served += e->hq[e->hlist[k]].n;
-    if (sr.a.bottom_up && !e->checked && queries_pay(e->csr, e->served)) {
-      // enough work for the check to pay (see prepare_set); the answer holds
-      // until the engine is idle
-      if ((s = check_symmetry(r, sr, e->vbase.data(), (int32_t)e->vbase.size() - 1)) != DPO_OK)
-        return s;
-      e->checked = true;
-    }
   }
   if (e->running > 0) {
-    // (the tallies of a query are zero from its admission until the first replay
-    // that makes them)
-    if (hipGraphLaunch(e->plain && !e->checked ? e->plain : e->exec, sr.stream) != hipSuccess)
-      return DPO_ERR_HIP;
+    // Bottom-up nodes while the running queries are enough work (see prepare_set)
+    // and the arena is not known to be asymmetric; the answer holds until the
+    // engine is idle.
+    bool up = !e->plain;
+    if (e->plain && queries_pay(e->csr, e->running_n)) {
+      if (!e->asked) {
+        e->hflags[4] = 0;
+        bool asked;
+        s = check_symmetry(r, sr, e->vbase.data(), (int32_t)e->vbase.size() - 1, 0, e->hflags + 4, &asked);
+        if (s != DPO_OK) return s;
+        if (!asked) e->hflags[4] = V_TOP_DOWN;
+        e->asked = true;
+      }
+      up = __atomic_load_n(e->hflags + 4, __ATOMIC_RELAXED) != V_TOP_DOWN;
+    }
+    // the tallies of a query are zero from its admission until the first replay
+    // that makes them; those of a level are cleared by the level before it, if that
+    // one makes them too
+    e->stale |= e->tallied && !up;
+    if (up && e->stale) {
+      e->stale = false;
+      void* cp[] = {&sr.a};
+      if (hipLaunchKernel(clear_tally_kernel_ptr(), dim3((unsigned)cdiv(2 * sr.a.nq, PB)), dim3(PB), cp, 0,
+                          sr.stream) != hipSuccess)
+        return DPO_ERR_HIP;
+    }
+    e->tallied = up;
+    if (hipGraphLaunch(up ? e->exec : e->plain, sr.stream) != hipSuccess) return DPO_ERR_HIP;
     if (hipMemcpyAsync(e->hq, sr.a.q, (size_t)e->max_queries * sizeof(Query),
                        hipMemcpyDeviceToHost, sr.stream) != hipSuccess)
       return DPO_ERR_HIP;

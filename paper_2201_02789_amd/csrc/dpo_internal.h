@@ -17,13 +17,15 @@ constexpr int NW = PB / 64;      // wave64s per workgroup
 // 248 -> 240.  At 768 2 M/30 takes 390 and 100 K/64 174; at 192 250 K/8 takes 292:
 // blocks of few edges cost more than they spread.
 constexpr int SPREAD_EDGES = 384;
-// A level that probes and claims one bitmap spreads over so many blocks at most:
-// where neighbours have ids close together its claims meet on few lines, the more
+// A single traversal's level that probes and claims one bitmap spreads over so many
+// blocks at most: where neighbours have ids close together its claims meet on few lines, the more
 // waves the worse (us, at 32 / 64 / without a limit; level steps of full blocks in
 // brackets: 300 layers of 3,000 vertices, degree 24, 9,980 / 11,390 / 11,990
 // [9,310], 100 layers of 20,000 3,840 / 3,840 / 5,080 [3,810], a 100^3 grid of 26
 // neighbours 3,950 / 3,910 / 4,430 [4,040]; ids at random: the same grid 3,040 /
 // 2,940 / 2,650 [3,170], Erdos-Renyi of 1 M, degree 16, 322 / 312 / 308 [331]).
+// Several queries' claims meet less: 300 queries served four at a time take 21.1 ms
+// with the limit, 19.8 without.
 constexpr uint32_t ONE_COPY_BLOCKS = 32;
 constexpr int STAGE = 512;       // LDS slots per wave for next-frontier staging
 constexpr int NQD = 8;           // descriptor queues (one per XCD: queue = virtual block % 8)
@@ -127,6 +129,7 @@ constexpr uint32_t BU_SORT = QB;   // queries it puts in order of their graphs
 constexpr uint32_t BU_LANE = 32;    // edges a lane looks at before the wave shares its row
 constexpr uint32_t SYM_EDGES = 1024;  // symmetry check: least edges per wave
 constexpr uint32_t SYM_SAMPLES = 128;  // entries whose reverse is looked up first, if
+constexpr int SYM_BLOCK_SAMPLES = 64;  // (an arena's check: per workgroup)
 constexpr uint32_t SYM_SAMPLE_DEGREE = 32;  // the row it would be in is this short
 
 enum { PROB_BFS = 0, PROB_SSSP = 1 };
@@ -276,6 +279,7 @@ const void* tally_kernel_ptr();
 const void* bottom_up_words_kernel_ptr();
 const void* bottom_up_queries_kernel_ptr();
 const void* settle_symmetry_kernel_ptr();
+const void* clear_tally_kernel_ptr();
 const void* start_kernel_ptr(int problem);
 const void* admit_kernel_ptr(int problem);
 const void* admit_sources_kernel_ptr();

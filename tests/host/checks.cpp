@@ -20,6 +20,7 @@ const void* bottom_up_kernel_ptr() { return fake::kernel("bottom_up"); }
 const void* tally_kernel_ptr() { return fake::kernel("tally"); }
 const void* bottom_up_words_kernel_ptr() { return fake::kernel("words"); }
 const void* bottom_up_queries_kernel_ptr() { return fake::kernel("bottom_up_queries"); }
+const void* clear_tally_kernel_ptr() { return fake::kernel("clear_tally"); }
 const void* settle_symmetry_kernel_ptr() { return fake::kernel("settle"); }
 const void* start_kernel_ptr(int) { return fake::kernel("start"); }
 const void* admit_kernel_ptr(int) { return fake::kernel("admit"); }
@@ -233,6 +234,81 @@ static void foreign_outputs() {
   }
 }
 
+static void answer_symmetry(uint32_t code) {
+  F.kernels["settle"] = [=](void** p) -> std::function<void()> {
+    const uint32_t ticket = *(uint32_t*)p[1];
+    uint32_t* verdict = *(uint32_t**)p[2];
+    return [=] { *verdict = ticket << 8 | code; };
+  };
+}
+
+// A large batch asks for its arena's symmetry and runs the level steps with
+// bottom-up nodes only if the answer is yes.
+static void batch_symmetry(bool symmetric) {
+  const int32_t n = 1000, m = 1 << 20, nq = 25;
+  std::vector<int32_t> vbase{0, n}, rp(n + 1), col(m), out((size_t)round32(n) * nq);
+  dpo_arena ar{1, vbase.data(), {n, m, rp.data(), col.data(), nullptr}};
+  std::vector<dpo_query> q(nq, dpo_query{0, 0, 0});
+  dpo_options o;
+  dpo_default_options(&o);
+  std::vector<char> ws(dpo_batch_workspace_bytes(&ar, q.data(), nq, &o));
+  answer_symmetry(symmetric ? V_BOTTOM_UP : V_TOP_DOWN);
+  F.kernels["advance"] = [](void** p) -> std::function<void()> {
+    uint32_t* flags = *(uint32_t**)p[2];
+    return [=] { flags[1] = 1; };
+  };
+  CHECK(dpo_bfs_batch(&ar, q.data(), nq, &o, 1, out.data(), ws.data(), ws.size(), nullptr, nullptr) == DPO_OK);
+  CHECK(F.launched["symmetry"] == 1 && F.launched["settle"] == 1);
+  CHECK(F.launched["parent"] == kBatchSteps && F.launched["harvest"] == kBatchSteps);
+  for (const char* k : {"tally", "words", "bottom_up_queries"}) CHECK(F.launched[k] == (symmetric ? kBatchSteps : 0));
+}
+
+// An engine's replays have bottom-up nodes while its running queries are enough
+// work, whatever it has served before, and none once its arena is known to be
+// asymmetric.
+static void engine_symmetry(bool symmetric) {
+  Served s({1000, 200000}, 25 << 20, 0, 1 << 20);
+  s.outs.reserve(64);
+  answer_symmetry(symmetric ? V_BOTTOM_UP : V_TOP_DOWN);
+  // queries of the first graph end with their second replay, of the second with
+  // their third
+  Query* table = s.e->sr.a.q;
+  uint32_t* flags = s.e->hflags;
+  const auto end_small = [=] {
+    for (int32_t q = 0; q < 64; ++q)
+      if (++table[q].lstart < (table[q].n > 1000 ? 3 : 2)) table[q].last = (int32_t)flags[0] - 1;
+      else table[q].last = -1;
+    flags[1] = 0;
+  };
+  s.e->exec->nodes.push_back({"end", end_small});
+  if (s.e->plain) s.e->plain->nodes.push_back({"end", end_small});
+  auto step = [&] {
+    const int before = F.launched["tally"];
+    CHECK(dpo_engine_step(s.e, nullptr, nullptr) == DPO_OK);
+    return F.launched["tally"] - before;
+  };
+  s.submit(0);
+  CHECK(step() == 0 && F.launched["symmetry"] == 0);  // too little work
+  s.submit(1);
+  s.submit(0);
+  CHECK(step() == 2 && F.launched["symmetry"] == 1);
+  CHECK(F.launched["clear_tally"] == 0);
+  s.submit(0);
+  CHECK(step() == (symmetric ? 2 : 0));
+  s.submit(0);
+  CHECK(step() == (symmetric ? 2 : 0));
+  for (int i = 0; i < 30; ++i) {  // the large one has ended: a trickle of small ones, never idle
+    s.submit(0);
+    CHECK(step() == 0);
+  }
+  s.submit(1);
+  s.submit(0);
+  CHECK(step() == (symmetric ? 2 : 0));
+  CHECK(F.launched["clear_tally"] == (symmetric ? 1 : 0));
+  CHECK(F.launched["symmetry"] == 1);
+  for (int i = 0; i < 5; ++i) step();
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "stale_solo") stale_verdict("solo", 100, 200);
@@ -240,6 +316,10 @@ int main(int argc, char** argv) {
   else if (name == "stale_unposted") stale_verdict_unposted();
   else if (name == "wide_run") wide_run(false);
   else if (name == "wide_run_noalloc") wide_run(true);
+  else if (name == "batch_symmetric") batch_symmetry(true);
+  else if (name == "batch_directed") batch_symmetry(false);
+  else if (name == "engine_symmetric") engine_symmetry(true);
+  else if (name == "engine_directed") engine_symmetry(false);
   else if (name == "failed_copy") failed_copy();
   else if (name == "foreign_outputs") foreign_outputs();
   else { printf("no check %s\n", name.c_str()); return 2; }

@@ -43,3 +43,10 @@ def test_results_for_other_memory_are_copied(checks):
 @pytest.mark.parametrize("name", ["wide_run", "wide_run_noalloc"])
 def test_a_run_of_wide_levels_is_launched_in_growing_parts(checks, name):
     _run(checks, name)
+
+
+@pytest.mark.parametrize("name", ["batch_symmetric", "batch_directed", "engine_symmetric", "engine_directed"])
+def test_bottom_up_nodes_only_where_they_pay(checks, name):
+    """A batch's or an engine's replays have them only on arenas found symmetric;
+    an engine's only while the running queries are enough work."""
+    _run(checks, name)
