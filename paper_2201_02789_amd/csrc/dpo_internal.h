@@ -41,10 +41,14 @@ constexpr int MAX_QUERIES = 4096;  // per-query tables are staged in LDS
 constexpr int ADMIT_CHUNK = 4096;  // output slots initialised per admit workgroup
 // SSSP bounds are kept from this many slots on: more distances than an XCD's L2
 // holds (4 MiB), while their bytes fit, so that fewer reads miss it (scale 21, the
-// widest level's child grids: 11.0 M -> 6.5 M misses).  Off / on (us): R-MAT of
-// 1 M vertices 1,656 / 1,706, of 2 M 1,860 / 1,820; 24 queries served in 4 M slots
-// 2,334 / 2,213.  What remains is the rate of random accesses.
-constexpr int64_t BOUND_MIN_SLOTS = 1 << 20;
+// widest level's child grids: 11.0 M -> 6.5 M misses).  Off / on (us; R-MAT of degree
+// 32 and 16, Erdos-Renyi of degree 16): 1 M vertices 1,330 / 1,315, 1,255 / 1,255,
+// 1,850 / 2,020; 1.25 M 1,430 / 1,405, 1,310 / 1,320, 2,080 / 2,190; 1.5 M 1,620 /
+// 1,580, 1,295 / 1,285, 2,670 / 2,680; 2 M 2,120 / 2,040, 1,665 / 1,635, 3,760 /
+// 3,655; 4 M 3,620 / 3,315, 2,930 / 2,805, 7,320 / 6,885.  An engine goes by its pool,
+// of which few slots may be in use: with one of 16 M, 24 queries of scales 11 to 13
+// take 871 / 857, of 13 to 16 1,230 / 1,257, of 13 to 18 2,325 / 2,165.
+constexpr int64_t BOUND_MIN_SLOTS = 3 << 19;
 constexpr int PRECHECK_MIN = 32;   // claim candidates per 512-lane batch above which
                                    // a coherent load precedes the atomics
 constexpr int NHINT = 8;           // BFS per-XCD visited copies (Args::hint), one per XCD
