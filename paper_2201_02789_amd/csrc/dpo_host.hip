@@ -473,12 +473,12 @@ int32_t admit_prefix(const Query* hq, int32_t* hlist, int32_t count) {
   return (int32_t)t;
 }
 
-dpo_status launch_admit(SetRun& sr, int32_t* hlist, int32_t count, int32_t reset, int32_t groups) {
+dpo_status launch_admit(SetRun& sr, int32_t* hlist, int32_t count, int32_t groups) {
   if (hipMemcpyAsync(sr.qlist, hlist, (size_t)(2 * count + 1) * 4, hipMemcpyHostToDevice,
                      sr.stream) != hipSuccess)
     return DPO_ERR_HIP;
   int32_t* dl = sr.qlist;
-  void* p1[] = {&sr.a, &dl, &count, &reset};
+  void* p1[] = {&sr.a, &dl, &count};
   if (hipLaunchKernel(admit_kernel_ptr(sr.problem), dim3((unsigned)groups), dim3(PB), p1, 0,
                       sr.stream) != hipSuccess)
     return DPO_ERR_HIP;
@@ -499,7 +499,7 @@ dpo_status admit(SetRun& sr, const Query* hq, int32_t nq, int32_t* hlist, int32_
   if (hipMemcpyAsync(sr.a.q, hq, (size_t)nq * sizeof(Query), hipMemcpyHostToDevice, sr.stream) !=
       hipSuccess)
     return DPO_ERR_HIP;
-  return launch_admit(sr, hlist, count, 0, admit_prefix(hq, hlist, count));
+  return launch_admit(sr, hlist, count, admit_prefix(hq, hlist, count));
 }
 
 dpo_status start_set(Runtime& r, SetRun& sr) {

@@ -71,8 +71,8 @@ constexpr uint32_t NARROW_FAR_EDGES = 1 << 13;
 // Bitmap words that go to LDS, beside half of NARROW_FRONT frontier entries or
 // more.
 constexpr int32_t NARROW_BITS = NARROW_WORDS - 4 * (NARROW_FRONT / 2);
-// Solo SSSP: vertices whose distances fit LDS beside 3,500 frontier entries or
-// more, and entries up to which one compute unit is faster than level steps on
+// Solo SSSP: vertices whose distances fit LDS beside 3,400 frontier entries or
+// more (3,481, with the two bit sets of the form with a bound), and entries up to which one compute unit is faster than level steps on
 // any graph (us, solo / level steps, 16,383 vertices and about 450,000 entries:
 // R-MAT 631 / 531, Erdos-Renyi 454 / 633).
 constexpr int32_t SOLO_VERTICES = 16384;
@@ -83,6 +83,7 @@ constexpr int32_t SOLO_EDGES = 1 << 18;
 constexpr int32_t SOLO_FAR_EDGES = 88 << 10;
 constexpr uint32_t SOLO_WORDS = 34 * 1024;
 constexpr uint32_t SOLO_FRONT = 4096;
+static_assert((SOLO_WORDS - 2 * (SOLO_VERTICES / 32) - SOLO_VERTICES) / 5 >= 3400, "solo frontier in LDS");
 // near-far SSSP: frontier entries, vertices (two bits each in LDS), edges of a
 // round, average weights by which the bound moves (a 301 x 257 road-like graph
 // takes 4.15 / 3.73 / 3.85 / 4.69 / 7.5 ms at 4 / 8 / 16 / 32 / 64)

@@ -648,7 +648,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
   if (TM) t_entry = realtime();
   PhaseClock<TM> pc;
   pc.start();
-  if (st->done || st->error || goes_bottom_up(st)) return;
+  if (st->done || st->error) return;
   const uint32_t L = st->base + step;
   LevelSet* prv = &st->set[(L + 2) % 3];  // fills of frontier L
   LevelSet* cur = &st->set[L % 3];        // this level: next-frontier fills, queues, groups
@@ -1314,7 +1314,7 @@ __global__ __launch_bounds__(PB) void child_kernel(Args a, uint32_t step) {
   if (TM) t_entry = realtime();
   PhaseClock<TM> pc;
   pc.start();
-  if (st->done || st->error || goes_bottom_up(st)) return;
+  if (st->done || st->error) return;
   const uint32_t L = st->base + step;
   LevelSet* cur = &st->set[L % 3];
   int32_t* fout = (L & 1) ? a.front0 : a.front1;
@@ -1514,7 +1514,7 @@ __global__ __launch_bounds__(PB) void harvest_kernel(Args a, uint32_t step) {
   if (TM) t_entry = realtime();
   PhaseClock<TM> pc;
   pc.start();
-  if (st->done || st->error || goes_bottom_up(st)) return;
+  if (st->done || st->error) return;
   const uint32_t L = st->base + step;
   LevelSet* cur = &st->set[L % 3];
   if (P == PROB_BFS && !(cur->vmode & 2u)) return;
@@ -3179,13 +3179,9 @@ __global__ __launch_bounds__(PB) void start_kernel(Args a, Query Q) {
 // their 32-slot chunks mapped to them.  Query list[k] is served by the
 // workgroups [pre[k], pre[k + 1]) (pre = list + count, a host-built prefix of
 // per-query workgroup counts proportional to n), so a batch of many small
-// queries does not leave most of the grid idle.  `reset` (host-known: every
-// earlier query has finished) also clears the level sets, whose fills are then
-// stale.
+// queries does not leave most of the grid idle.
 template <int P>
-__global__ __launch_bounds__(PB) void admit_kernel(Args a, const int32_t* list, int32_t count,
-                                                   int32_t reset) {
-  State* st = a.st;
+__global__ __launch_bounds__(PB) void admit_kernel(Args a, const int32_t* list, int32_t count) {
   const int32_t* pre = list + count;
   // query of this workgroup: largest k with pre[k] <= blockIdx.x
   int32_t lo = 0, hi = count;
@@ -3225,16 +3221,6 @@ __global__ __launch_bounds__(PB) void admit_kernel(Args a, const int32_t* list, 
       for (int k = 0; k < 8; ++k) f[k] = 0u;
       if (a.bound)
         for (int k = 0; k < 8; ++k) ((uint32_t*)a.bound)[(size_t)(s0 / 32 + i) * 8 + k] = ~0u;
-    }
-  }
-  if (reset) {
-    const uint32_t gsz = gridDim.x * PB;
-    const uint32_t gid = blockIdx.x * PB + threadIdx.x;
-    uint32_t* sw = (uint32_t*)&st->set[0];
-    for (uint32_t i = gid; i < 3 * sizeof(LevelSet) / 4; i += gsz) sw[i] = 0;
-    for (uint32_t i = gid; i < 3u * (uint32_t)a.ngroups_cap; i += gsz) {
-      a.grp_packed[i] = 0;
-      a.grp_done[i] = 0;
     }
   }
 }
