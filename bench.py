@@ -672,9 +672,10 @@ def summarize_profiles(args, d):
     md += [f"| {n} | {c} | {t / 1e6:.3f} | {t / c / 1e3:.2f} |" for n, (c, t) in top]
     md += ["", f"Traversals traced: {traversals}; level-step launches per traversal "
                f"{launches_per:.4g} (levels + 1).",
-           f"Level step (parent_kernel + child_kernel"
+           f"Level kernels' time per level-step launch (parent_kernel + child_kernel"
            f" + harvest_kernel{'; the parent kernel runs as two kernels, pass 1 before and pass 2 after the child kernel' if args.workload.startswith('sssp') else ''}"
-           f") kernel time per launch: **{kernel_us:.2f} us** "
+           f"{'' if args.workload.startswith('sssp') else '; narrow, bottom-up and symmetry kernels'}"
+           f"): **{kernel_us:.2f} us** "
            f"(bench line of the traced run: mean_launch_us {line['roofline']['mean_launch_us']}, "
            f"which also holds the gaps between graph nodes).", "",
            "## HBM traffic (`rocprofv3 --pmc FETCH_SIZE`, then `--pmc WRITE_SIZE`)", "",
@@ -796,43 +797,51 @@ def workload_line(args, dpo, torch, name, steps, warmup, with_cpu, with_baseline
     log(f"[bench] T+C+A: {gteps:.2f} GTEPS, {t_step_ms.mean():.3f} ms/step, wall {wall:.3f}s")
 
     # roofline of the level step: algorithmic bytes per launch / mean launch
-    # duration, both per traversal divided by its launch count.  The count is
-    # that of the level steps; the timed calls run narrow and bottom-up levels
-    # by other kernels, so only the quotient of the two is a rate.
+    # duration, both per traversal divided by its launch count.  SSSP of this
+    # size runs level steps only.  A timed BFS runs narrow and bottom-up levels
+    # by other kernels, which do not move a level step's bytes: its rates are
+    # null, and the counts are those of the run with counters (level steps).
+    steps_only = wl.kind == "sssp"
     launches = np.array([r[2]["levels"] + 1 for r in rs], dtype=np.float64)
     bytes_call = algorithmic_bytes(wl.kind, m_r, n_r)
     mean_call_ms = per_call.mean(axis=0)
     achieved = float((bytes_call.sum() / launches.sum()) /
                      ((mean_call_ms.sum() * 1e-3) / launches.sum()) / 1e9)
-    roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
+    roofline = {"bound": "hbm", "achieved": round(achieved, 1) if steps_only else None,
+                "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": round(achieved / HBM_PEAK_GBS, 4) if steps_only else None,
                 "traffic": measured_traffic(name, opts.label()),
                 "kernel": (f"level step: parent_kernel + child_kernel"
                            f"{' + parent_kernel pass 2' if wl.kind == 'sssp' else ''} + harvest_kernel "
                            f"<{wl.kind.upper()}, {opts.label()}>"),
                 "launches_per_traversal": float(launches.mean()),
-                "mean_launch_us": round(float(mean_call_ms.sum() / launches.sum() * 1e3), 2),
+                "mean_launch_us": (round(float(mean_call_ms.sum() / launches.sum() * 1e3), 2)
+                                   if steps_only else None),
                 "algorithmic_bytes_per_launch": round(float(bytes_call.sum() / launches.sum()))}
 
     # second roofline: the child body's dependent random probes (BFS: the
     # n-bit visited bitmap; SSSP: the n-word distance array), one per edge
     # run, against the rate the chip sustains for random 4-byte loads from a
-    # table of that size (measured here, 8 loads in flight per lane).  A BFS
-    # whose wide levels go bottom-up probes fewer, so its share may pass 1.
+    # table of that size (measured here, 8 loads in flight per lane).  Null for
+    # a BFS, as above, and for SSSP with bound bytes (from 3 * 2^19 vertices on),
+    # most of whose probes are of a byte each instead.
+    words_probed = steps_only and wl.g.n < 3 << 19
     probed_bytes = wl.g.n // 8 if wl.kind == "bfs" else 4 * wl.g.n
     table = 1 << max(12, int(np.ceil(np.log2(max(probed_bytes, 1)))))
     ceiling = random_load_rate(torch, table)
     probes = np.array([r[2]["edges_serial"] + r[2]["edges_child"] for r in rs], dtype=np.float64)
     p_rate = float((probes.sum() / launches.sum()) / ((mean_call_ms.sum() * 1e-3) / launches.sum()))
     counters = measured_traffic(name, opts.label(), "l2_requests_per_s")
-    roofline_probe = {"bound": "random 4-byte loads", "achieved": round(p_rate / 1e9, 2),
+    roofline_probe = {"bound": "random 4-byte loads",
+                      "achieved": round(p_rate / 1e9, 2) if words_probed else None,
                       "peak": round(ceiling / 1e9, 2), "unit": "G loads/s",
-                      "frac": round(p_rate / ceiling, 4),
+                      "frac": round(p_rate / ceiling, 4) if words_probed else None,
                       "table_bytes": table, "probes_per_traversal": float(probes.mean()),
                       "child_l2_requests_per_s_counters": counters,
                       "hbm_frac_cap": round(float(bytes_call.sum() / probes.sum()) * ceiling / 1e9
                                             / HBM_PEAK_GBS, 4)}
-    log(f"[bench] probes {p_rate / 1e9:.1f} G/s of {ceiling / 1e9:.1f} G/s measured ceiling")
+    log(f"[bench] {probes.mean():.0f} edges run per traversal (run with counters); random loads "
+        f"{ceiling / 1e9:.1f} G/s measured")
 
     baselines = {}
     if with_baselines:
