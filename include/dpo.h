@@ -83,7 +83,7 @@ typedef struct {
   int32_t agg_blocks;       /* k >= 2 for DPO_AGG_MULTIBLOCK (e.g. 4 or 16)         */
   int32_t child_block;      /* original child block size bDim in {64, 128, 256}    */
   int32_t steps_per_replay; /* level steps per HIP-graph replay; 0 = 16 (batch
-                               calls 8).  A single
+                               calls 8 on dense graphs).  A single
                                traversal that needs no replays (nested, aggregated,
                                without counters) launches its steps as they come
                                due instead; results are the same               */

@@ -263,6 +263,34 @@ static void batch_symmetry(bool symmetric) {
   for (const char* k : {"tally", "words", "bottom_up_queries"}) CHECK(F.launched[k] == (symmetric ? kBatchSteps : 0));
 }
 
+// A batch's replays by default: short ones, two at a time from the third on, on a
+// dense graph; long ones on a sparse one, or as the options say.
+static void batch_replays() {
+  const int32_t n = 1000;
+  std::vector<int32_t> vbase{0, n}, rp(n + 1), col(1 << 14), out(1024);
+  std::vector<uint32_t> w(1 << 14);
+  dpo_query q{0, 0, 0};
+  struct { int32_t m, steps, k, at_once; } forms[] = {{1 << 14, 0, 8, 2}, {2000, 0, 16, 1}, {1 << 14, 8, 8, 1}, {1 << 14, 4, 4, 1}};
+  for (auto& f : forms) {
+    dpo_arena ar{1, vbase.data(), {n, f.m, rp.data(), col.data(), w.data()}};
+    dpo_options o;
+    dpo_default_options(&o);
+    o.steps_per_replay = f.steps;
+    std::vector<char> ws(dpo_batch_workspace_bytes(&ar, &q, 1, &o));
+    auto ends = std::make_shared<int>(0);  // replays run
+    F.kernels["advance"] = [=](void** p) -> std::function<void()> {
+      uint32_t* flags = *(uint32_t**)p[2];
+      return [=] { flags[1] = ++*ends >= 5; };
+    };
+    F.launched.clear();
+    CHECK(dpo_sssp_batch(&ar, &q, 1, &o, 1, (uint32_t*)out.data(), ws.data(), ws.size(), nullptr, nullptr) == DPO_OK);
+    CHECK(F.launched["advance"] == (f.at_once == 2 ? 6 : 5));  // 1, 1, 2, 2
+    CHECK(F.launched["parent"] == F.launched["advance"] * f.k);
+    std::lock_guard<std::mutex> lock(rt().mu);
+    rt().graphs.clear();  // their nodes keep this form's counter
+  }
+}
+
 // An engine's replays have bottom-up nodes while its running queries are enough
 // work, whatever it has served before, and none once its arena is known to be
 // asymmetric.
@@ -316,6 +344,7 @@ int main(int argc, char** argv) {
   else if (name == "stale_unposted") stale_verdict_unposted();
   else if (name == "wide_run") wide_run(false);
   else if (name == "wide_run_noalloc") wide_run(true);
+  else if (name == "batch_replays") batch_replays();
   else if (name == "batch_symmetric") batch_symmetry(true);
   else if (name == "batch_directed") batch_symmetry(false);
   else if (name == "engine_symmetric") engine_symmetry(true);

@@ -50,3 +50,7 @@ def test_bottom_up_nodes_only_where_they_pay(checks, name):
     """A batch's or an engine's replays have them only on arenas found symmetric;
     an engine's only while the running queries are enough work."""
     _run(checks, name)
+
+
+def test_replays_of_a_batch(checks):
+    _run(checks, "batch_replays")
