@@ -117,6 +117,12 @@ constexpr uint32_t BU_ALPHA = 16;
 // 2,040).  One-copy levels are slow enough for bottom-up ones to win all the same
 // (the band 1,080 without this, 1,460 with it).
 constexpr uint32_t BU_VAIN = 8;
+// A query of several: found less than 1 / BU_QUERY_FEW, then 1 / BU_QUERY_VAIN (us,
+// never / 4 and 4 / 8 and 4 / 8 and 2 / 2 and 2: 24 queries served over 40 layers of
+// 8,000 vertices 4,560 / 3,080 / 3,180 / 2,960 / 2,870, a batch over 100 layers of
+// 2,000 4,530 / 4,160 / 4,150 / 4,045 / 4,035, 512 over R-MAT graphs 1,795 / 1,845 /
+// 1,815 / 1,805 / 1,965).
+constexpr uint32_t BU_QUERY_FEW = 8, BU_QUERY_VAIN = 2;
 // Queries go bottom-up if they have this many entries together.  Measured (us, top-down /
 // bottom-up): batches of 2.4 M entries 228 / 280, 12 M 420 / 465, 19 M 390 / 390 and 449 /
 // 456, 30 M 676 / 602, 50 M 700 / 618; served queries of 13 M 333 / 412, 15 M 365 / 447,

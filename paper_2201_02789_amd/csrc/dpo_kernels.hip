@@ -524,14 +524,32 @@ __device__ __forceinline__ bool goes_bottom_up(const State* st) {
 }
 
 // Does query q go bottom-up at level L?  Its frontier's edges against those it
-// has not run, as for a single traversal (BU_ALPHA).  The tallies do not change
-// between the tally kernel of a level and the next level's.
+// has not run, as for a single traversal (BU_ALPHA; BU_QUERY_FEW, BU_QUERY_VAIN).  The tallies do not
+// change between the tally kernel of a level and the next level's, except that the
+// words kernel of a level, by then the only one to ask, finds out whether the level
+// before went bottom-up in vain and marks the query with it (ask: 0, or 1 there).
+constexpr uint32_t IN_VAIN = 1u << 31;  // in a query's fourth tally, beside its edges
+
+__device__ __forceinline__ bool share_goes_bottom_up(uint32_t E, uint32_t before, uint32_t graph) {
+  const uint32_t m = graph & ~IN_VAIN;
+  return E >= BU_QUERY_EDGES &&
+         (uint64_t)E * (graph & IN_VAIN ? BU_QUERY_VAIN : BU_ALPHA) >= (m > before ? m - before : 0u);
+}
+
+template <bool ASK>
 __device__ __forceinline__ bool query_goes_bottom_up(const Args& a, uint32_t q, uint32_t L) {
-  const uint32_t* t = a.tally;
+  uint32_t* t = a.tally;
   const uint32_t nq = (uint32_t)a.nq, E = t[(L & 1) * nq + q];
   if (E < BU_QUERY_EDGES) return false;
-  const uint32_t before = t[2 * nq + q] - E, m = t[3 * nq + q];
-  return (uint64_t)E * BU_ALPHA >= (m > before ? m - before : 0u);
+  const uint32_t before = t[2 * nq + q] - E;
+  uint32_t graph = t[3 * nq + q];
+  if (ASK) {
+    const uint32_t last = t[((L + 1) & 1) * nq + q], m = graph & ~IN_VAIN;
+    // (as another workgroup finds it if this one has written it already)
+    if (share_goes_bottom_up(last, before - last, graph) && (uint64_t)E * BU_QUERY_FEW < (m > before ? m - before : 0u))
+      t[3 * nq + q] = graph |= IN_VAIN;
+  }
+  return share_goes_bottom_up(E, before, graph);
 }
 
 // Append one aggregated grid to descriptor queue q (one lane).
@@ -711,7 +729,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
 
   if (by_query)
     for (int i = tid; i < (a.nq + 63) / 64 * 64; i += PB) {
-      const unsigned long long m = __ballot(i < a.nq && query_goes_bottom_up(a, (uint32_t)i, L));
+      const unsigned long long m = __ballot(i < a.nq && query_goes_bottom_up<false>(a, (uint32_t)i, L));
       if ((lane & 31) == 0) s_up[i >> 5] = (uint32_t)(m >> (lane & 32));
     }
 
@@ -2893,7 +2911,7 @@ __global__ __launch_bounds__(QB) void bottom_up_words_kernel(Args a, uint32_t st
   uint32_t count = 0;
   for (int q0 = 0; q0 < a.nq; q0 += QB) {
     const int q = q0 + tid;
-    const bool on = q < a.nq && query_goes_bottom_up(a, (uint32_t)q, L);
+    const bool on = q < a.nq && query_goes_bottom_up<true>(a, (uint32_t)q, L);
     const unsigned long long m = __ballot(on);
     if (lane == 0) s_sum[0][wave] = (uint32_t)__popcll(m);
     __syncthreads();

@@ -61,3 +61,35 @@ def test_levels_match_oracle(name, widths, deg, shuffle, one_way):
             out.fill_(-7)
             call()
             assert np.array_equal(out.cpu().numpy(), want), (name, o)
+
+
+def test_queries_over_layers():
+    """A batch and an engine with enough work for bottom-up queries, whose bottom-up
+    levels find little: each query goes back to top-down and up again near its end."""
+    gs = [_layers([1] + [4000] * 12, 9, 1)[0], _layers([1, 500] + [6000] * 8, 9, 2, shuffle=True)[0],
+          gg.rmat(14, 24, 7, perm_seed=3)]
+    ar, vbase = gg.pack_arena(gs)
+    da = dpo.DeviceArena(ar, vbase)
+    rng = np.random.default_rng(6)
+    qs = [(k, int(rng.choice(np.flatnonzero(gs[k].degrees())))) for k in (0, 1, 2) * 14]
+    want = [oracle.bfs(gs[k], s)[0] for k, s in qs]
+    for o in (dict(), dict(threshold=16, coarsen=1, steps_per_replay=3)):
+        opts = dpo.Options(**o)
+        tot, slot0 = dpo.dpo_batch_slots(da, qs)
+        out = torch.full((tot,), -7, dtype=torch.int32, device="cuda")
+        ws = torch.full((dpo.dpo_batch_workspace_bytes(da, qs, opts),), 0xC3, dtype=torch.uint8, device="cuda")
+        dpo.dpo_bfs_batch(da, qs, [opts], out, ws)
+        host = out.cpu().numpy()
+        for i, (k, s) in enumerate(qs):
+            assert np.array_equal(host[slot0[i]:slot0[i] + gs[k].n], want[i]), (o, i)
+        eng = dpo.Engine(da, "bfs", [opts], max_queries=64, max_slots=1 << 22)
+        outs = [torch.full((gs[k].n,), -9, dtype=torch.int32, device="cuda") for k, _ in qs]
+        for (k, s), t in zip(qs, outs):
+            eng.submit(k, s, t)
+        for _ in range(2000):
+            if eng.step() == (0, 0):
+                break
+        assert len(eng.poll()) == len(qs)
+        for w, t in zip(want, outs):
+            assert np.array_equal(t.cpu().numpy(), w), o
+        eng.close()
