@@ -109,7 +109,7 @@ static void stale_verdict_unposted() {
   CHECK(F.launched["parent"] == 1);
 }
 
-// A run of wide levels takes half as many level steps at a time as it has had;
+// A run of wide levels takes as many level steps at a time as it has had;
 // a narrow or bottom-up level in between ends the run.
 static void wide_run(bool noalloc) {
   Single s(5000, 10);
@@ -129,8 +129,11 @@ static void wide_run(bool noalloc) {
   };
   CHECK((noalloc ? dpo_bfs_noalloc(&s.g, 0, &s.o, (int32_t*)s.out.data(), nullptr) : s.bfs()) == DPO_OK);
   const uint32_t B = AFTER_BOTTOM_UP;
-  CHECK((*after == std::vector<uint32_t>{0, 1, 1, 1, 1, 2, 3, 1, 1, B, B, 1, 1}));
-  CHECK((*steps == std::vector<uint32_t>{0, 0, 0, 0, 0, 1, 0, 1, 2, 0, 0, 0, 0}));
+  CHECK((*after == std::vector<uint32_t>{0, 1, 1, 2, 4, 8, 16, 1, 1, B, B, 1, 1}));
+  std::vector<uint32_t> expected;
+  for (uint32_t k : {1, 1, 2, 4, 8, 16, 1, 1, 1, 1})
+    for (uint32_t i = 0; i < k; ++i) expected.push_back(i);
+  CHECK(*steps == expected);
 }
 
 // An engine over graphs of the given sizes whose replays end every query.
