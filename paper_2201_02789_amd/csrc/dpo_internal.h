@@ -109,14 +109,21 @@ constexpr uint32_t AFTER_BOTTOM_UP = ~0u;
 // 386 / 382 / 382 / 584, a batch of 512 1,860 / 1,824 / 1,903 / 2,085; R-MAT of
 // scale 22 618 / 472 / 472.
 constexpr uint32_t BU_ALPHA = 16;
-// Once a bottom-up level has found less than 1 / BU_VAIN of the edges left, it has
-// run most rows to their ends in vain, and the graph is one of many wide levels:
-// those that would be split levels top-down then need that share to go bottom-up
-// (us, never / 4 / 8: 30 layers of 100,000 vertices 1,200 / 1,090 / 1,060, a band
-// of 1 M vertices 855 / 820 / 805, a 100^3 grid of 26 neighbours 2,025 / 2,090 /
-// 2,040).  One-copy levels are slow enough for bottom-up ones to win all the same
-// (the band 1,080 without this, 1,460 with it).
-constexpr uint32_t BU_VAIN = 8;
+// The edges left count what the search never reaches, and rows that end without a
+// visited neighbour are read whole.  So before the symmetry check, and when the
+// frontier has less than 1 / BU_SURE of the edges left, a sample of the unvisited
+// vertices (sample_row) says how many entries the level would read, and how many
+// edges those have that it finds: twice the entries read are to be at most BU_READ
+// times the frontier's edges and the found vertices' together, and all entries, which
+// the check reads, at most BU_CHECK times.  One-copy levels are slow enough for the
+// larger factors.  Us, top-down only / without the sample / with it: R-MAT of scale
+// 20 beside another, beside 3, beside 7 445 / 655 / 420, 450 / 1,235 / 420, 470 /
+// 1,690 / 425; 30 layers of 100,000 vertices 975 / 1,200 / 1,000, a 100^3 grid of 26
+// neighbours 2,650 / 2,025 / 1,950; R-MAT of scale 20 450 / 245 / 245, Erdos-Renyi of
+// 1 M, degree 24, 408 / 275 / 280 (BU_READ 2 / 3 / 5 of the entries against the
+// frontier's edges alone: 340 / 300 / 280, but two R-MAT graphs 412 / 473 / 641); a
+// band of 1 M vertices in one-copy levels 1,400 / 1,065 / 1,120.
+constexpr uint32_t BU_SURE = 8, BU_READ = 1, BU_READ_ONE_COPY = 16, BU_CHECK = 5, BU_CHECK_ONE_COPY = 40;
 // A query of several: found less than 1 / BU_QUERY_FEW, then 1 / BU_QUERY_VAIN (us,
 // never / 4 and 4 / 8 and 4 / 8 and 2 / 2 and 2: 24 queries served over 40 layers of
 // 8,000 vertices 4,560 / 3,080 / 3,180 / 2,960 / 2,870, a batch over 100 layers of
@@ -187,8 +194,7 @@ struct State {
   unsigned long long sym_sum[8];  // symmetry check: shares of the signed sum
   unsigned long long plan_edges;  // edges of the level planned last, not in run_edges yet
   uint32_t asymmetric;  // symmetry check: met an id out of range
-  uint32_t in_vain;     // a bottom-up level found less than 1 / BU_VAIN of the edges left
-  uint32_t pad[30];
+  uint32_t pad[31];
   LevelSet set[3];
 };
 

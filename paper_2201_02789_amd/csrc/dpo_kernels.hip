@@ -1704,6 +1704,35 @@ __device__ __forceinline__ bool lacks_reverse(const Args& a, uint32_t n, uint32_
   return missing;
 }
 
+// Entries that a bottom-up level would read of the row of a vertex drawn by h (0 if
+// it is visited), and its degree if it would be found.  The first SAMPLE_ROW entries
+// are looked at; a row without a visited neighbour among them counts in full.
+__device__ __forceinline__ void sample_row(const Args& a, uint32_t n, const uint32_t* vis, uint32_t h,
+                                           uint32_t& read, uint32_t& found) {
+  constexpr uint32_t SAMPLE_ROW = 16;
+  h = (h ^ h >> 15) * 0x85EBCA6Bu;
+  h ^= h >> 13;
+  const uint32_t v = (uint32_t)((uint64_t)h * n >> 32);
+  const uint32_t b = (uint32_t)a.rp[v], e = (uint32_t)a.rp[v + 1];
+  read = found = 0;
+  if (vis[v >> 5] >> (v & 31) & 1u || b >= e || e > (uint32_t)a.m) return;
+  uint32_t t[SAMPLE_ROW];
+#pragma unroll
+  for (uint32_t u = 0; u < SAMPLE_ROW; ++u) t[u] = min((uint32_t)a.col[min(b + u, e - 1)], n - 1);
+  pin(t);
+#pragma unroll
+  for (uint32_t u = 0; u < SAMPLE_ROW; ++u) t[u] = vis[t[u] >> 5] >> (t[u] & 31) & 1u;
+  pin(t);
+  const uint32_t deg = min(e - b, 1u << 20);
+  read = deg;
+#pragma unroll
+  for (uint32_t u = SAMPLE_ROW; u-- > 0;)
+    if (t[u]) {
+      read = min(u + 1, deg);
+      found = deg;
+    }
+}
+
 // after: what ran since the last launch: so many level steps, or AFTER_BOTTOM_UP.
 // LDS: the visited bits are in LDS.
 template <bool LDS>
@@ -1724,7 +1753,6 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
   // (a planned level's edges count once it has run, however often it is planned,
   // and for those of the level steps behind it)
   unsigned long long run_edges = st->run_edges + adv * st->plan_edges, plan_edges = 0;
-  uint32_t in_vain = st->in_vain;
   uint32_t L = st->base + adv;
   const uint32_t n = (uint32_t)a.q[0].n, T = (uint32_t)a.q[0].T;
   if (tid == 0) sh.bad = 0;
@@ -1943,9 +1971,35 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     for (uint32_t w = 0; w < NB / 64; ++w) E += sh.wsum[w];
     if (F > NB) E = E * F / NB;
     const unsigned long long left = (unsigned long long)a.m > run_edges ? a.m - run_edges : 0;
-    in_vain |= adv && after == AFTER_BOTTOM_UP && E * BU_VAIN < left;
-    const uint32_t alpha = in_vain && F >= (uint32_t)a.split_min ? BU_VAIN : BU_ALPHA;
-    if (symmetric != 2 && E * alpha >= left) {
+    bool pays = symmetric != 2 && E * BU_ALPHA >= left;
+    if (pays && (!symmetric || E * BU_SURE < left)) {
+      // what the level would read, and find, from an unvisited vertex per thread
+      uint32_t read, found;
+      sample_row(a, n, vis, (L * NB + tid) * 0x9E3779B1u, read, found);
+#pragma unroll
+      for (int o = 32; o; o >>= 1) {
+        read += (uint32_t)__shfl_xor((int)read, o, 64);
+        found += (uint32_t)__shfl_xor((int)found, o, 64);
+      }
+      __syncthreads();
+      if (lane == 0) {
+        sh.wsum[wave] = read;
+        sh.wrows[wave] = found;
+      }
+      __syncthreads();
+      unsigned long long S = 0, H = 0;
+#pragma unroll
+      for (uint32_t w = 0; w < NB / 64; ++w) {
+        S += sh.wsum[w];
+        H += sh.wrows[w];
+      }
+      S = S * n / NB;
+      H = H * n / NB;
+      const bool one_copy = F < (uint32_t)a.split_min;
+      pays = S * 2 <= (E + H) * (one_copy ? BU_READ_ONE_COPY : BU_READ) &&
+             (symmetric || (unsigned long long)a.m <= (E + H) * (one_copy ? BU_CHECK_ONE_COPY : BU_CHECK));
+    }
+    if (pays) {
       code = V_BOTTOM_UP;
       if (!symmetric) {
         // (on the directed graphs one meets a few entries tell)
@@ -1965,7 +2019,6 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     st->symmetric = symmetric;
     st->run_edges = run_edges;
     st->plan_edges = plan_edges;
-    st->in_vain = in_vain;
     if (L != L0) {
       st->vsel[L & 1] = c;
       st->vstale[L & 1] = 1u;

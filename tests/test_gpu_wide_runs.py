@@ -93,3 +93,19 @@ def test_queries_over_layers():
         for w, t in zip(want, outs):
             assert np.array_equal(t.cpu().numpy(), w), o
         eng.close()
+
+
+@pytest.mark.parametrize("parts", [2, 5])
+@pytest.mark.parametrize("o", [dict(split_min=2048, child_block=128, threshold=64, coarsen=1), dict()], ids=str)
+def test_beside_what_the_search_never_reaches(parts, o):
+    """Several graphs in one CSR, isolated vertices among them: bottom-up levels would
+    read the rows of the others."""
+    gs = [gg.rmat(15, 20, k, perm_seed=k + 3) for k in range(parts)]
+    ar, vbase = gg.pack_arena(gs)
+    dg = dpo.DeviceGraph.from_host(ar)
+    opts = dpo.Options(**o)
+    ws = dpo.alloc_workspace(dg, opts)
+    out = torch.full((ar.n,), -7, dtype=torch.int32, device="cuda")
+    for s in [int(vbase[k]) + gg.max_degree_vertex(gs[k]) for k in range(parts)] + [int(np.flatnonzero(ar.degrees() == 0)[0])]:
+        dpo.dpo_bfs(dg, s, opts, out, ws)
+        assert np.array_equal(out.cpu().numpy(), oracle.bfs(ar, s)[0]), s
