@@ -422,7 +422,7 @@ dpo_status prepare_set(Runtime& r, int problem, const dpo_csr* g, const dpo_opti
   a.desc_cap = lay.desc_cap;
   a.fcap = lay.fcap;
   a.count_stats = count_stats ? 1 : 0;
-  static_assert(4 * MAX_QUERIES * 4 <= MAX_GRID * NSTAT * 8, "the tallies take the counters' place");
+  static_assert(TALLIES * MAX_QUERIES * 4 < MAX_GRID * NSTAT * 8, "the tallies take the counters' place");
   a.bottom_up = by_query && hint ? BU_QUERIES : BU_OFF;
   a.tally = (uint32_t*)(base + lay.stats);
   sr->qlist = (int32_t*)(base + lay.qlist);
@@ -547,8 +547,8 @@ dpo_status launch_symmetry(Runtime& r, SetRun& sr, const uint32_t* vbase = nullp
 // the tallies holds, which stays unchecked.
 dpo_status check_symmetry(Runtime& r, SetRun& sr, const int32_t* graph_vbase, int32_t ngraphs,
                           uint32_t ticket, uint32_t* verdict, bool* asked) {
-  uint32_t* vbase = sr.a.tally + 4 * sr.a.nq;
-  *asked = (size_t)(4 * sr.a.nq + ngraphs + 1) * 4 <= (size_t)MAX_GRID * NSTAT * 8;
+  uint32_t* vbase = sr.a.tally + TALLIES * sr.a.nq;
+  *asked = (size_t)(TALLIES * sr.a.nq + ngraphs + 1) * 4 <= (size_t)MAX_GRID * NSTAT * 8;
   if (!*asked) return DPO_OK;
   // (pageable memory: copied before the call returns)
   if (hipMemcpyAsync(vbase, graph_vbase, (size_t)(ngraphs + 1) * 4, hipMemcpyHostToDevice, sr.stream) !=

@@ -124,12 +124,13 @@ constexpr uint32_t BU_ALPHA = 16;
 // frontier's edges alone: 340 / 300 / 280, but two R-MAT graphs 412 / 473 / 641); a
 // band of 1 M vertices in one-copy levels 1,400 / 1,065 / 1,120.
 constexpr uint32_t BU_SURE = 8, BU_READ = 1, BU_READ_ONE_COPY = 16, BU_CHECK = 5, BU_CHECK_ONE_COPY = 40;
-// A query of several: found less than 1 / BU_QUERY_FEW, then 1 / BU_QUERY_VAIN (us,
-// never / 4 and 4 / 8 and 4 / 8 and 2 / 2 and 2: 24 queries served over 40 layers of
-// 8,000 vertices 4,560 / 3,080 / 3,180 / 2,960 / 2,870, a batch over 100 layers of
-// 2,000 4,530 / 4,160 / 4,150 / 4,045 / 4,035, 512 over R-MAT graphs 1,795 / 1,845 /
-// 1,815 / 1,805 / 1,965).
-constexpr uint32_t BU_QUERY_FEW = 8, BU_QUERY_VAIN = 2;
+// For a query of several, whose rows are read for up to BU_GROUP queries at once (us,
+// top-down only / without the sample / with it at 1 / 3 / 10: 64 over 8 graphs of 8
+// R-MAT graphs each 528 / 822 / 569 / 569 / 701, served 854 / 900 / 640 / 641 / 792; 48
+// over 6 of 4 631 / 738 / 597 / 677 / 732; 24 served over 40 layers of 8,000 vertices
+// 2,412 / 4,570 / 2,925 / 3,165 / 4,365; 512 over R-MAT graphs 5,905 / 1,795 / 1,785 /
+// 1,790 / 1,820; 32 over 4 of 2 1,088 / 901 / 999 / 1,011 / 938).
+constexpr uint32_t BU_QUERY_READ = 1;
 // Queries go bottom-up if they have this many entries together.  Measured (us, top-down /
 // bottom-up): batches of 2.4 M entries 228 / 280, 12 M 420 / 465, 19 M 390 / 390 and 449 /
 // 456, 30 M 676 / 602, 50 M 700 / 618; served queries of 13 M 333 / 412, 15 M 365 / 447,
@@ -271,11 +272,14 @@ struct Args {
   int32_t bottom_up;               // wide BFS levels may go bottom-up (with Args::hint):
                                    // BU_SINGLE as the narrow kernel plans, BU_QUERIES each
                                    // query's by its tallied edges
-  uint32_t* tally;                 // BU_QUERIES: [nq] each: edges of the frontier at an even
-                                   // level, at an odd one, of all levels tallied, of the graph;
-                                   // then the arena's graph_vbase for the symmetry check (all
+  uint32_t* tally;                 // BU_QUERIES: [nq] each (TALLIES): edges of the frontier at an
+                                   // even level, at an odd one, of all levels tallied, of the
+                                   // graph; entries a bottom-up level would read, edges it would
+                                   // find; then the arena's graph_vbase for the symmetry check (all
                                    // in the place of Args::stats, whose counters are off)
 };
+
+constexpr int TALLIES = 6;
 
 enum { BU_OFF = 0, BU_SINGLE = 1, BU_QUERIES = 2 };
 

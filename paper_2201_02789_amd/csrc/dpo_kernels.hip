@@ -524,32 +524,16 @@ __device__ __forceinline__ bool goes_bottom_up(const State* st) {
 }
 
 // Does query q go bottom-up at level L?  Its frontier's edges against those it
-// has not run, as for a single traversal (BU_ALPHA; BU_QUERY_FEW, BU_QUERY_VAIN).  The tallies do not
-// change between the tally kernel of a level and the next level's, except that the
-// words kernel of a level, by then the only one to ask, finds out whether the level
-// before went bottom-up in vain and marks the query with it (ask: 0, or 1 there).
-constexpr uint32_t IN_VAIN = 1u << 31;  // in a query's fourth tally, beside its edges
-
-__device__ __forceinline__ bool share_goes_bottom_up(uint32_t E, uint32_t before, uint32_t graph) {
-  const uint32_t m = graph & ~IN_VAIN;
-  return E >= BU_QUERY_EDGES &&
-         (uint64_t)E * (graph & IN_VAIN ? BU_QUERY_VAIN : BU_ALPHA) >= (m > before ? m - before : 0u);
-}
-
-template <bool ASK>
+// has not run, and against what the level would read and find, as for a single
+// traversal (BU_ALPHA, BU_QUERY_READ).  The tallies do not change between the tally
+// kernel of a level and the next level's.
 __device__ __forceinline__ bool query_goes_bottom_up(const Args& a, uint32_t q, uint32_t L) {
-  uint32_t* t = a.tally;
+  const uint32_t* t = a.tally;
   const uint32_t nq = (uint32_t)a.nq, E = t[(L & 1) * nq + q];
   if (E < BU_QUERY_EDGES) return false;
-  const uint32_t before = t[2 * nq + q] - E;
-  uint32_t graph = t[3 * nq + q];
-  if (ASK) {
-    const uint32_t last = t[((L + 1) & 1) * nq + q], m = graph & ~IN_VAIN;
-    // (as another workgroup finds it if this one has written it already)
-    if (share_goes_bottom_up(last, before - last, graph) && (uint64_t)E * BU_QUERY_FEW < (m > before ? m - before : 0u))
-      t[3 * nq + q] = graph |= IN_VAIN;
-  }
-  return share_goes_bottom_up(E, before, graph);
+  const uint32_t before = t[2 * nq + q] - E, m = t[3 * nq + q];
+  return (uint64_t)E * BU_ALPHA >= (m > before ? m - before : 0u) &&
+         (uint64_t)t[4 * nq + q] * 2 <= ((uint64_t)E + t[5 * nq + q]) * BU_QUERY_READ;
 }
 
 // Append one aggregated grid to descriptor queue q (one lane).
@@ -729,7 +713,7 @@ __global__ __launch_bounds__(PB) void parent_kernel(Args a, uint32_t step) {
 
   if (by_query)
     for (int i = tid; i < (a.nq + 63) / 64 * 64; i += PB) {
-      const unsigned long long m = __ballot(i < a.nq && query_goes_bottom_up<false>(a, (uint32_t)i, L));
+      const unsigned long long m = __ballot(i < a.nq && query_goes_bottom_up(a, (uint32_t)i, L));
       if ((lane & 31) == 0) s_up[i >> 5] = (uint32_t)(m >> (lane & 32));
     }
 
@@ -1707,18 +1691,19 @@ __device__ __forceinline__ bool lacks_reverse(const Args& a, uint32_t n, uint32_
 // Entries that a bottom-up level would read of the row of a vertex drawn by h (0 if
 // it is visited), and its degree if it would be found.  The first SAMPLE_ROW entries
 // are looked at; a row without a visited neighbour among them counts in full.
-__device__ __forceinline__ void sample_row(const Args& a, uint32_t n, const uint32_t* vis, uint32_t h,
-                                           uint32_t& read, uint32_t& found) {
+// vbase, n: the graph's vertices; vis: their bits.
+__device__ __forceinline__ void sample_row(const Args& a, uint32_t vbase, uint32_t n, const uint32_t* vis,
+                                           uint32_t h, uint32_t& read, uint32_t& found) {
   constexpr uint32_t SAMPLE_ROW = 16;
   h = (h ^ h >> 15) * 0x85EBCA6Bu;
   h ^= h >> 13;
   const uint32_t v = (uint32_t)((uint64_t)h * n >> 32);
-  const uint32_t b = (uint32_t)a.rp[v], e = (uint32_t)a.rp[v + 1];
+  const uint32_t b = (uint32_t)a.rp[vbase + v], e = (uint32_t)a.rp[vbase + v + 1];
   read = found = 0;
   if (vis[v >> 5] >> (v & 31) & 1u || b >= e || e > (uint32_t)a.m) return;
   uint32_t t[SAMPLE_ROW];
 #pragma unroll
-  for (uint32_t u = 0; u < SAMPLE_ROW; ++u) t[u] = min((uint32_t)a.col[min(b + u, e - 1)], n - 1);
+  for (uint32_t u = 0; u < SAMPLE_ROW; ++u) t[u] = min((uint32_t)a.col[min(b + u, e - 1)] - vbase, n - 1);
   pin(t);
 #pragma unroll
   for (uint32_t u = 0; u < SAMPLE_ROW; ++u) t[u] = vis[t[u] >> 5] >> (t[u] & 31) & 1u;
@@ -1975,7 +1960,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     if (pays && (!symmetric || E * BU_SURE < left)) {
       // what the level would read, and find, from an unvisited vertex per thread
       uint32_t read, found;
-      sample_row(a, n, vis, (L * NB + tid) * 0x9E3779B1u, read, found);
+      sample_row(a, 0, n, vis, (L * NB + tid) * 0x9E3779B1u, read, found);
 #pragma unroll
       for (int o = 32; o; o >>= 1) {
         read += (uint32_t)__shfl_xor((int)read, o, 64);
@@ -2875,7 +2860,8 @@ __global__ __launch_bounds__(PB) void bottom_up_kernel(Args a) {
 // Tally: the degrees of a sample of the frontier, 64 consecutive entries of
 // every `stride` * 64 so that about TALLY_SAMPLE are read.  The entries of a
 // wave are mostly one query's (the harvest appends in slot order): they are
-// summed by the wave, else in LDS.
+// summed by the wave, else in LDS.  Then a wave per running query samples the rows
+// that a bottom-up level would read.
 __global__ __launch_bounds__(PB) void tally_kernel(Args a, uint32_t step) {
   __shared__ uint32_t s_fpre[NQF + 2];
   __shared__ uint32_t s_edges[MAX_QUERIES];
@@ -2894,6 +2880,22 @@ __global__ __launch_bounds__(PB) void tally_kernel(Args a, uint32_t step) {
   __syncthreads();
   const uint32_t F = s_fpre[NQF + 1];
   if (F < TALLY_MIN || F > (uint32_t)a.slots) return;
+  for (uint32_t q = blockIdx.x * NW + wave; q < (uint32_t)a.nq; q += gridDim.x * NW) {
+    const Query Q = a.q[q];
+    if (Q.n <= 0 || Q.last + 1 < (int32_t)L) continue;
+    uint32_t read, found;
+    sample_row(a, (uint32_t)Q.vbase, (uint32_t)Q.n, a.visit + ((uint32_t)Q.slot0 >> 5),
+               (L * 64u + (uint32_t)lane + 1) * 0x9E3779B1u, read, found);
+#pragma unroll
+    for (int o = 32; o; o >>= 1) {
+      read += (uint32_t)__shfl_xor((int)read, o, 64);
+      found += (uint32_t)__shfl_xor((int)found, o, 64);
+    }
+    if (lane == 0) {
+      a.tally[4 * a.nq + q] = (uint32_t)min((uint64_t)read * (uint32_t)Q.n / 64u, (uint64_t)0xFFFFFFFFu);
+      a.tally[5 * a.nq + q] = (uint32_t)min((uint64_t)found * (uint32_t)Q.n / 64u, (uint64_t)0xFFFFFFFFu);
+    }
+  }
   const int32_t* fin = (L & 1) ? a.front1 : a.front0;
   const uint32_t stride = ceil_div(F, TALLY_SAMPLE);
   for (uint32_t c = blockIdx.x * NW + wave; c * stride * 64u < F; c += gridDim.x * NW) {
@@ -2964,7 +2966,7 @@ __global__ __launch_bounds__(QB) void bottom_up_words_kernel(Args a, uint32_t st
   uint32_t count = 0;
   for (int q0 = 0; q0 < a.nq; q0 += QB) {
     const int q = q0 + tid;
-    const bool on = q < a.nq && query_goes_bottom_up<true>(a, (uint32_t)q, L);
+    const bool on = q < a.nq && query_goes_bottom_up(a, (uint32_t)q, L);
     const unsigned long long m = __ballot(on);
     if (lane == 0) s_sum[0][wave] = (uint32_t)__popcll(m);
     __syncthreads();

@@ -64,14 +64,15 @@ def test_levels_match_oracle(name, widths, deg, shuffle, one_way):
 
 
 def test_queries_over_layers():
-    """A batch and an engine with enough work for bottom-up queries, whose bottom-up
-    levels find little: each query goes back to top-down and up again near its end."""
+    """A batch and an engine with enough work for bottom-up queries, of which some go
+    bottom-up near their end, some on their wide levels and some, beside what they
+    never reach, not at all."""
     gs = [_layers([1] + [4000] * 12, 9, 1)[0], _layers([1, 500] + [6000] * 8, 9, 2, shuffle=True)[0],
-          gg.rmat(14, 24, 7, perm_seed=3)]
+          gg.rmat(14, 24, 7, perm_seed=3), gg.pack_arena([gg.rmat(13, 24, k, perm_seed=k) for k in range(4)])[0]]
     ar, vbase = gg.pack_arena(gs)
     da = dpo.DeviceArena(ar, vbase)
     rng = np.random.default_rng(6)
-    qs = [(k, int(rng.choice(np.flatnonzero(gs[k].degrees())))) for k in (0, 1, 2) * 14]
+    qs = [(k, int(rng.choice(np.flatnonzero(gs[k].degrees())))) for k in (0, 1, 2, 3) * 14]
     want = [oracle.bfs(gs[k], s)[0] for k, s in qs]
     for o in (dict(), dict(threshold=16, coarsen=1, steps_per_replay=3)):
         opts = dpo.Options(**o)
