@@ -259,7 +259,7 @@ LEVEL_KERNELS = ("parent_kernel", "child_kernel", "harvest_kernel", "narrow_kern
 START_KERNELS = ("init_kernel", "start_kernel")  # one per traversal set
 KERNEL_SOURCES = ["paper_2201_02789_amd/csrc/dpo_kernels.hip",
                   "paper_2201_02789_amd/csrc/dpo_host.hip",
-                  "paper_2201_02789_amd/csrc/dpo_internal.h"]
+                  "paper_2201_02789_amd/csrc/dpo_internal.h", "paper_2201_02789_amd/csrc/dpo_pair.h"]
 
 
 def kernel_sources_sha():
