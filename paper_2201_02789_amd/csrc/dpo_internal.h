@@ -123,6 +123,10 @@ constexpr uint32_t BU_ALPHA = 16;
 // 1 M, degree 24, 408 / 275 / 280 (BU_READ 2 / 3 / 5 of the entries against the
 // frontier's edges alone: 340 / 300 / 280, but two R-MAT graphs 412 / 473 / 641); a
 // band of 1 M vertices in one-copy levels 1,400 / 1,065 / 1,120.
+// Vertices in it, 34 random accesses each, of which a compute unit makes about one a
+// ns: of 1,024 the launch takes 13 us longer on an Erdos-Renyi graph of 2 M vertices, of
+// 256 4; of 128 an R-MAT of scale 20 beside another takes 560 us instead of 405.
+constexpr uint32_t BU_SAMPLES = 256;
 constexpr uint32_t BU_SURE = 8, BU_READ = 1, BU_READ_ONE_COPY = 16, BU_CHECK = 5, BU_CHECK_ONE_COPY = 40;
 // For a query of several, whose rows are read for up to BU_GROUP queries at once (us,
 // top-down only / without the sample / with it at 1 / 3 / 10: 64 over 8 graphs of 8

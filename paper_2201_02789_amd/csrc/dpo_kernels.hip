@@ -1958,9 +1958,9 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
     const unsigned long long left = (unsigned long long)a.m > run_edges ? a.m - run_edges : 0;
     bool pays = symmetric != 2 && E * BU_ALPHA >= left;
     if (pays && (!symmetric || E * BU_SURE < left)) {
-      // what the level would read, and find, from an unvisited vertex per thread
-      uint32_t read, found;
-      sample_row(a, 0, n, vis, (L * NB + tid) * 0x9E3779B1u, read, found);
+      // what the level would read, and find, from some of its vertices
+      uint32_t read = 0, found = 0;
+      if (tid < BU_SAMPLES) sample_row(a, 0, n, vis, (L * NB + tid) * 0x9E3779B1u, read, found);
 #pragma unroll
       for (int o = 32; o; o >>= 1) {
         read += (uint32_t)__shfl_xor((int)read, o, 64);
@@ -1978,8 +1978,8 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
         S += sh.wsum[w];
         H += sh.wrows[w];
       }
-      S = S * n / NB;
-      H = H * n / NB;
+      S = S * n / BU_SAMPLES;
+      H = H * n / BU_SAMPLES;
       const bool one_copy = F < (uint32_t)a.split_min;
       pays = S * 2 <= (E + H) * (one_copy ? BU_READ_ONE_COPY : BU_READ) &&
              (symmetric || (unsigned long long)a.m <= (E + H) * (one_copy ? BU_CHECK_ONE_COPY : BU_CHECK));
