@@ -2027,7 +2027,7 @@ __global__ __launch_bounds__(NARROW_BLOCK) void narrow_kernel(Args a, uint32_t a
 // half of the entries have been run it is lifted, as what is left is many levels
 // of few edges.  8,191 vertices, 204,000 entries, weights up to 255: 14 levels and
 // 2 new bounds instead of 13 levels, a third of the edges; level steps 422 us,
-// level order 356, with the bound 195 (never lifted 227; moved to 1.25 or 2 times
+// level order 356, with the bound 195 (other seeds 180 to 265; never lifted 227; moved to 1.25 or 2 times
 // the least distance 277 / 272).  16,383 vertices, 245,000 entries 459 -> 261.
 // Equal weights gain nothing and pay for the two bit sets: 131 -> 145.
 struct SoloLds {
@@ -2597,7 +2597,9 @@ __global__ __launch_bounds__(NARROW_BLOCK) void near_kernel(Args a, uint32_t src
 // sets that were looked for.  The key is drawn anew for each check.  An id out of
 // range counts as asymmetric, and so does a row that ends before it starts or rows
 // that are not those of a.m entries: what a level step reports of them, a bottom-up
-// level would not.
+// level would not.  Bound by its instructions (three quarter-rate multiply-adds an
+// entry among them) and the adjacency stream together: scale 22, 513 MB in 157 us,
+// 3.3 TB/s.
 //
 // A wave runs an even share of the entries in slices of 64 * U, the next slice's
 // loads issued before a slice is summed; the rows come in windows of 64.
@@ -2769,7 +2771,7 @@ __global__ __launch_bounds__(PB) void symmetry_kernel(Args a, uint32_t n, const 
 // entries, then by the wave together.  Bound by the lines its row heads lie in:
 // scale 22's growing, widest and next level take 59, 23 and 11 us where a level
 // step takes 270 (growing) and 540 (widest), so that with the check, once per
-// traversal, the traversal goes from 1083 to 484 us.
+// traversal, the traversal goes from 1083 to 484 us (454 since).
 __global__ __launch_bounds__(PB) void bottom_up_kernel(Args a) {
   __shared__ int32_t s_stage[NW][STAGE];
   __shared__ uint32_t s_bc[NW + 8];
