@@ -336,7 +336,9 @@ dpo_status dpo_engine_create(const dpo_arena* arena, int32_t kind, const dpo_opt
                              void* stream, dpo_engine** engine);
 
 /* Queue a query: `out` is a device array of n_g entries written before the
- * ticket is reported by dpo_engine_poll.  DPO_ERR_CAPACITY if the graph can
+ * ticket is reported by dpo_engine_poll (word-aligned memory of the engine's
+ * device by one kernel for all that finish together, any other memory by a copy
+ * command each).  DPO_ERR_CAPACITY if the graph can
  * never fit in max_slots. */
 dpo_status dpo_engine_submit(dpo_engine* e, int32_t graph, int32_t source, void* out,
                              uint64_t* ticket);
